@@ -75,7 +75,7 @@ std::array<DevBuf*, Workspace::kNumBuffers> Workspace::buffers() {
           &inc_F, &inc_L0, &inc_Ll, &inc_B0, &inc_B1, &inc_bm, &inc_wl0, &inc_wl1, &scan_tmp,
           &deferred_work, &deferred_done, &rank, &rk_key0, &rk_key1, &rk_val0, &rk_val1, &rk_deg0,
           &rk_deg1, &rk_tmp, &gr_rp, &gr_ci, &gr_cnt, &gr_init, &own_rp, &own_ci, &pair_set, &inc_T8,
-          &inc_done};
+          &inc_done, &inc_core};
 }
 
 void Workspace::release() {
@@ -731,18 +731,70 @@ int run_incremental(Call& c, const GraphView& g, const KeySource& k, const int32
   };
   bool tail_on = !(c.P.flags & COLOR_FLAG_NO_TAIL) && tail_blocks_resident() > 0;
   const int64_t tail_at = c.P.tail_threshold > 0 ? c.P.tail_threshold : kTailDefault;
+  // worklists of at most core_at vertices go to the core kernels
+  const int64_t core_at = std::min<int64_t>(
+      tail_at, core_capacity(std::min(core_blocks_resident(), std::max(8, c.P.max_workgroups))));
+  bool core_on = tail_on && core_at > 0;
   int local = 0;
   int R = std::max(1, c.P.rounds_per_poll);
   int64_t prev_total = 0;
   int prev_local = 0;
+  const int cap = max_rounds > 0 ? max_rounds : INT_MAX;
+  static_assert(offsetof(Scalars, tail_left) == offsetof(Scalars, bar) + sizeof(Scalars::bar) + sizeof(int32_t),
+                "barrier words and tail flags are cleared together");
+  // What a cooperative launch left: its error bits and flag, the rounds done
+  // and the next worklist's counts.
+  auto after_launch = [&]() -> int {
+    c.launches += 1;
+    if (hipMemcpyAsync(&H->tail_err, &S->tail_err, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, c.st) != hipSuccess ||
+        hipMemcpyAsync(H, S, offsetof(Scalars, max_split_work), hipMemcpyDeviceToHost, c.st) != hipSuccess)
+      return COLOR_EHIP;
+    return hipStreamSynchronize(c.st) == hipSuccess ? COLOR_OK : COLOR_EHIP;
+  };
   while (true) {
     int64_t total = 0;
     for (int i = 0; i < kBins; ++i) total += known[i];
     if (total == 0) break;
     if (max_rounds > 0 && local >= max_rounds) return COLOR_ENOCONVERGE;
+    if (core_on && total <= core_at) {
+      const int32_t left = static_cast<int32_t>(total);
+      // without its scratch the rounds go on in the tail kernel
+      core_on = w->inc_core.ensure(core_scratch_bytes(left), false, c.st) == COLOR_OK;
+      if (core_on) {
+        const IncBufs b = round_bufs(local + 1);
+        if (hipMemsetAsync(S->bar, 0, sizeof(S->bar) + 2 * sizeof(int32_t), c.st) != hipSuccess) return COLOR_EHIP;
+        if (c.timing && c.record_event(2)) return COLOR_EHIP;
+        if (launch_core(k, b, IL, known, left, b.A_in == b.A_out, local + 1, cap, w->inc_core.p, S->bar, &S->tail_err,
+                        &S->tail_left, c.P.tail_checkin_us, c.st)) {
+          if (c.timing && c.record_event(-1)) return COLOR_EHIP;
+          c.launches += core_launches(left) - 1;
+          if ((e = after_launch())) return e;
+          const int32_t bits = H->tail_err & ~kErrCoreHanded;
+          // a wait gave up, or the launch ended part-way: the outputs are not valid
+          if ((bits & kErrTailBarrier) || (bits && bits != H->tail_err)) return kRcRetryNoTail;
+          if (bits == kErrTailCheckin) {
+            // its workgroups were not all resident, the tail's would not be
+            // either: per-round launches from here on
+            c.tail_fallbacks += 1;
+            core_on = tail_on = false;
+            continue;
+          }
+          if (bits) {  // kErrCoreWindow
+            core_on = false;  // it changed nothing: the tail kernel runs the rounds
+            continue;
+          }
+          c.tail_rounds += std::max(0, H->rounds_done - round0 - local);
+          return H->tail_left ? COLOR_ENOCONVERGE : COLOR_OK;
+        }
+        // cooperative launch refused
+        (void)hipGetLastError();
+        if (c.timing) c.event_kind.back() = -1;
+        core_on = false;
+      }
+    }
     if (tail_on && total <= tail_at) {
-      // the remaining rounds in one cooperative launch: no launch gaps and no
-      // host polls between the (small) rounds of the tail
+      // small rounds in one cooperative launch: no launch gaps and no host
+      // polls between them, down to the core kernel's size
       int64_t g = std::max<int64_t>((total + kBlock - 1) / kBlock, inc_round_units(known, IL));
       g = std::min<int64_t>(g, std::min(tail_blocks_resident(), std::max(8, c.P.max_workgroups)));
       if (g >= 8) g = g / 8 * 8;
@@ -756,36 +808,32 @@ int run_incremental(Call& c, const GraphView& g, const KeySource& k, const int32
       set.A0 = A0;
       set.uniform1 = init ? 0 : 1;
       set.defer1 = init ? 0 : 1;
-      static_assert(offsetof(Scalars, tail_left) == offsetof(Scalars, bar) + sizeof(Scalars::bar) + sizeof(int32_t),
-                    "barrier words and tail flags are cleared together");
       if (hipMemsetAsync(S->bar, 0, sizeof(S->bar) + 2 * sizeof(int32_t), c.st) != hipSuccess) return COLOR_EHIP;
-      const int cap = max_rounds > 0 ? max_rounds : INT_MAX;
       if (c.timing && c.record_event(2)) return COLOR_EHIP;
-      if (launch_inc_tail(k, set, IL, local + 1, cap, S->bar, &S->tail_err, &S->tail_left,
-                          static_cast<int>(std::max<int64_t>(1, g)), c.P.tail_checkin_us, c.st)) {
+      if (launch_inc_tail(k, set, IL, local + 1, cap, core_on ? static_cast<int32_t>(core_at) : 0, S->bar,
+                          &S->tail_err, &S->tail_left, static_cast<int>(std::max<int64_t>(1, g)),
+                          c.P.tail_checkin_us, c.st)) {
         if (c.timing && c.record_event(-1)) return COLOR_EHIP;
-        c.launches += 1;
-        if (hipMemcpyAsync(&H->tail_err, &S->tail_err, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, c.st) !=
-                hipSuccess ||
-            hipMemcpyAsync(&H->rounds_done, &S->rounds_done, sizeof(int32_t), hipMemcpyDeviceToHost, c.st) !=
-                hipSuccess)
-          return COLOR_EHIP;
-        if (hipStreamSynchronize(c.st) != hipSuccess) return COLOR_EHIP;
+        if ((e = after_launch())) return e;
         if (H->tail_err == kErrTailCheckin) {
           // its workgroups were not all resident: it ran nothing, so the
           // rounds go on from the same state as per-round launches
           c.tail_fallbacks += 1;
-          tail_on = false;
+          core_on = tail_on = false;
           continue;
         }
         if (H->tail_err) return kRcRetryNoTail;  // a grid barrier gave up: the outputs are not valid
-        c.tail_rounds = std::max(0, H->rounds_done - round0 - local);
-        return H->tail_left ? COLOR_ENOCONVERGE : COLOR_OK;
+        const int done = std::max(local, H->rounds_done - round0);
+        c.tail_rounds += done - local;
+        local = done;
+        if (H->tail_left) return COLOR_ENOCONVERGE;
+        for (int i = 0; i < kBins; ++i) known[i] = H->cnt[local & 1][i];
+        continue;
       }
       // cooperative launch refused: per-round launches from here on
       (void)hipGetLastError();
       if (c.timing) c.event_kind.back() = -1;
-      tail_on = false;
+      core_on = tail_on = false;
     }
     int64_t gc = std::min<int64_t>((total + kBlock - 1) / kBlock, resident);
     if (gc >= 8) gc = gc / 8 * 8;

@@ -5,6 +5,7 @@
 #include <mutex>
 #include <vector>
 
+#include "core.hpp"
 #include "graphcolor.h"
 #include "inc.hpp"
 #include "keys.hpp"
@@ -63,6 +64,7 @@ struct Workspace {
   DevBuf deferred, inc_len, inc_words, inc_fwoff, inc_aoff, inc_F, inc_L0, inc_Ll, inc_B0, inc_B1, inc_bm, scan_tmp;
   DevBuf inc_wl0, inc_wl1;  // incremental engine: worklists binned by active-list length
   DevBuf inc_T8, inc_done;  // incremental engine: tentative colors as bytes, committed bits
+  DevBuf inc_core;          // incremental engine: the core kernel's vertex order and exchange words
   DevBuf deferred_work, deferred_done;  // setup: per heavy D2/PD2 vertex, its work and slices done
   DevBuf rank, rk_key0, rk_key1, rk_val0, rk_val1, rk_deg0, rk_deg1, rk_tmp;  // recolorDegrees ranks
   DevBuf gr_rp, gr_ci, gr_cnt, gr_init;  // tentative ghost recoloring: local CSR with ghost rows, start colors
@@ -72,7 +74,7 @@ struct Workspace {
   std::vector<hipEvent_t> events;  // pool for COLOR_FLAG_KERNEL_TIMING
   ~Workspace();
   void release();
-  static constexpr int kNumBuffers = 47;
+  static constexpr int kNumBuffers = 48;
   std::array<DevBuf*, kNumBuffers> buffers();   // every DevBuf above
 };
 
@@ -97,7 +99,7 @@ struct Call {
   size_t n_events = 0;
   std::vector<int> event_kind;  // per event pair start index: 0 color, 1 detect, 2 tail, -1 none
   int color_launches = 0, detect_launches = 0;
-  int tail_rounds = 0;  // rounds run by the incremental engine's tail kernel
+  int tail_rounds = 0;  // rounds run by the incremental engine's tail and core kernels
   int tail_fallbacks = 0;  // tail launches that found their workgroups not all resident
   bool user_bins = false;  // the caller set degree-bin bounds
   int engine = 1;

@@ -93,13 +93,15 @@ constexpr int kBarWords = kBarState + 32;
 constexpr int32_t kTailDefault = 32768;     // default worklist size at which the tail kernel takes over
 
 void launch_inc_color(const IncBufs& b, const BinLayout& L, int round, int grid, hipStream_t st);
-// All remaining rounds in one cooperative launch (grid <= tail_blocks_resident());
-// false if the runtime refused the launch.
+// The rounds from round0 on in one cooperative launch (grid <= tail_blocks_resident()),
+// until a worklist of at most stop_at vertices is left; false if the runtime refused the launch.
 // checkin_us: how long the workgroups wait for each other at entry (< 0: not
 // at all); if they are not all resident by then, none runs a round and *err
 // receives kErrTailCheckin.
 bool launch_inc_tail(const KeySource& k, const IncRoundSet& set, const BinLayout& L, int round0, int round_cap,
-                    uint32_t* bar, int32_t* err, int32_t* left, int grid, int32_t checkin_us, hipStream_t st);
+                    int32_t stop_at, uint32_t* bar, int32_t* err, int32_t* left, int grid, int32_t checkin_us,
+                    hipStream_t st);
+uint64_t wall_clock_khz();  // ticks of wall_clock64 per millisecond
 // Workgroups of the tail kernel that fit on the device at once (-1: unknown).
 int tail_blocks_resident();
 void launch_inc_detect(const KeySource& k, const IncBufs& b, const BinLayout& L, int round, int grid,
