@@ -102,6 +102,7 @@ struct Call {
   int tail_rounds = 0;  // rounds run by the incremental engine's tail and core kernels
   int tail_fallbacks = 0;  // tail launches that found their workgroups not all resident
   bool user_bins = false;  // the caller set degree-bin bounds
+  bool user_lanes = false; // the caller set lanes per vertex
   int engine = 1;
   int record_event(int kind_of_next);  // records the next pool event on st
 };
@@ -113,6 +114,7 @@ constexpr int kRcRetryNoTail = -1000;
 void default_params(int mode, color_params* p);
 int degree_rank(Call& c, int32_t m, const int32_t* deg_ptr, int32_t n_rows, const int32_t* extra_deg, KeySource& k);
 void incremental_bins(int mode, int32_t bin_hi[4]);
+void pull_lanes(int32_t lanes[3]);
 int validate_job(const color_job& j, void* stream);
 int merge_params(int mode, const color_params* user, color_params* out);
 int begin_call(Call& c, int mode, const color_params* user, color_stats* stats, void* stream, int32_t n,

@@ -117,7 +117,7 @@ __device__ __forceinline__ int64_t job_vertex_work(const GraphView& g, int32_t v
 
 // Setup A: static work, initial colors, per-bin counts.
 template <int MODE, int LD>
-__device__ void setup_a_unit(BatchJob* J, const JobView& V, const BatchTune& t, int32_t u, int32_t* s_bc) {
+__device__ __forceinline__ void setup_a_unit(BatchJob* J, const JobView& V, const BatchTune& t, int32_t u, int32_t* s_bc) {
   const int tid = threadIdx.x;
   const int wave = tid / kWave;
   const int32_t v = u * kBlock + tid;
@@ -146,7 +146,7 @@ __device__ void setup_a_unit(BatchJob* J, const JobView& V, const BatchTune& t, 
 
 // Setup B: every vertex into its bin's region of W_1 (order within a bin is
 // arbitrary; the result does not depend on it).
-__device__ void setup_b_unit(BatchJob* J, const JobView& V, const BatchTune& t, int32_t u, int32_t* s_bc,
+__device__ __forceinline__ void setup_b_unit(BatchJob* J, const JobView& V, const BatchTune& t, int32_t u, int32_t* s_bc,
                              int32_t* s_base) {
   const int tid = threadIdx.x;
   const int wave = tid / kWave;
@@ -229,33 +229,33 @@ __device__ __forceinline__ void round_units(BatchJob* J, const JobView& V, const
       const int G = bin == 0 ? t.lanes[0] : (bin == 1 ? t.lanes[1] : t.lanes[2]);
       if (!detect) {
         switch (G) {
-          case 1: color_chunk_group<MODE, 1, LD>(g, b, wl, cnt, work_acc); break;
-          case 2: color_chunk_group<MODE, 2, LD>(g, b, wl, cnt, work_acc); break;
-          case 4: color_chunk_group<MODE, 4, LD>(g, b, wl, cnt, work_acc); break;
-          case 8: color_chunk_group<MODE, 8, LD>(g, b, wl, cnt, work_acc); break;
-          case 16: color_chunk_group<MODE, 16, LD>(g, b, wl, cnt, work_acc); break;
-          case 32: color_chunk_group<MODE, 32, LD>(g, b, wl, cnt, work_acc); break;
-          default: color_chunk_group<MODE, 64, LD>(g, b, wl, cnt, work_acc); break;
+          case 1: color_chunk_group<MODE, 1, LD, 1>(g, b, wl, cnt, work_acc); break;
+          case 2: color_chunk_group<MODE, 2, LD, 1>(g, b, wl, cnt, work_acc); break;
+          case 4: color_chunk_group<MODE, 4, LD, 1>(g, b, wl, cnt, work_acc); break;
+          case 8: color_chunk_group<MODE, 8, LD, 1>(g, b, wl, cnt, work_acc); break;
+          case 16: color_chunk_group<MODE, 16, LD, 1>(g, b, wl, cnt, work_acc); break;
+          case 32: color_chunk_group<MODE, 32, LD, 1>(g, b, wl, cnt, work_acc); break;
+          default: color_chunk_group<MODE, 64, LD, 1>(g, b, wl, cnt, work_acc); break;
         }
       } else {
         const int32_t oo = sh.off[bin];
         switch (G) {
-          case 1: detect_chunk_group<MODE, 1, LD>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
-          case 2: detect_chunk_group<MODE, 2, LD>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
-          case 4: detect_chunk_group<MODE, 4, LD>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
-          case 8: detect_chunk_group<MODE, 8, LD>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
-          case 16: detect_chunk_group<MODE, 16, LD>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
-          case 32: detect_chunk_group<MODE, 32, LD>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
-          default: detect_chunk_group<MODE, 64, LD>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
+          case 1: detect_chunk_group<MODE, 1, LD, 1>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
+          case 2: detect_chunk_group<MODE, 2, LD, 1>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
+          case 4: detect_chunk_group<MODE, 4, LD, 1>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
+          case 8: detect_chunk_group<MODE, 8, LD, 1>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
+          case 16: detect_chunk_group<MODE, 16, LD, 1>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
+          case 32: detect_chunk_group<MODE, 32, LD, 1>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
+          default: detect_chunk_group<MODE, 64, LD, 1>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
         }
       }
     } else {
       const int32_t v = ld_dev(&b.wl_in[sh.off[3] + (uu - light)]);
       if (!detect) {
-        color_vertex_block<MODE, LD>(g, b, v, sh.ovf, sh.red, &sh.misc[0]);
+        color_vertex_block<MODE, LD, 1>(g, b, v, sh.ovf, sh.red, &sh.misc[0]);
         if (threadIdx.x == 0) work_acc += static_cast<uint64_t>(ld_dev(&b.work[v]));
       } else {
-        detect_vertex_block<MODE, LD>(g, k, b, v, sh.off[3], maxc_acc);
+        detect_vertex_block<MODE, LD, 1>(g, k, b, v, sh.off[3], maxc_acc);
       }
     }
     __syncthreads();

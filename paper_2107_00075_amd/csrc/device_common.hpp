@@ -123,12 +123,25 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
                                    __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
 }
 
+// x of another lane of its row of 16, by a DPP control word (no LDS access).
+template <int CTRL>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t x) {
+  const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(x), CTRL, 0xf, 0xf, true));
+  const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(x >> 32), CTRL, 0xf, 0xf, true));
+  return static_cast<uint64_t>(hi) << 32 | lo;
+}
+
 // OR of a 64-bit value over aligned groups of G lanes (all lanes of a group
-// must be active).
+// must be active).  Within a row of 16 lanes by DPP: neighbours, pairs, then
+// the mirrored half row and row (whose lanes hold equal values by then).
 template <int G>
 __device__ __forceinline__ uint64_t group_or(uint64_t x) {
-#pragma unroll
-  for (int off = 1; off < G; off <<= 1) x |= __shfl_xor(x, off, kWave);
+  if constexpr (G >= 2) x |= dpp_u64<0xB1>(x);    // quad_perm 1,0,3,2
+  if constexpr (G >= 4) x |= dpp_u64<0x4E>(x);    // quad_perm 2,3,0,1
+  if constexpr (G >= 8) x |= dpp_u64<0x141>(x);   // row_half_mirror
+  if constexpr (G >= 16) x |= dpp_u64<0x140>(x);  // row_mirror
+  if constexpr (G >= 32) x |= __shfl_xor(x, 16, kWave);
+  if constexpr (G >= 64) x |= __shfl_xor(x, 32, kWave);
   return x;
 }
 

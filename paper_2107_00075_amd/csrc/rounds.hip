@@ -28,7 +28,7 @@
 // merge their windows into a global per-vertex bitset; the last workgroup to
 // arrive picks the color or commits (the edge-split parallelism that the
 // paper's edge-based kernel provides for very high degrees, Section 3.2).
-// Light bins are cut into chunks of 256 worklist entries that workgroups take
+// Light bins are cut into chunks of worklist entries that workgroups take
 // by a static XCD-aware partition (no device atomics on the hot path; one
 // atomic per chunk appends the chunk's losers); heavy units are taken
 // dynamically from a device counter afterwards.
@@ -40,11 +40,15 @@
 namespace gcol {
 
 // Per-round work map, built once per workgroup in LDS.  Light bins (0..2) are
-// cut into chunks of kBlock worklist entries that workgroups take by a static,
-// XCD-aware partition; heavy units (one per bin-3 vertex, split_chunks per
+// cut into chunks of up to kBlock worklist entries that workgroups take by a
+// static, XCD-aware partition.  A chunk of a small bin holds only as many
+// passes of the workgroup's lane groups as the grid needs: a full chunk of a
+// 64-lane bin is 64 passes one after the other, which left a round of a few
+// hundred wide vertices on one or two workgroups.  Heavy units (one per bin-3 vertex, split_chunks per
 // bin-4 vertex) are taken dynamically from a device counter afterwards.
 struct RoundMap {
   int32_t cnt[kBins];
+  int32_t csize[3];      // worklist entries per chunk of bins 0..2
   int32_t chunks[3];
   int32_t light_total;
   int32_t heavy_block;   // units of bin 3
@@ -55,7 +59,8 @@ __device__ __forceinline__ void make_round_map(const RoundBufs& b, const BinLayo
   int32_t lt = 0;
   for (int i = 0; i < kBins; ++i) m.cnt[i] = atomic_load_i32(&b.cnt_in[i]);
   for (int i = 0; i < 3; ++i) {
-    m.chunks[i] = (m.cnt[i] + kBlock - 1) / kBlock;
+    m.csize[i] = round_chunk_size(m.cnt[i], L.lanes[i], static_cast<int32_t>(gridDim.x));
+    m.chunks[i] = (m.cnt[i] + m.csize[i] - 1) / m.csize[i];
     lt += m.chunks[i];
   }
   m.light_total = lt;
@@ -73,21 +78,21 @@ __device__ __forceinline__ void light_chunk(const RoundMap& m, int32_t c, int& b
     c -= m.chunks[bin];
     ++bin;
   }
-  first = c * kBlock;
-  count = min(kBlock, m.cnt[bin] - first);
+  first = c * m.csize[bin];
+  count = min(m.csize[bin], m.cnt[bin] - first);
 }
 
 // ---------------------------------------------------------------------------
 // color: one chunk of a split vertex
 // ---------------------------------------------------------------------------
 template <int MODE>
-__device__ void color_split_chunk(const GraphView& g, const RoundBufs& b, const BinLayout& L,
+__device__ __forceinline__ void color_split_chunk(const GraphView& g, const RoundBufs& b, const BinLayout& L,
                                   int32_t si, int chunk, uint32_t* ovf, uint64_t* red,
                                   int32_t* s_misc, uint64_t& work_acc) {
   const int tid = threadIdx.x;
   const int wave = tid / kWave;
   const int nch = L.split_chunks;
-  const int32_t v = ld_dev(&b.split_vertex[si]);
+  const int32_t v = ld_mut<0>(&b.split_vertex[si]);
   const int32_t rb = g.rp[v], re = g.rp[v + 1];
   const int64_t len = re - rb;
   const int32_t cb = rb + static_cast<int32_t>(len * chunk / nch);
@@ -99,8 +104,7 @@ __device__ void color_split_chunk(const GraphView& g, const RoundBufs& b, const 
   for (int w = tid; w < kOvfWords; w += kBlock) ovf[w] = 0u;
   __syncthreads();
   uint64_t m = 0;
-  scan_nbhd<MODE>(g, v, cb, ce, tid, kBlock, [&](int32_t u) {
-    const int32_t c = ld_dev(&C[u]);
+  scan_nbhd<MODE>(g, v, cb, ce, tid, kBlock, [&](int32_t u) __attribute__((always_inline)) { return ld_mut<0>(&C[u]); }, [&](int32_t c) __attribute__((always_inline)) {
     if (c <= 0) return false;
     uint32_t d = static_cast<uint32_t>(c - 1);  // bit c-1 stands for color c
     if (d < 64u) {
@@ -120,7 +124,7 @@ __device__ void color_split_chunk(const GraphView& g, const RoundBufs& b, const 
     m = red[0] | red[1] | red[2] | red[3];
     if (static_cast<uint32_t>(m)) atomicOr(&gm[0], static_cast<uint32_t>(m));
     if (m >> 32) atomicOr(&gm[1], static_cast<uint32_t>(m >> 32));
-    if (chunk == 0) work_acc += static_cast<uint64_t>(ld_dev(&b.work[v]));
+    if (chunk == 0) work_acc += static_cast<uint64_t>(ld_mut<0>(&b.work[v]));
   }
   for (int w = tid; w < kOvfWords && 2 + w < b.capw; w += kBlock) {
     const uint32_t x = ovf[w];
@@ -211,12 +215,12 @@ __global__ __launch_bounds__(kBlock) void color_round_kernel(GraphView g, KeySou
       __syncthreads();
       if (u >= M.heavy_total) break;
       if (u < M.heavy_block) {
-        const int32_t v = ld_dev(&b.wl_in[L.off[kBlockBin] + u]);
+        const int32_t v = ld_mut<0>(&b.wl_in[L.off[kBlockBin] + u]);
         color_vertex_block<MODE>(g, b, v, ovf, red, &s_misc[0]);
-        if (threadIdx.x == 0) work_acc += static_cast<uint64_t>(ld_dev(&b.work[v]));
+        if (threadIdx.x == 0) work_acc += static_cast<uint64_t>(ld_mut<0>(&b.work[v]));
       } else {
         const int32_t us = u - M.heavy_block;
-        const int32_t si = ld_dev(&b.wl_in[L.off[kSplitBin] + us / L.split_chunks]);
+        const int32_t si = ld_mut<0>(&b.wl_in[L.off[kSplitBin] + us / L.split_chunks]);
         color_split_chunk<MODE>(g, b, L, si, us % L.split_chunks, ovf, red, s_misc, work_acc);
       }
     }
@@ -228,28 +232,27 @@ __global__ __launch_bounds__(kBlock) void color_round_kernel(GraphView g, KeySou
 }
 
 template <int MODE>
-__device__ void detect_split_chunk(const GraphView& g, const KeySource& k, const RoundBufs& b,
+__device__ __forceinline__ void detect_split_chunk(const GraphView& g, const KeySource& k, const RoundBufs& b,
                                    const BinLayout& L, int32_t si, int chunk, int32_t* s_misc,
                                    int32_t& maxc_acc) {
   const int tid = threadIdx.x;
   const int nch = L.split_chunks;
-  const int32_t v = ld_dev(&b.split_vertex[si]);
+  const int32_t v = ld_mut<0>(&b.split_vertex[si]);
   const int32_t rb = g.rp[v], re = g.rp[v + 1];
   const int64_t len = re - rb;
   const int32_t cb = rb + static_cast<int32_t>(len * chunk / nch);
   const int32_t ce = rb + static_cast<int32_t>(len * (chunk + 1) / nch);
   const int32_t* __restrict__ T = b.T;
-  const int32_t tv = ld_dev(&T[v]);
+  const int32_t tv = ld_mut<0>(&T[v]);
   const uint64_t kv = key_of(k, v);
   bool lose = false;
   if (atomic_load_u32(&b.split_flag[si]) == 0u) {  // another chunk may already have decided
-    scan_nbhd<MODE>(g, v, cb, ce, tid, kBlock, [&](int32_t u) {
-      if (key_of(k, u) > kv && ld_dev(&T[u]) == tv) {
-        lose = true;
-        return true;
-      }
-      return false;
-    });
+    scan_nbhd<MODE>(g, v, cb, ce, tid, kBlock,
+                    [&](int32_t u) __attribute__((always_inline)) { return key_of(k, u) > kv ? ld_mut<0>(&T[u]) : 0; },
+                    [&](int32_t c) __attribute__((always_inline)) {
+                      lose = lose || c == tv;
+                      return lose;
+                    });
   }
   lose = __syncthreads_or(lose);
   if (tid == 0 && lose) atomicOr(&b.split_flag[si], 1u);
@@ -318,11 +321,11 @@ __global__ __launch_bounds__(kBlock) void detect_round_kernel(GraphView g, KeySo
       __syncthreads();
       if (u >= M.heavy_total) break;
       if (u < M.heavy_block) {
-        const int32_t v = ld_dev(&b.wl_in[L.off[kBlockBin] + u]);
+        const int32_t v = ld_mut<0>(&b.wl_in[L.off[kBlockBin] + u]);
         detect_vertex_block<MODE>(g, k, b, v, L.off[kBlockBin], maxc_acc);
       } else {
         const int32_t us = u - M.heavy_block;
-        const int32_t si = ld_dev(&b.wl_in[L.off[kSplitBin] + us / L.split_chunks]);
+        const int32_t si = ld_mut<0>(&b.wl_in[L.off[kSplitBin] + us / L.split_chunks]);
         detect_split_chunk<MODE>(g, k, b, L, si, us % L.split_chunks, s_misc, maxc_acc);
       }
     }

@@ -68,11 +68,21 @@ template <int MODE>
 void launch_detect_round(const GraphView& g, const KeySource& k, const RoundBufs& b,
                          const BinLayout& L, int round, int grid, hipStream_t st);
 
-// Workgroups a round kernel can use for the given per-bin counts: light
-// chunks of kBlock entries plus heavy units.
+// Worklist entries per chunk of a bin of cnt vertices with `lanes` lanes each:
+// as few passes of kBlock / lanes vertices as give every workgroup of the
+// grid a chunk, at most kBlock entries.
+__host__ __device__ inline int32_t round_chunk_size(int32_t cnt, int32_t lanes, int32_t grid) {
+  const int32_t per = kBlock / lanes;
+  const int64_t pass = static_cast<int64_t>(per) * grid;
+  const int64_t k = (cnt + pass - 1) / pass;
+  return k >= lanes ? kBlock : k > 1 ? per * static_cast<int32_t>(k) : per;
+}
+
+// Workgroups a round kernel can use for the given per-bin counts: one pass of
+// every light bin's lane groups, and the heavy units.
 inline int64_t round_units(const int32_t cnt[kBins], const BinLayout& L) {
   int64_t u = 0;
-  for (int b = 0; b < 3; ++b) u += (cnt[b] + kBlock - 1) / kBlock;
+  for (int b = 0; b < 3; ++b) u += (static_cast<int64_t>(cnt[b]) * L.lanes[b] + kBlock - 1) / kBlock;
   u += cnt[kBlockBin];
   u += static_cast<int64_t>(cnt[kSplitBin]) * L.split_chunks;
   return u;
