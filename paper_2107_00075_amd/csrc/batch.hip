@@ -95,12 +95,32 @@ __device__ __forceinline__ int bin_of(const BatchTune& t, int32_t w) {
   return 3;
 }
 
-// Units of a color/detect phase: light chunks of kBlock entries, then one
-// unit per workgroup vertex.
-__host__ __device__ inline uint32_t phase_units(const int32_t cnt[kBatchBins]) {
+// Worklist entries per unit of a light bin: as few passes of the workgroup's
+// lane groups as cut the bin into 1024 units.  (A unit of kBlock entries is 64
+// passes of 64-lane groups one after the other: a round of an R-MAT 14 job
+// took 110 us whatever else the launch did.)
+constexpr int32_t kUnitsPerBin = 1024;
+__device__ __forceinline__ int32_t unit_size(int32_t cnt, int32_t lanes) {
+  return round_chunk_size(cnt, lanes, kUnitsPerBin);
+}
+
+// Units of a color/detect phase: the light bins' chunks, then one unit per
+// workgroup vertex.
+__device__ __forceinline__ uint32_t phase_units(const int32_t cnt[kBatchBins], const BatchTune& t) {
   uint32_t u = 0;
-  for (int b = 0; b < 3; ++b) u += static_cast<uint32_t>((cnt[b] + kBlock - 1) / kBlock);
+  for (int b = 0; b < 3; ++b) {
+    const int32_t s = unit_size(cnt[b], t.lanes[b]);
+    u += static_cast<uint32_t>((cnt[b] + s - 1) / s);
+  }
   return u + static_cast<uint32_t>(cnt[3]);
+}
+
+// Every access to a job's mutable state is device-scope (performed beyond the
+// L2s), so handing it over needs no cache writeback or invalidation, only
+// that the accesses before have completed.  A workgroup's: before its barrier.
+__device__ __forceinline__ void wait_own_accesses() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0);
 }
 
 template <int MODE, int LD>
@@ -207,9 +227,9 @@ __device__ __forceinline__ void round_units(BatchJob* J, const JobView& V, const
   b.cnt_out = J->cnt[p ^ 1];
   // scalars, not arrays: a dynamically indexed local array would live in
   // scratch memory
-  const int32_t ch0 = (sh.cnt_in[0] + kBlock - 1) / kBlock;
-  const int32_t ch1 = (sh.cnt_in[1] + kBlock - 1) / kBlock;
-  const int32_t ch2 = (sh.cnt_in[2] + kBlock - 1) / kBlock;
+  const int32_t cs0 = unit_size(sh.cnt_in[0], t.lanes[0]), ch0 = (sh.cnt_in[0] + cs0 - 1) / cs0;
+  const int32_t cs1 = unit_size(sh.cnt_in[1], t.lanes[1]), ch1 = (sh.cnt_in[1] + cs1 - 1) / cs1;
+  const int32_t cs2 = unit_size(sh.cnt_in[2], t.lanes[2]), ch2 = (sh.cnt_in[2] + cs2 - 1) / cs2;
   const int32_t light = ch0 + ch1 + ch2;
   for (uint32_t q = 0; q < count; ++q) {
     int32_t uu = static_cast<int32_t>(first + q);
@@ -223,8 +243,9 @@ __device__ __forceinline__ void round_units(BatchJob* J, const JobView& V, const
           bin = 2;
         }
       }
-      const int32_t f = uu * kBlock;
-      const int32_t cnt = min(kBlock, sh.cnt_in[bin] - f);
+      const int32_t cs = bin == 0 ? cs0 : (bin == 1 ? cs1 : cs2);
+      const int32_t f = uu * cs;
+      const int32_t cnt = min(cs, sh.cnt_in[bin] - f);
       const int32_t* wl = b.wl_in + sh.off[bin] + f;
       const int G = bin == 0 ? t.lanes[0] : (bin == 1 ? t.lanes[1] : t.lanes[2]);
       if (!detect) {
@@ -264,18 +285,18 @@ __device__ __forceinline__ void round_units(BatchJob* J, const JobView& V, const
 
 // Opens epoch e with U units, or parks the job there when its epoch budget
 // is used up.
-__device__ void open_phase(BatchJob* J, uint64_t* word, uint32_t e, uint32_t U, int32_t* retired) {
+__device__ __forceinline__ void open_phase(BatchJob* J, uint64_t* word, uint32_t e, uint32_t U, int32_t* retired) {
   atomic_reset_u32(&J->done);
   if (static_cast<int32_t>(e) >= ld_dev(&J->stop_epoch)) {
     st_dev(&J->parked_epoch, static_cast<int32_t>(e));
     st_dev(&J->parked_units, static_cast<int32_t>(U));
     st_dev(&J->status, static_cast<int32_t>(kJobParked));
-    __threadfence();
+    wait_own_accesses();
     store_word(word, phase_word(e, 0, 0));
     atomicAdd(retired, 1);
     return;
   }
-  __threadfence();
+  wait_own_accesses();
   store_word(word, phase_word(e, U, 0));
 }
 
@@ -284,14 +305,14 @@ __device__ void finish_job(BatchJob* J, uint64_t* word, uint32_t e, int32_t roun
   st_dev(&J->rounds, rounds);
   st_dev(&J->rc, rc);
   st_dev(&J->status, static_cast<int32_t>(kJobFinished));
-  __threadfence();
+  wait_own_accesses();
   store_word(word, phase_word((e + 1) & 0xFFFFu, 0, 0));
   atomicAdd(retired, 1);
 }
 
 // The last unit of epoch e has completed: open the next phase.
-__device__ void close_phase(BatchJob* J, int32_t n, int32_t max_rounds, uint64_t* word, uint32_t e, uint32_t U,
-                            int32_t* retired) {
+__device__ __forceinline__ void close_phase(BatchJob* J, int32_t n, int32_t max_rounds, uint64_t* word, uint32_t e, uint32_t U,
+                            const BatchTune t, int32_t* retired) {
   if (e == 1) {
     int32_t o = 0;
     for (int b = 0; b < kBatchBins; ++b) {
@@ -309,7 +330,7 @@ __device__ void close_phase(BatchJob* J, int32_t n, int32_t max_rounds, uint64_t
       atomic_reset_i32(&J->cnt[1][b]);
     }
     atomicAdd(&J->visits[0], static_cast<unsigned long long>(n));
-    open_phase(J, word, 3, phase_units(c), retired);
+    open_phase(J, word, 3, phase_units(c, t), retired);
   } else if (e & 1u) {
     open_phase(J, word, e + 1, U, retired);  // color step done: detect over the same worklist
   } else {
@@ -328,17 +349,16 @@ __device__ void close_phase(BatchJob* J, int32_t n, int32_t max_rounds, uint64_t
     } else {
       for (int b = 0; b < kBatchBins; ++b) atomic_reset_i32(&J->cnt[p][b]);
       atomicAdd(&J->visits[0], static_cast<unsigned long long>(total));
-      open_phase(J, word, e + 1, phase_units(c), retired);
+      open_phase(J, word, e + 1, phase_units(c, t), retired);
     }
   }
 }
 
 // Runs the owned units of one grab.
 template <int MODE, int LD>
-__device__ __forceinline__ void run_grab(BatchJob* J, const JobView& V, const BatchTune* tune, uint32_t e, uint32_t first,
+__device__ __forceinline__ void run_grab(BatchJob* J, const JobView& V, const BatchTune& t, uint32_t e, uint32_t first,
                          uint32_t count, StepShared& sh, int32_t* s_bc, int32_t* s_base, uint64_t& work_acc,
                          int32_t& maxc_acc) {
-  const BatchTune t = tune_of<LD>(V, tune);
   if (e == 1) {
     for (uint32_t q = 0; q < count; ++q) setup_a_unit<MODE, LD>(J, V, t, static_cast<int32_t>(first + q), s_bc);
   } else if (e == 2) {
@@ -409,7 +429,6 @@ __global__ __launch_bounds__(kBlock) void batch_kernel(BatchJob* jobs, uint64_t*
         s_exit = job < 0 && atomic_load_i32(retired) >= active;
         s_work = 0ull;
         s_max = 0;
-        if (job >= 0) __threadfence();
       }
     }
     __syncthreads();
@@ -425,10 +444,11 @@ __global__ __launch_bounds__(kBlock) void batch_kernel(BatchJob* jobs, uint64_t*
     const uint32_t e = s_e;
     uint64_t work_acc = 0;
     int32_t maxc_acc = 0;
+    const BatchTune t = tune_of<LD>(V, tune);
     switch (V.mode) {
-      case kD1: run_grab<kD1, LD>(J, V, tune, e, s_first, s_cnt, sh, s_bc, s_base, work_acc, maxc_acc); break;
-      case kD2: run_grab<kD2, LD>(J, V, tune, e, s_first, s_cnt, sh, s_bc, s_base, work_acc, maxc_acc); break;
-      default: run_grab<kPD2, LD>(J, V, tune, e, s_first, s_cnt, sh, s_bc, s_base, work_acc, maxc_acc); break;
+      case kD1: run_grab<kD1, LD>(J, V, t, e, s_first, s_cnt, sh, s_bc, s_base, work_acc, maxc_acc); break;
+      case kD2: run_grab<kD2, LD>(J, V, t, e, s_first, s_cnt, sh, s_bc, s_base, work_acc, maxc_acc); break;
+      default: run_grab<kPD2, LD>(J, V, t, e, s_first, s_cnt, sh, s_bc, s_base, work_acc, maxc_acc); break;
     }
     work_acc = wave_sum_u64(work_acc);
     maxc_acc = wave_max_i32(maxc_acc);
@@ -436,16 +456,14 @@ __global__ __launch_bounds__(kBlock) void batch_kernel(BatchJob* jobs, uint64_t*
       if (work_acc) atomicAdd(&s_work, static_cast<unsigned long long>(work_acc));
       if (maxc_acc > 0) atomicMax(&s_max, maxc_acc);
     }
+    wait_own_accesses();
     __syncthreads();
     if (threadIdx.x == 0) {
       if (s_work) atomicAdd(&J->visits[1], s_work);
       if (s_max > 0) atomicMax(&J->maxc, s_max);
-      __threadfence();
+      wait_own_accesses();
       const uint32_t before = atomicAdd(&J->done, s_cnt);
-      if (before + s_cnt == s_u) {
-        __threadfence();
-        close_phase(J, V.n, V.max_rounds, &words[job], e, s_u, retired);
-      }
+      if (before + s_cnt == s_u) close_phase(J, V.n, V.max_rounds, &words[job], e, s_u, t, retired);
     }
     __syncthreads();
   }
