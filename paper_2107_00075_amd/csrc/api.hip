@@ -654,6 +654,7 @@ int run_incremental(Call& c, const GraphView& g, const KeySource& k, const int32
   ib.T = w->T.as<int32_t>();
   ib.work = w->work.as<int32_t>();
   ib.tile_ctr = S->tile_ctr;
+  ib.light_ctr = &S->light_ctr;
   ib.aoff = aoff;
   ib.fw_off = w->inc_fwoff.as<int32_t>();
   ib.F = w->inc_F.as<uint32_t>();

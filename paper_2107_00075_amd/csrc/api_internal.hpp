@@ -38,7 +38,7 @@ struct Scalars {
   int32_t max_split_work;       // largest work of an uncolored split vertex
   int32_t err;                  // validation error bits
   int32_t aux_max;
-  int32_t pad_;
+  int32_t light_ctr;            // light-chunk counter of the incremental detect kernel
   int32_t count_all[8];
   int32_t count_unc[8];
   unsigned long long visits[8]; // [0] sum |W_r|, [1] sum work(W_r), [2] list entries, [3] color bytes,

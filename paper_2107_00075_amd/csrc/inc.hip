@@ -110,6 +110,51 @@ __device__ __forceinline__ void push_color(const IncBufs& b, int32_t x, int32_t 
   }
 }
 
+// The same for N list entries of a lane at once (x < 0: none), leaving out
+// committed vertices: the N committed words are loaded together, then the N
+// offsets and the N bitset words, so that a batch waits once per kind of load.
+template <int MUT, int N>
+__device__ __forceinline__ void push_colors(const IncBufs& b, const int32_t (&x)[N], int32_t c, uint64_t& pushes) {
+  const int32_t w = (c - 1) >> 5;
+  const uint32_t bit = 1u << ((c - 1) & 31);
+  uint32_t dw[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) dw[j] = x[j] >= 0 ? ld_mut<MUT>(&b.done[x[j] >> 5]) : ~0u;
+  bool live[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) live[j] = x[j] >= 0 && !((dw[j] >> (x[j] & 31)) & 1u);
+  if (w == 0) {
+    uint32_t f[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) f[j] = live[j] ? ld_mut<MUT>(&b.F[x[j]]) : ~0u;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      if (!(f[j] & bit)) {
+        atomicOr(&b.F[x[j]], bit);
+        ++pushes;
+      }
+    }
+  } else {
+    int32_t w0[N], w1[N];
+    uint32_t f[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      w0[j] = live[j] ? ld_mut<MUT>(&b.fw_off[x[j]]) : 0;
+      w1[j] = live[j] ? ld_mut<MUT>(&b.fw_off[x[j] + 1]) : 0;
+    }
+    // (beyond the bitset: a color x can never take)
+#pragma unroll
+    for (int j = 0; j < N; ++j) f[j] = w <= w1[j] - w0[j] ? ld_mut<MUT>(&b.Fx[w0[j] + w - 1]) : ~0u;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      if (!(f[j] & bit)) {
+        atomicOr(&b.Fx[w0[j] + w - 1], bit);
+        ++pushes;
+      }
+    }
+  }
+}
+
 // A loser compacts its list to the neighbours not yet committed in the first
 // kCompactAlways rounds (where most neighbours commit), whenever its list is
 // still the read-only adjacency (round 1 of D1), and else once every
@@ -183,6 +228,7 @@ __device__ __forceinline__ void inc_color_phase(const IncBufs& b, const BinLayou
     s_acc[0] = s_acc[1] = s_acc[2] = 0ull;
     if (blockIdx.x == 0) {
       for (int i = 0; i < kBins; ++i) atomic_reset_i32(&b.cnt_out[i]);
+      atomic_reset_i32(b.light_ctr);
       atomic_reset_i32(&b.tile_ctr[1]);
       if (M.total > 0) {
         const int gr = round + b.round_base;
@@ -232,7 +278,7 @@ __device__ __forceinline__ void inc_color_phase(const IncBufs& b, const BinLayou
       w = found ? (t - 1) / 32 : nw;  // the word that held t (or all of them)
       bytes += 8;  // the two offsets
     }
-    st_dev(&b.T[v], t);
+    st_mut<MUT>(&b.T[v], t);
     if (round <= b.t8_last) st_mut<MUT>(&b.T8[v], static_cast<uint8_t>(t));
     work += static_cast<uint64_t>(ld_mut<MUT>(&b.work[v]));
     lists += static_cast<uint64_t>(ld_mut<MUT>(&b.alen_in[v]));
@@ -269,92 +315,150 @@ __global__ __launch_bounds__(kBlock) void inc_color_kernel(IncBufs b, BinLayout 
 // lower ones at the back of the vertex's list region (length llen).  Only a
 // higher-key neighbour can beat v, so later detect scans read the front part
 // only; the one push a winner makes reads both parts.
+//
+// A chunk runs in two steps.  First every vertex's front entries are tested,
+// by groups of at most kProbeLanes lanes with kProbeBatch entries per lane in
+// flight: a loser mostly meets its conflict there, and its cost is one chain
+// of dependent loads (id, fields, entries, tentative colors) shared with the
+// wavefront's other groups.  What is left (longer scans, the winners' pushes,
+// the losers due a compaction) is listed, and the bin's own groups of G lanes
+// take it.  (With one group of 64 lanes per vertex from the start, a vertex
+// of a late R-MAT 22 round cost its wavefront 13 us.)
+constexpr int kProbeLanes = 16;
+constexpr int kProbeBatch = 4;
+enum : int8_t { kScan = -1, kWin = -2, kCompact = -3 };  // pending states in s_tb
+
+// Whether one of the group's lanes holds a conflict among the entries e0 +
+// sub + j G (j < N, below len) of v's list.
+template <int G, int MUT, int N>
+__device__ __forceinline__ bool inc_conflict(const KeySource& k, const IncBufs& b, const int32_t* A, int32_t e0,
+                                             int sub, int32_t len, int32_t tv, uint64_t kv, bool first_pass, bool t8,
+                                             int32_t& read, int32_t& gath) {
+  int32_t u[N], t[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    const int32_t e = e0 + sub + j * G;
+    u[j] = e < len ? ld_mut<MUT>(&A[e]) : -1;
+    read += u[j] >= 0 ? 1 : 0;
+  }
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    const bool higher = u[j] >= 0 && (!first_pass || key_of(k, u[j]) > kv);
+    t[j] = higher ? (b.uniform ? tv : tentative_of<MUT>(b, t8, u[j])) : -1;
+    gath += (higher && !b.uniform) ? 1 : 0;
+  }
+  bool hit = false;
+#pragma unroll
+  for (int j = 0; j < N; ++j) hit = hit || t[j] == tv;
+  return group_any<G>(hit);
+}
+
 template <int G, int MUT>
 __device__ __forceinline__ void inc_detect_chunk(const KeySource& k, const IncBufs& b, const BinLayout& L, int round,
                                                  const int32_t* wl, int32_t count, int32_t* s_ent, int8_t* s_tb,
-                                                 int32_t* s_wc, int32_t& maxc_acc, uint64_t& bytes,
+                                                 int32_t* s_wc, int16_t* s_pend, int32_t& maxc_acc, uint64_t& bytes,
                                                  uint64_t& pushes) {
+  constexpr int P = G < kProbeLanes ? G : kProbeLanes;
+  const bool first_pass = b.A_in != b.A_out;
+  const bool t8 = round <= b.t8_last;
+  if (threadIdx.x == 0) s_wc[0] = 0;  // pending vertices
+  __syncthreads();
+  {
+    constexpr int per_pass = kBlock / P;
+    const int sub = threadIdx.x % P;
+    int32_t idx = threadIdx.x / P;
+    int32_t v = idx < count ? ld_mut<MUT>(&wl[idx]) : 0;
+    while (idx < count) {
+      const int32_t next = idx + per_pass;
+      const int32_t tv = ld_mut<MUT>(&b.T[v]);
+      const int32_t base = ld_mut<MUT>(&b.aoff[v]);
+      const int32_t len = ld_mut<MUT>(&b.alen_in[v]);
+      const int32_t llen = first_pass ? 0 : ld_mut<MUT>(&b.llen[v]);
+      const int32_t vn = next < count ? ld_mut<MUT>(&wl[next]) : 0;
+      int32_t read = 0, gath = 0;
+      const bool lose = inc_conflict<P, MUT, kProbeBatch>(k, b, b.A_in + base, 0, sub, len, tv, key_of(k, v),
+                                                          first_pass, t8, read, gath);
+      // list entries and tentative colors this lane read
+      bytes += 4ull * static_cast<uint64_t>(read) + (t8 ? 1ull : 4ull) * static_cast<uint64_t>(gath);
+      if (sub == 0) {
+        s_ent[idx] = v;
+        if (lose && !compact_now<MUT>(b, round, v)) {
+          s_tb[idx] = static_cast<int8_t>(inc_bin_of(L, len + llen));
+          bytes += 24;
+        } else {
+          s_tb[idx] = lose ? kCompact : len <= P * kProbeBatch ? kWin : kScan;
+          s_pend[atomicAdd(&s_wc[0], 1)] = static_cast<int16_t>(idx);
+        }
+      }
+      idx = next;
+      v = vn;
+    }
+  }
+  __syncthreads();
+  const int32_t pending = s_wc[0];
   constexpr int per_pass = kBlock / G;
-  const int gi = threadIdx.x / G;
   const int sub = threadIdx.x % G;
   const int first = lane_id() & ~(G - 1);
   const uint64_t gm = (G == 64) ? ~0ull : ((1ull << G) - 1ull);
-  const bool first_pass = b.A_in != b.A_out;
-  const bool t8 = round <= b.t8_last;
-  for (int32_t idx = gi; idx < count; idx += per_pass) {
-    const int32_t v = ld_mut<MUT>(&wl[idx]);
+  for (int32_t i = threadIdx.x / G; i < pending; i += per_pass) {
+    const int32_t idx = s_pend[i];
+    const int8_t state = s_tb[idx];
+    const int32_t v = s_ent[idx];
     const int32_t tv = ld_mut<MUT>(&b.T[v]);
     const uint64_t kv = key_of(k, v);
     const int32_t base = ld_mut<MUT>(&b.aoff[v]);
     const int32_t len = ld_mut<MUT>(&b.alen_in[v]);
+    const int32_t cap = ld_mut<MUT>(&b.aoff[v + 1]) - base;
+    const int32_t lo_len = first_pass ? 0 : ld_mut<MUT>(&b.llen[v]);
     const int32_t* A = b.A_in + base;
-    bool lose = false;
-    int32_t read = 0, gath = 0;
-    // the group steps through the list together, two entries per lane per
-    // step, and stops at the first step in which any of its lanes found a
-    // conflict (a lane-by-lane stop would keep the group scanning until its
-    // slowest lane reached the end; measured on MI355X, two entries per step
-    // beat four: R-MAT 22 D1 39.3 -> 38.4 ms)
-    // wide groups take one entry per lane in their first step (a loser
-    // mostly meets its conflict near the front of its list)
-    for (int32_t e0 = 0, per = (G >= 32 ? 1 : 2); e0 < len; e0 += per * G, per = 2) {
-      int32_t u[2], t[2];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int32_t e = e0 + sub + j * G;
-        const bool in = j < per && e < len;
-        u[j] = in ? ld_mut<MUT>(&A[e]) : -1;
-        read += in ? 1 : 0;
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const bool higher = u[j] >= 0 && (!first_pass || key_of(k, u[j]) > kv);
-        t[j] = higher ? (b.uniform ? tv : tentative_of<MUT>(b, t8, u[j])) : -1;
-        gath += (higher && !b.uniform) ? 1 : 0;
-      }
-      bool hit = false;
-#pragma unroll
-      for (int j = 0; j < 2; ++j) hit = hit || t[j] == tv;
-      if (group_any<G>(hit)) {
-        lose = true;
-        break;
-      }
+    bool lose = state == kCompact;
+    if (state == kScan) {
+      // the group steps on through the list together and stops at the first
+      // step in which any of its lanes found a conflict
+      int32_t read = 0, gath = 0;
+      for (int32_t e0 = P * kProbeBatch; e0 < len && !lose; e0 += 4 * G)
+        lose = inc_conflict<G, MUT, 4>(k, b, A, e0, sub, len, tv, kv, first_pass, t8, read, gath);
+      bytes += 4ull * static_cast<uint64_t>(read) + (t8 ? 1ull : 4ull) * static_cast<uint64_t>(gath);
     }
-    // list entries and tentative colors this lane read
-    bytes += 4ull * static_cast<uint64_t>(read) + (t8 ? 1ull : 4ull) * static_cast<uint64_t>(gath);
-    if (lose && !compact_now<MUT>(b, round, v)) {
+    if (lose && state == kScan && !compact_now<MUT>(b, round, v)) {
       if (sub == 0) {
-        s_ent[idx] = v;
-        s_tb[idx] = static_cast<int8_t>(inc_bin_of(L, first_pass ? len : len + ld_mut<MUT>(&b.llen[v])));
+        s_tb[idx] = static_cast<int8_t>(inc_bin_of(L, len + lo_len));
         bytes += 24;
       }
     } else if (lose) {
       // keep the neighbours that are not committed (yet); the first pass
-      // also splits them by key
-      const int32_t cap = ld_mut<MUT>(&b.aoff[v + 1]) - base;
+      // also splits them by key.  In place (later passes) the entries of a
+      // step are read before its writes, which land below its first entry or
+      // inside it.
       int32_t kept = 0, kept_lo = 0;
-      for (int32_t e0 = 0; e0 < len; e0 += G) {
-        const int32_t e = e0 + sub;
-        int32_t u = -1;
-        bool keep = false, hi = true;
-        if (e < len) {
-          u = ld_mut<MUT>(&A[e]);
-          keep = b.uniform || !committed<MUT>(b, u);  // round 1: nobody was committed before it
-          if (first_pass) hi = key_of(k, u) > kv;
+      for (int32_t e0 = 0; e0 < len; e0 += 4 * G) {
+        int32_t u[4];
+        uint32_t dw[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int32_t e = e0 + sub + j * G;
+          u[j] = e < len ? ld_mut<MUT>(&A[e]) : -1;
         }
-        const uint64_t bal_h = (__ballot(keep && hi) >> first) & gm;
-        const uint64_t bal_l = (__ballot(keep && !hi) >> first) & gm;
-        const uint64_t below = (1ull << sub) - 1ull;
-        if (keep && hi) st_dev(&b.A_out[base + kept + __popcll(bal_h & below)], u);
-        if (keep && !hi) st_dev(&b.A_out[base + cap - 1 - (kept_lo + __popcll(bal_l & below))], u);
-        kept += __popcll(bal_h);
-        kept_lo += __popcll(bal_l);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)  // round 1: nobody was committed before it
+          dw[j] = u[j] >= 0 ? (b.uniform ? 0u : ld_mut<MUT>(&b.done[u[j] >> 5])) : ~0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const bool keep = u[j] >= 0 && !((dw[j] >> (u[j] & 31)) & 1u);
+          const bool hi = !first_pass || (keep && key_of(k, u[j]) > kv);
+          const uint64_t bal_h = (__ballot(keep && hi) >> first) & gm;
+          const uint64_t bal_l = (__ballot(keep && !hi) >> first) & gm;
+          const uint64_t below = (1ull << sub) - 1ull;
+          if (keep && hi) st_mut<MUT>(&b.A_out[base + kept + __popcll(bal_h & below)], u[j]);
+          if (keep && !hi) st_mut<MUT>(&b.A_out[base + cap - 1 - (kept_lo + __popcll(bal_l & below))], u[j]);
+          kept += __popcll(bal_h);
+          kept_lo += __popcll(bal_l);
+        }
       }
       if (sub == 0) {
-        st_dev(&b.alen_out[v], kept);
-        if (first_pass) st_dev(&b.llen[v], kept_lo);
-        else kept_lo = ld_mut<MUT>(&b.llen[v]);
-        s_ent[idx] = v;
+        st_mut<MUT>(&b.alen_out[v], kept);
+        if (first_pass) st_mut<MUT>(&b.llen[v], kept_lo);
+        else kept_lo = lo_len;
         s_tb[idx] = static_cast<int8_t>(inc_bin_of(L, kept + kept_lo));
         bytes += 28 + 8ull * static_cast<uint64_t>(len) + 4ull * static_cast<uint64_t>(kept + kept_lo);
       }
@@ -365,8 +469,6 @@ __device__ __forceinline__ void inc_detect_chunk(const KeySource& k, const IncBu
       // more than the pushes it saved); a neighbour committing in the same
       // round may still get the push, which is harmless: a committed
       // vertex's bitset is never read again.
-      const int32_t cap = first_pass ? len : ld_mut<MUT>(&b.aoff[v + 1]) - base;
-      const int32_t lo_len = first_pass ? 0 : ld_mut<MUT>(&b.llen[v]);
       for (int part = 0; part < 2; ++part) {
         const int32_t pb = part == 0 ? 0 : cap - lo_len;
         const int32_t pe = part == 0 ? len : cap;
@@ -377,13 +479,11 @@ __device__ __forceinline__ void inc_detect_chunk(const KeySource& k, const IncBu
             const int32_t e = e0 + j * G;
             x[j] = e < pe ? ld_mut<MUT>(&A[e]) : -1;
           }
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (x[j] >= 0 && !committed<MUT>(b, x[j])) push_color<MUT>(b, x[j], tv, pushes);
+          push_colors<MUT>(b, x, tv, pushes);
         }
       }
       if (sub == 0) {
-        st_dev(&b.C[v], tv);
+        st_mut<MUT>(&b.C[v], tv);
         mark_committed(b, v);
         maxc_acc = max(maxc_acc, tv);
         s_ent[idx] = -1;
@@ -420,7 +520,7 @@ __device__ __forceinline__ void inc_detect_chunk(const KeySource& k, const IncBu
   if (x >= 0) {
     const uint64_t mine = t == 0 ? b0 : t == 1 ? b1 : t == 2 ? b2 : b3;
     const int q = t == kBlockBin ? 3 : t;
-    st_dev(&b.wl_out[L.off[t] + s_wc[4 * kWavesPerBlock + q] + s_wc[q * kWavesPerBlock + wave] +
+    st_mut<MUT>(&b.wl_out[L.off[t] + s_wc[4 * kWavesPerBlock + q] + s_wc[q * kWavesPerBlock + wave] +
                      static_cast<int32_t>(lanes_below(mine))],
            x);
   }
@@ -439,6 +539,77 @@ struct HeavyVertex {
 };
 constexpr int kHeavyBatch = 8;
 
+// In-place compaction of one part of a list by the workgroup: entry q of the
+// part is *in(q), and the entries of vertices not yet committed move to
+// *hi(0), *hi(1), ... or, with SPLIT (the first pass, out of place), those of
+// lower key to *lo(0), ....  The order is free, so positions come from
+// ballots (no scan), a step's one barrier both exchanges the wavefronts'
+// counts and orders its reads before its writes (which land at entries of
+// this or earlier steps), and the next step's entries are loaded behind it.
+// (With wavefront scans, two barriers and no prefetch a step of 2048 entries
+// took about 8 us: a PD2 hub of 10^6 entries held its round for 4 ms.)
+template <int MUT, bool SPLIT, typename IN, typename HI, typename LO>
+__device__ __forceinline__ void inc_compact_block(const KeySource& k, const IncBufs& b, uint64_t kv, int32_t len,
+                                                  int32_t* s_wc, int32_t& kept, int32_t& kept_lo, IN&& in, HI&& hi,
+                                                  LO&& lo) {
+  constexpr int32_t step = kBlock * kIncBatch;
+  const int tid = threadIdx.x, wave = tid / kWave;
+  int32_t u[kIncBatch];
+#pragma unroll
+  for (int j = 0; j < kIncBatch; ++j) u[j] = j * kBlock + tid < len ? ld_mut<MUT>(in(j * kBlock + tid)) : -1;
+  int par = 0;
+  for (int32_t e0 = 0; e0 < len; e0 += step, par ^= 2 * kWavesPerBlock) {
+    uint32_t dw[kIncBatch];
+    int32_t next[kIncBatch];
+#pragma unroll
+    for (int j = 0; j < kIncBatch; ++j)  // round 1: nobody was committed before it
+      dw[j] = u[j] >= 0 ? (b.uniform ? 0u : ld_mut<MUT>(&b.done[u[j] >> 5])) : ~0u;
+#pragma unroll
+    for (int j = 0; j < kIncBatch; ++j) {
+      const int32_t e = e0 + step + j * kBlock + tid;
+      next[j] = e < len ? ld_mut<MUT>(in(e)) : -1;
+    }
+    uint32_t keep_hi = 0, keep_lo = 0;
+    int32_t mine[kIncBatch];  // position within the wavefront's kept entries of this step
+    int32_t tot = 0, tot_lo = 0;
+#pragma unroll
+    for (int j = 0; j < kIncBatch; ++j) {
+      const bool keep = u[j] >= 0 && !((dw[j] >> (u[j] & 31)) & 1u);
+      const bool h = !SPLIT || (keep && key_of(k, u[j]) > kv);
+      const uint64_t bh = __ballot(keep && h);
+      const uint64_t bl = SPLIT ? __ballot(keep && !h) : 0ull;
+      mine[j] = h ? tot + static_cast<int32_t>(lanes_below(bh)) : tot_lo + static_cast<int32_t>(lanes_below(bl));
+      tot += static_cast<int32_t>(__popcll(bh));
+      tot_lo += static_cast<int32_t>(__popcll(bl));
+      keep_hi |= (keep && h) ? 1u << j : 0u;
+      keep_lo |= (keep && !h) ? 1u << j : 0u;
+    }
+    if (lane_id() == 0) {
+      s_wc[par + wave] = tot;
+      s_wc[par + kWavesPerBlock + wave] = tot_lo;
+    }
+    __syncthreads();
+    int32_t pos = kept, pos_lo = kept_lo;
+#pragma unroll
+    for (int w = 0; w < kWavesPerBlock; ++w) {
+      const int32_t c = s_wc[par + w], cl = s_wc[par + kWavesPerBlock + w];
+      if (w < wave) {
+        pos += c;
+        pos_lo += cl;
+      }
+      kept += c;
+      kept_lo += cl;
+    }
+#pragma unroll
+    for (int j = 0; j < kIncBatch; ++j) {
+      if (keep_hi & (1u << j)) st_mut<MUT>(hi(pos + mine[j]), u[j]);
+      if (SPLIT && (keep_lo & (1u << j))) st_mut<MUT>(lo(pos_lo + mine[j]), u[j]);
+      u[j] = next[j];
+    }
+  }
+  __syncthreads();
+}
+
 // Returns the bin of the next worklist if v lost (its append is left to the
 // caller, batched), else -1.
 template <int MUT>
@@ -446,7 +617,6 @@ __device__ __forceinline__ int inc_detect_block(const KeySource& k, const IncBuf
                                                 const HeavyVertex& h, int32_t* s_wc, int32_t& maxc_acc,
                                                 uint64_t& bytes, uint64_t& pushes) {
   const int tid = threadIdx.x;
-  const int wave = tid / kWave;
   const bool first_pass = b.A_in != b.A_out;
   const bool t8 = round <= b.t8_last;
   const int32_t v = h.v;
@@ -458,18 +628,17 @@ __device__ __forceinline__ int inc_detect_block(const KeySource& k, const IncBuf
   constexpr int32_t step = kBlock * kIncBatch;
   bool lose = false;
   uint32_t read = 0, gath = 0;
-  // steps of one, two, then kIncBatch entries per thread: a losing vertex
-  // mostly meets a conflict near the front, where a full step would read
-  // kIncBatch times more than it needs (measured on MI355X: R-MAT 22 D1
-  // 34.8 -> 32.5 ms per call, the PD2 pattern 64.4 -> 62.9 ms)
-  for (int32_t e0 = 0, per = 1; e0 < len; e0 += per * kBlock, per = (per == 1 ? 2 : kIncBatch)) {
-    int32_t u[kIncBatch], t[kIncBatch];
+  // a step of two entries per thread, then of kIncBatch (the list's front has
+  // been tested); the next step's entries are loaded behind this one's test
+  int32_t u[kIncBatch];
+#pragma unroll
+  for (int j = 0; j < kIncBatch; ++j) u[j] = j < 2 && j * kBlock + tid < len ? ld_mut<MUT>(&A[j * kBlock + tid]) : -1;
+  for (int32_t e0 = 2 * kBlock;; e0 += step) {
+    int32_t t[kIncBatch], next[kIncBatch];
 #pragma unroll
     for (int j = 0; j < kIncBatch; ++j) {
       const int32_t e = e0 + j * kBlock + tid;
-      const bool in = j < per && e < len;
-      u[j] = in ? ld_mut<MUT>(&A[e]) : -1;
-      read += in ? 1u : 0u;
+      next[j] = e < len ? ld_mut<MUT>(&A[e]) : -1;
     }
     // only a higher-key neighbour can beat v: before the lists are split by
     // key, compare keys first and read the tentative colors of those only
@@ -477,15 +646,19 @@ __device__ __forceinline__ int inc_detect_block(const KeySource& k, const IncBuf
     for (int j = 0; j < kIncBatch; ++j) {
       const bool higher = u[j] >= 0 && (!first_pass || key_of(k, u[j]) > kv);
       t[j] = higher ? (b.uniform ? tv : tentative_of<MUT>(b, t8, u[j])) : -1;
+      read += u[j] >= 0 ? 1u : 0u;
       gath += (higher && !b.uniform) ? 1u : 0u;
     }
 #pragma unroll
-    for (int j = 0; j < kIncBatch; ++j)
+    for (int j = 0; j < kIncBatch; ++j) {
       if (t[j] == tv) lose = true;
+      u[j] = next[j];
+    }
     if (__syncthreads_or(lose)) {
       lose = true;
       break;
     }
+    if (e0 >= len) break;
   }
   bytes += 4ull * read + (t8 ? 1ull : 4ull) * gath;  // list entries and tentative colors this thread read
   int next_bin = -1;
@@ -495,126 +668,62 @@ __device__ __forceinline__ int inc_detect_block(const KeySource& k, const IncBuf
   } else if (lose) {
     // keep the neighbours that are not committed (yet), order free; the
     // first pass also splits them by key (higher to the front, lower to the
-    // back).  Later passes compact the front part in place: every entry of a
-    // step is read before the barrier that precedes the step's writes, and
-    // writes land below the step's first entry or inside it.
+    // back).  Later passes compact both parts in place (the lower-key part is
+    // read by a push only, but a heavy vertex that commits late would push
+    // over every lower-key neighbour it had in round 1); back index q = 0, 1,
+    // ... is list position cap-1-q.
     const int32_t cap = h.end - base;
-    int32_t kept = 0, kept_lo = 0;
-    int32_t* s_lo = s_wc + kWavesPerBlock;
-    for (int32_t e0 = 0; e0 < len; e0 += step) {
-      int32_t u[kIncBatch];
-      uint32_t keep_hi = 0, keep_lo = 0;  // bit j: entry j kept in the front / back part
-#pragma unroll
-      for (int j = 0; j < kIncBatch; ++j) {
-        const int32_t e = e0 + j * kBlock + tid;
-        u[j] = e < len ? ld_mut<MUT>(&A[e]) : -1;
-      }
-#pragma unroll
-      for (int j = 0; j < kIncBatch; ++j) {
-        const bool keep = u[j] >= 0 && (b.uniform || !committed<MUT>(b, u[j]));
-        const bool hi = !first_pass || (u[j] >= 0 && key_of(k, u[j]) > kv);
-        keep_hi |= (keep && hi) ? (1u << j) : 0u;
-        keep_lo |= (keep && !hi) ? (1u << j) : 0u;
-      }
-      const int32_t cnt = __builtin_popcount(keep_hi), cnt_lo = __builtin_popcount(keep_lo);
-      int32_t incl = cnt, incl_lo = cnt_lo;
-#pragma unroll
-      for (int o = 1; o < kWave; o <<= 1) {
-        const int32_t y = __shfl_up(incl, o, kWave);
-        const int32_t z = __shfl_up(incl_lo, o, kWave);
-        if (lane_id() >= o) {
-          incl += y;
-          incl_lo += z;
-        }
-      }
-      if (lane_id() == kWave - 1) {
-        s_wc[wave] = incl;
-        s_lo[wave] = incl_lo;
-      }
-      __syncthreads();
-      int32_t pos = kept + incl - cnt, pos_lo = kept_lo + incl_lo - cnt_lo;
-      int32_t tot = 0, tot_lo = 0;
-      for (int w = 0; w < kWavesPerBlock; ++w) {
-        if (w < wave) {
-          pos += s_wc[w];
-          pos_lo += s_lo[w];
-        }
-        tot += s_wc[w];
-        tot_lo += s_lo[w];
-      }
-#pragma unroll
-      for (int j = 0; j < kIncBatch; ++j) {
-        if (keep_hi & (1u << j)) st_dev(&b.A_out[base + pos++], u[j]);
-        if (keep_lo & (1u << j)) st_dev(&b.A_out[base + cap - 1 - pos_lo++], u[j]);
-      }
-      kept += tot;
-      kept_lo += tot_lo;
-      __syncthreads();
-    }
-    // later passes also drop the committed entries of the lower-key part
-    // (the part only a push reads: without this, a heavy vertex that commits
-    // late would push over every lower-key neighbour it had in round 1).
-    // Back index q = 0, 1, ... is list position cap-1-q; kept entries move
-    // to back indices below or at their own, in step order as above.
+    int32_t kept = 0, kept_lo = 0, none = 0;
+    int32_t* out = b.A_out + base;
     const int32_t lo_len = first_pass ? 0 : h.llen;
-    for (int32_t q0 = 0; q0 < lo_len; q0 += step) {
-      int32_t u[kIncBatch];
-      uint32_t keep = 0;
-#pragma unroll
-      for (int j = 0; j < kIncBatch; ++j) {
-        const int32_t q = q0 + j * kBlock + tid;
-        u[j] = q < lo_len ? ld_mut<MUT>(&A[cap - 1 - q]) : -1;
-      }
-#pragma unroll
-      for (int j = 0; j < kIncBatch; ++j) keep |= (u[j] >= 0 && !committed<MUT>(b, u[j])) ? (1u << j) : 0u;
-      const int32_t cnt = __builtin_popcount(keep);
-      int32_t incl = cnt;
-#pragma unroll
-      for (int o = 1; o < kWave; o <<= 1) {
-        const int32_t y = __shfl_up(incl, o, kWave);
-        if (lane_id() >= o) incl += y;
-      }
-      if (lane_id() == kWave - 1) s_lo[wave] = incl;
-      __syncthreads();
-      int32_t pos = kept_lo + incl - cnt, tot = 0;
-      for (int w = 0; w < kWavesPerBlock; ++w) {
-        if (w < wave) pos += s_lo[w];
-        tot += s_lo[w];
-      }
-#pragma unroll
-      for (int j = 0; j < kIncBatch; ++j)
-        if (keep & (1u << j)) st_dev(&b.A_out[base + cap - 1 - pos++], u[j]);
-      kept_lo += tot;
-      __syncthreads();
+    if (first_pass) {
+      inc_compact_block<MUT, true>(
+          k, b, kv, len, s_wc, kept, kept_lo, [&](int32_t q) { return A + q; }, [&](int32_t q) { return out + q; },
+          [&](int32_t q) { return out + cap - 1 - q; });
+    } else {
+      inc_compact_block<MUT, false>(
+          k, b, kv, len, s_wc, kept, none, [&](int32_t q) { return A + q; }, [&](int32_t q) { return out + q; },
+          [&](int32_t q) { return out + q; });
+      inc_compact_block<MUT, false>(
+          k, b, kv, lo_len, s_wc, kept_lo, none, [&](int32_t q) { return A + cap - 1 - q; },
+          [&](int32_t q) { return out + cap - 1 - q; }, [&](int32_t q) { return out + q; });
     }
     next_bin = inc_bin_of(L, kept + kept_lo);
     if (tid == 0) {
-      st_dev(&b.alen_out[v], kept);
-      st_dev(&b.llen[v], kept_lo);
+      st_mut<MUT>(&b.alen_out[v], kept);
+      st_mut<MUT>(&b.llen[v], kept_lo);
       bytes += 24 + 8ull * static_cast<uint64_t>(len + lo_len) + 4ull * static_cast<uint64_t>(kept + kept_lo);
     }
   } else {
     // push the color to every list entry not yet committed (as in the
-    // lane-group path): the whole list on the first pass, else both parts
+    // lane-group path): the whole list on the first pass, else both parts;
+    // the next step's entries are loaded behind this one's pushes
     const int32_t cap = first_pass ? len : h.end - base;
     const int32_t lo_len = first_pass ? 0 : h.llen;
     for (int part = 0; part < 2; ++part) {
       const int32_t pb = part == 0 ? 0 : cap - lo_len;
       const int32_t pe = part == 0 ? len : cap;
+      int32_t x[2][kIncBatch / 2];
+#pragma unroll
+      for (int j = 0; j < kIncBatch; ++j) {
+        const int32_t e = pb + j * kBlock + tid;
+        x[j & 1][j >> 1] = e < pe ? ld_mut<MUT>(&A[e]) : -1;
+      }
       for (int32_t e0 = pb; e0 < pe; e0 += step) {
-        int32_t x[kIncBatch];
+        int32_t next[2][kIncBatch / 2];
 #pragma unroll
         for (int j = 0; j < kIncBatch; ++j) {
-          const int32_t e = e0 + j * kBlock + tid;
-          x[j] = e < pe ? ld_mut<MUT>(&A[e]) : -1;
+          const int32_t e = e0 + step + j * kBlock + tid;
+          next[j & 1][j >> 1] = e < pe ? ld_mut<MUT>(&A[e]) : -1;
         }
+        push_colors<MUT>(b, x[0], tv, pushes);
+        push_colors<MUT>(b, x[1], tv, pushes);
 #pragma unroll
-        for (int j = 0; j < kIncBatch; ++j)
-          if (x[j] >= 0 && !committed<MUT>(b, x[j])) push_color<MUT>(b, x[j], tv, pushes);
+        for (int j = 0; j < kIncBatch; ++j) x[j & 1][j >> 1] = next[j & 1][j >> 1];
       }
     }
     if (tid == 0) {
-      st_dev(&b.C[v], tv);
+      st_mut<MUT>(&b.C[v], tv);
       mark_committed(b, v);
       maxc_acc = max(maxc_acc, tv);
       bytes += 20 + 8ull * static_cast<uint64_t>(len + lo_len);  // own fields, C write, entries + committed bits
@@ -629,6 +738,7 @@ struct IncDetectShared {
   int32_t max;
   int32_t ent[kBlock];
   int8_t tb[kBlock];                    // target bin of each loser in ent
+  int16_t pend[kBlock];                 // a chunk's vertices left to its second step
   int32_t wc[4 * kWavesPerBlock + 4];   // per-target-bin wave offsets, then per-bin bases
   unsigned long long acc[2];
   IncMap M;
@@ -671,29 +781,8 @@ __device__ __forceinline__ void inc_detect_phase(const KeySource& k, const IncBu
       light_total -= M.chunks[light_bins];
     }
   }
-  const int32_t c0 = static_cast<int32_t>(static_cast<int64_t>(lb) * light_total / gridDim.x);
-  const int32_t c1 = static_cast<int32_t>(static_cast<int64_t>(lb + 1) * light_total / gridDim.x);
-  for (int32_t c = c0; c < c1; ++c) {
-    int bin = 0;
-    int32_t cc = c;
-    while (bin < 2 && cc >= M.chunks[bin]) {
-      cc -= M.chunks[bin];
-      ++bin;
-    }
-    const int32_t firstc = cc * M.csize[bin];
-    const int32_t count = min(M.csize[bin], M.cnt[bin] - firstc);
-    const int32_t* wl = b.wl_in + L.off[bin] + firstc;
-    switch (L.lanes[bin]) {
-      case 1: inc_detect_chunk<1, MUT>(k, b, L, round, wl, count, s_ent, s_tb, s_wc, maxc_acc, bytes, pushes); break;
-      case 2: inc_detect_chunk<2, MUT>(k, b, L, round, wl, count, s_ent, s_tb, s_wc, maxc_acc, bytes, pushes); break;
-      case 4: inc_detect_chunk<4, MUT>(k, b, L, round, wl, count, s_ent, s_tb, s_wc, maxc_acc, bytes, pushes); break;
-      case 8: inc_detect_chunk<8, MUT>(k, b, L, round, wl, count, s_ent, s_tb, s_wc, maxc_acc, bytes, pushes); break;
-      case 16: inc_detect_chunk<16, MUT>(k, b, L, round, wl, count, s_ent, s_tb, s_wc, maxc_acc, bytes, pushes); break;
-      case 32: inc_detect_chunk<32, MUT>(k, b, L, round, wl, count, s_ent, s_tb, s_wc, maxc_acc, bytes, pushes); break;
-      default: inc_detect_chunk<64, MUT>(k, b, L, round, wl, count, s_ent, s_tb, s_wc, maxc_acc, bytes, pushes); break;
-    }
-  }
-  // heavy units, kHeavyBatch at a time: first the workgroup's own
+  // heavy units first (the longest lists would otherwise start last),
+  // kHeavyBatch at a time: first the workgroup's own
   // (units lb, lb + G, lb + 2G, ... : no atomic), then batches of consecutive
   // units above G * kHeavyBatch handed out by a counter.  The batch's vertex
   // fields are loaded at once, and its losers are appended together, one
@@ -728,9 +817,27 @@ __device__ __forceinline__ void inc_detect_phase(const KeySource& k, const IncBu
       sh.hb[j] = -1;
     }
     __syncthreads();
+    // the front of every list of the batch at once, a group of lanes each:
+    // most losers are done with that
+    {
+      constexpr int P = kBlock / kHeavyBatch;
+      const int j = threadIdx.x / P, sub = threadIdx.x % P;
+      const HeavyVertex h = sh.hv[j];
+      int32_t read = 0, gath = 0;
+      const bool first_pass = b.A_in != b.A_out, t8 = round <= b.t8_last;
+      const bool lose = inc_conflict<P, MUT, kProbeBatch>(k, b, b.A_in + h.base, 0, sub, h.v >= 0 ? h.len : 0, h.tv,
+                                                          h.v >= 0 ? key_of(k, h.v) : 0ull, first_pass, t8, read,
+                                                          gath);
+      bytes += 4ull * static_cast<uint64_t>(read) + (t8 ? 1ull : 4ull) * static_cast<uint64_t>(gath);
+      if (sub == 0 && lose && !compact_now<MUT>(b, round, h.v)) {
+        sh.hb[j] = static_cast<int8_t>(inc_bin_of(L, first_pass ? h.len : h.len + h.llen));
+        bytes += 28;
+      }
+    }
+    __syncthreads();
     for (int j = 0; j < kHeavyBatch; ++j) {
       const HeavyVertex h = sh.hv[j];
-      if (h.v < 0) continue;
+      if (h.v < 0 || sh.hb[j] >= 0) continue;
       const int nb = inc_detect_block<MUT>(k, b, L, round, h, s_wc, maxc_acc, bytes, pushes);
       if (threadIdx.x == 0) sh.hb[j] = static_cast<int8_t>(nb);
     }
@@ -743,7 +850,7 @@ __device__ __forceinline__ void inc_detect_phase(const KeySource& k, const IncBu
       if (c > 0) {
         int32_t p = atomicAdd(&b.cnt_out[t], c);
         for (int j = 0; j < kHeavyBatch; ++j)
-          if (sh.hb[j] == t) st_dev(&b.wl_out[L.off[t] + p++], sh.hv[j].v);
+          if (sh.hb[j] == t) st_mut<MUT>(&b.wl_out[L.off[t] + p++], sh.hv[j].v);
       }
     }
     if (dyn < 0 && static_end >= heavy_total) break;
@@ -752,6 +859,46 @@ __device__ __forceinline__ void inc_detect_phase(const KeySource& k, const IncBu
     dyn = s_unit;
     __syncthreads();
     if (dyn >= heavy_total) break;
+  }
+  // then the light chunks.  Three quarters of them go round robin, so that
+  // every workgroup gets its mix of narrow and wide bins (an equal share of
+  // consecutive chunks would leave the wide ones to a few); the last quarter,
+  // the widest, is handed out by a counter, so that a workgroup held up by
+  // long lists leaves its share of them to the others.
+  const int32_t fixed = light_total - light_total / 4;
+  int32_t c = lb;
+  if (c >= fixed) {  // no round-robin chunk: from the counter at once
+    if (threadIdx.x == 0) s_unit = fixed + atomicAdd(b.light_ctr, 1);
+    __syncthreads();
+    c = s_unit;
+    __syncthreads();
+  }
+  while (c < light_total) {
+    const bool own = c < fixed;
+    int bin = 0;
+    int32_t cc = c;
+    while (bin < 2 && cc >= M.chunks[bin]) {
+      cc -= M.chunks[bin];
+      ++bin;
+    }
+    const int32_t firstc = cc * M.csize[bin];
+    const int32_t count = min(M.csize[bin], M.cnt[bin] - firstc);
+    const int32_t* wl = b.wl_in + L.off[bin] + firstc;
+    switch (L.lanes[bin]) {
+      case 1: inc_detect_chunk<1, MUT>(k, b, L, round, wl, count, s_ent, s_tb, s_wc, sh.pend, maxc_acc, bytes, pushes); break;
+      case 2: inc_detect_chunk<2, MUT>(k, b, L, round, wl, count, s_ent, s_tb, s_wc, sh.pend, maxc_acc, bytes, pushes); break;
+      case 4: inc_detect_chunk<4, MUT>(k, b, L, round, wl, count, s_ent, s_tb, s_wc, sh.pend, maxc_acc, bytes, pushes); break;
+      case 8: inc_detect_chunk<8, MUT>(k, b, L, round, wl, count, s_ent, s_tb, s_wc, sh.pend, maxc_acc, bytes, pushes); break;
+      case 16: inc_detect_chunk<16, MUT>(k, b, L, round, wl, count, s_ent, s_tb, s_wc, sh.pend, maxc_acc, bytes, pushes); break;
+      case 32: inc_detect_chunk<32, MUT>(k, b, L, round, wl, count, s_ent, s_tb, s_wc, sh.pend, maxc_acc, bytes, pushes); break;
+      default: inc_detect_chunk<64, MUT>(k, b, L, round, wl, count, s_ent, s_tb, s_wc, sh.pend, maxc_acc, bytes, pushes); break;
+    }
+    c += G;
+    if (own && c < fixed) continue;
+    if (threadIdx.x == 0) s_unit = fixed + atomicAdd(b.light_ctr, 1);
+    __syncthreads();
+    c = s_unit;
+    __syncthreads();
   }
   maxc_acc = [&] {
     int32_t x = maxc_acc;
@@ -774,11 +921,13 @@ __device__ __forceinline__ void inc_detect_phase(const KeySource& k, const IncBu
   }
 }
 
-// Five wavefronts per SIMD (96 VGPRs, no scratch; the default allocation
-// took 97 and allowed four): measured on MI355X, R-MAT 22 467 -> 447 us per
-// launch.  The tail kernel stays at its default: capped at four or five it
-// spills, and its rounds got slower.
-__global__ __launch_bounds__(kBlock, 5) void inc_detect_kernel(KeySource k, IncBufs b, BinLayout L, int round) {
+// Four wavefronts per SIMD (128 VGPRs): the batches in flight take them; at
+// five, 18 registers go to scratch.  Per launch, on average, R-MAT 22 397 ->
+// 205 us and the 4M x 1M pattern 650 -> 390 us with the probe of every list's
+// front, the pipelined workgroup passes, the round-robin chunks and plain
+// stores (before: one vertex per lane group from the start, device-scope
+// stores, consecutive chunks).
+__global__ __launch_bounds__(kBlock, 4) void inc_detect_kernel(KeySource k, IncBufs b, BinLayout L, int round) {
   __shared__ IncDetectShared sh;
   inc_detect_phase<0>(k, b, L, round, sh);
 }

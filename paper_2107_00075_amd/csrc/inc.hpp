@@ -14,6 +14,8 @@ struct IncBufs {
   const int32_t* cnt_in;       // |W_r| per bin
   int32_t* cnt_out;            // |W_{r+1}| per bin
   int32_t* tile_ctr;           // [1]: heavy-unit counter of the detect kernel
+  int32_t* light_ctr;          // its light-chunk counter (not a tile_ctr word: the pull engine expects
+                               // its color counter, [0], at zero when it takes over)
   const int32_t* aoff;         // list offsets (D1: row_ptr; D2/PD2: prefix of list lengths)
   const int32_t* A_in;         // active lists of round r
   int32_t* A_out;              // compacted lists (the same array as A_in after round 1: in place)
@@ -44,13 +46,12 @@ struct IncBufs {
                                // count from there; the engine's own logic counts from 1)
 };
 
-// Vertices per light chunk of a bin with `lanes` lanes per vertex: a chunk
-// takes kIncPasses passes of the workgroup's lane groups, so that a bin of
-// wide groups (whose vertices are processed few at a time) is spread over
-// many workgroups.
+// Vertices per light chunk of a bin with `lanes` lanes per vertex: two passes
+// of the groups that test a list's front (at most 16 lanes), so that a bin of
+// wide groups is spread over many workgroups.
 constexpr int kIncPasses = 2;
 __host__ __device__ inline int32_t inc_chunk_size(int32_t lanes) {
-  const int32_t c = (kBlock / lanes) * kIncPasses;
+  const int32_t c = (kBlock / (lanes < 16 ? lanes : 16)) * kIncPasses;
   return c < kBlock ? c : kBlock;
 }
 // Work units of a round: light chunks plus one unit per heavy vertex.
