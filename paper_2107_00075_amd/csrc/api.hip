@@ -362,7 +362,6 @@ int setup_bins(Call& c, const GraphView& g, const int32_t* init, int32_t* C, int
     s.deferred_done = w->deferred_done.as<int32_t>();
   }
   s.deferred_cnt = &S->deferred_cnt;
-  s.deferred_grab = &S->deferred_grab[0];
   s.total_work = &S->total_work;
   launch_bin<MODE>(g, s, c.st);
   c.launches += 1;
@@ -628,12 +627,14 @@ int run_incremental(Call& c, const GraphView& g, const KeySource& k, const int32
     const int32_t nb_max = sets ? static_cast<int32_t>(std::max<int64_t>(
                                       1, std::min<int64_t>(nd, kSetsBatchWords / words)))
                                 : 0;
-    launch_inc_fill<MODE>(g, aoff, len, B, Lb, w->deferred.as<int32_t>(), &S->deferred_cnt, &S->deferred_grab[1],
-                          !sets, c.st);
-    c.launches += sets ? 2 : 3;
+    int32_t* longs = c.wl[1];  // (this engine's worklists are its own)
+    launch_inc_fill<MODE>(g, aoff, len, B, Lb, longs, &S->long_cnt, w->deferred.as<int32_t>(), &S->deferred_cnt,
+                          &S->deferred_grab, !sets, c.st);
+    c.launches += sets ? 1 : 2;
     A0 = B;
-    const int grid = dedup_grid(words);
-    const size_t bm_bytes = sizeof(uint32_t) * static_cast<size_t>(words) * static_cast<size_t>(grid);
+    const bool in_memory = dedup_in_memory(words);
+    const size_t bm_bytes =
+        in_memory ? sizeof(uint32_t) * static_cast<size_t>(words) * static_cast<size_t>(dedup_grid(words)) : 0;
     const size_t sets_bytes = sizeof(uint32_t) * static_cast<size_t>(words) * static_cast<size_t>(nb_max);
     if ((e = w->inc_bm.ensure(std::max(bm_bytes, sets_bytes), false, c.st))) return e;
     for (int32_t i0 = 0; sets && i0 < nd; i0 += nb_max) {
@@ -644,8 +645,8 @@ int run_incremental(Call& c, const GraphView& g, const KeySource& k, const int32
                                    B, c.st);
       c.launches += 2;
     }
-    if (hipMemsetAsync(w->inc_bm.p, 0, bm_bytes, c.st) != hipSuccess) return COLOR_EHIP;
-    launch_inc_dedup(n, aoff, Lb, B, w->inc_bm.as<uint32_t>(), words, grid, sets ? g.rp : nullptr, c.st);
+    if (in_memory && hipMemsetAsync(w->inc_bm.p, 0, bm_bytes, c.st) != hipSuccess) return COLOR_EHIP;
+    launch_inc_dedup(longs, &S->long_cnt, aoff, Lb, B, w->inc_bm.as<uint32_t>(), words, c.st);
     c.launches += 1;
     B = w->inc_B1.as<int32_t>();  // the split lists
   }
@@ -1438,8 +1439,8 @@ static int ghost2_step_once(int32_t n_owned, int32_t n_ghost, const int32_t* rp1
   // counts still hold phase 1's
   launch_ghost_fill(n_owned, n_ghost, ghost_colors, Cint, w->T.as<int32_t>(), &c.S->maxc, c.st);
   c.launches += 2;
-  static_assert(offsetof(Scalars, deferred_grab) == offsetof(Scalars, max_work) + 2 * sizeof(int32_t),
-                "max_work, deferred_cnt and deferred_grab are cleared together");
+  static_assert(offsetof(Scalars, long_cnt) == offsetof(Scalars, max_work) + 3 * sizeof(int32_t),
+                "max_work, deferred_cnt, deferred_grab and long_cnt are cleared together");
   launch_zero_words(c.S->count_all, 16, c.st);
   launch_zero_words(c.S->cnt, sizeof(c.S->cnt) / 4, c.st);
   launch_zero_words(&c.S->max_split_work, 1, c.st);

@@ -46,7 +46,8 @@ struct Scalars {
   unsigned long long list_total; // incremental engine: entries of all lists
   int32_t max_work;              // largest work of an uncolored vertex
   int32_t deferred_cnt;          // heavy D2/PD2 vertices set up by workgroups
-  int32_t deferred_grab[2];      // their work counters (work, list fill)
+  int32_t deferred_grab;         // their work counter (list fill)
+  int32_t long_cnt;              // two-hop lists to make duplicate-free
   uint32_t bar[kBarWords];       // tail kernel: grid-barrier words
   int32_t tail_err;              // tail kernel: error bits (a barrier gave up)
   int32_t tail_left;             // tail kernel: 1 if it stopped at the round cap with vertices left
@@ -65,7 +66,7 @@ struct Workspace {
   DevBuf inc_wl0, inc_wl1;  // incremental engine: worklists binned by active-list length
   DevBuf inc_T8, inc_done;  // incremental engine: tentative colors as bytes, committed bits
   DevBuf inc_core;          // incremental engine: the core kernel's vertex order and exchange words
-  DevBuf deferred_work, deferred_done;  // setup: per heavy D2/PD2 vertex, its work and slices done
+  DevBuf deferred_work, deferred_done;  // setup: per heavy D2/PD2 vertex, its work and units done
   DevBuf rank, rk_key0, rk_key1, rk_val0, rk_val1, rk_deg0, rk_deg1, rk_tmp;  // recolorDegrees ranks
   DevBuf gr_rp, gr_ci, gr_cnt, gr_init;  // tentative ghost recoloring: local CSR with ghost rows, start colors
   DevBuf own_rp, own_ci;                 // ghost step: the owned-induced subgraph of phase 1

@@ -115,14 +115,8 @@ __device__ __forceinline__ uint32_t phase_units(const int32_t cnt[kBatchBins], c
   return u + static_cast<uint32_t>(cnt[3]);
 }
 
-// Every access to a job's mutable state is device-scope (performed beyond the
-// L2s), so handing it over needs no cache writeback or invalidation, only
-// that the accesses before have completed.  A workgroup's: before its barrier.
-__device__ __forceinline__ void wait_own_accesses() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_s_waitcnt(0);
-}
-
+// Every access to a job's mutable state is device-scope, so handing it over
+// takes wait_own_accesses only.  A workgroup's: before its barrier.
 template <int MODE, int LD>
 __device__ __forceinline__ int64_t job_vertex_work(const GraphView& g, int32_t v) {
   const int32_t b = gld<LD>(&g.rp[v]), e = gld<LD>(&g.rp[v + 1]);

@@ -172,4 +172,64 @@ __device__ __forceinline__ int32_t atomic_load_i32(const int32_t* p) {
 __device__ __forceinline__ void atomic_reset_u32(uint32_t* p) { (void)atomicExch(p, 0u); }
 __device__ __forceinline__ void atomic_reset_i32(int32_t* p) { (void)atomicExch(p, 0); }
 
+// Waits until the caller's accesses to memory have completed.  Mutable state
+// that only device-scope accesses (performed beyond the L2s) touch is handed
+// over by this and a flag; __threadfence also writes the L2 back and
+// invalidates it.
+__device__ __forceinline__ void wait_own_accesses() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0);
+}
+
+// The first hops of the vertices list[0 .. n) cut into units of at most slice
+// entries, dealt to the grid's workgroups in turn: body(i, v, a, z, slices)
+// runs for unit [a, z) of v = list[i], which has slices units, with all T
+// threads.  T vertices at a time are looked up by the T threads at once; a
+// lookup per unit, or a work counter, costs a chain of accesses each.
+template <int T>
+struct HeavyUnits {
+  int32_t wave_sum[T / kWave];
+  int32_t end[T];  // units up to and with the vertex
+};
+
+template <int T, typename F>
+__device__ __forceinline__ void for_heavy_units(const int32_t* rp, const int32_t* list, int32_t n, int32_t slice,
+                                                HeavyUnits<T>& sh, F&& body) {
+  const int tid = threadIdx.x, wave = tid / kWave;
+  int64_t done = 0;  // units of the vertices before i0
+  for (int32_t i0 = 0; i0 < n; i0 += T) {
+    int32_t incl = 0;
+    if (i0 + tid < n) {
+      const int32_t v = list[i0 + tid];
+      incl = (max(1, rp[v + 1] - rp[v]) - 1) / slice + 1;
+    }
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+      const int32_t y = __shfl_up(incl, off, kWave);
+      if (lane_id() >= off) incl += y;
+    }
+    if (lane_id() == kWave - 1) sh.wave_sum[wave] = incl;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) incl += sh.wave_sum[w];
+    sh.end[tid] = incl;
+    __syncthreads();
+    const int32_t all = sh.end[T - 1];
+    int64_t u = (done + gridDim.x - 1 - blockIdx.x) / gridDim.x * gridDim.x + blockIdx.x - done;
+    for (; u < all; u += gridDim.x) {
+      int r = 0;
+#pragma unroll
+      for (int step = T / 2; step > 0; step >>= 1) r += sh.end[r + step - 1] <= u ? step : 0;
+      const int32_t before = r > 0 ? sh.end[r - 1] : 0;
+      const int32_t slices = sh.end[r] - before, j = static_cast<int32_t>(u) - before;
+      const int32_t v = list[i0 + r];
+      const int32_t q0 = rp[v], q1 = rp[v + 1];
+      const int32_t a = q0 + j * slice;
+      body(i0 + r, v, a, q1 - a < slice ? q1 : a + slice, slices);
+      __syncthreads();
+    }
+    done += all;
+    __syncthreads();
+  }
+}
+
 }  // namespace gcol

@@ -35,6 +35,14 @@ namespace gcol {
 
 namespace {
 
+// Set building: workgroups with a bitmap of the id range in LDS (4096 words
+// for ids below 131072, 37376 for ids below 1196032), and a unit of a
+// heavy vertex's first hop.
+constexpr int kSetThreads = 1024;
+constexpr int kSetWordsSmall = 4096;
+constexpr int kSetWords = 37376;
+constexpr int32_t kSetSlice = 32768;
+
 struct IncMap {
   int32_t cnt[kBins];
   int32_t csize[3];     // vertices per chunk of bins 0..2: kIncPasses passes of the lane groups
@@ -1054,72 +1062,131 @@ __global__ __launch_bounds__(kBlock) void inc_sizes_kernel(GraphView g, const in
   st_dev(&words[v], static_cast<int32_t>(min<int64_t>(l, max(g.n, g.ids)) / 32));
 }
 
-// Materializes the two-hop list of a vertex with a short first hop (one
-// thread).  At most len(v) entries are written.  Every fill keeps only
-// members below g.limit: the colorable vertices, or (a rank's ghost step,
-// whose walks pass through ghosts) the owned ones.
-template <int MODE>
-// Every fill stores the number of entries it wrote as the list length
-// (alen), so that a list never exposes an unwritten slot, even where the
-// graph breaks the input contract and the walk is shorter than its bound.
-__global__ __launch_bounds__(kBlock) void inc_fill_kernel(GraphView g, const int32_t* aoff, const int32_t* len,
-                                                          int32_t* A, int32_t* alen) {
-  const int32_t v = blockIdx.x * kBlock + threadIdx.x;
-  if (v >= g.n || g.rp[v + 1] - g.rp[v] > kFillThread) return;
-  const int32_t base = ld_dev(&aoff[v]);
-  const int32_t end = base + ld_dev(&len[v]);
-  int32_t o = base;
-  for (int32_t q = g.rp[v]; q < g.rp[v + 1]; ++q) {
-    const int32_t u = g.ci[q];
-    if (MODE == kD2 && u < g.limit && o < end) st_dev(&A[o++], u);
-    for (int32_t p = g.rp2[u]; p < g.rp2[u + 1]; ++p) {
-      const int32_t x = g.ci2[p];
-      if (x != v && x < g.limit && o < end) st_dev(&A[o++], x);
+// Walks the second-hop rows of the first-hop entries [q0, q1) of v with a
+// group of G lanes: the rows of G first-hop entries are laid end to end by a
+// scan of their lengths and the lanes stride over the whole (the row of an
+// entry by binary search over the G ends, in LDS), so that rows of any length
+// keep every lane busy, reads are contiguous, and four entries per lane are in
+// flight.  f(x) takes a batch in every lane of the group (x < 0: none); only
+// members below g.limit other than v are given.  s_row: 2 G words.
+template <int MODE, int G, typename F>
+__device__ __forceinline__ void walk_two_hop(const GraphView& g, int32_t v, int32_t q0, int32_t q1, int32_t* s_row,
+                                             F&& f) {
+  const int sub = lane_id() & (G - 1);
+  int32_t* s_at = s_row;       // row start minus the entries before it
+  int32_t* s_end = s_row + G;  // entries up to the row's end
+  // a pass's entries are read two passes ahead, its row bounds one
+  auto entry = [&](int32_t q) { return q < q1 ? g.ci[q] : -1; };
+  int32_t u = entry(q0 + sub), un = entry(q0 + sub + G);
+  int32_t b2 = u >= 0 ? g.rp2[u] : 0, e2 = u >= 0 ? g.rp2[u + 1] : 0;
+  for (int32_t qb = q0; qb < q1; qb += G) {
+    const int32_t len = e2 - b2;
+    const int32_t unn = entry(qb + sub + 2 * G);
+    const int32_t bn = un >= 0 ? g.rp2[un] : 0, en = un >= 0 ? g.rp2[un + 1] : 0;
+    if (MODE == kD2) {
+      const int32_t x[4] = {u < g.limit ? u : -1, -1, -1, -1};
+      f(x);
     }
+    int32_t incl = len;
+#pragma unroll
+    for (int off = 1; off < G; off <<= 1) {
+      const int32_t y = __shfl_up(incl, off, G);
+      if (sub >= off) incl += y;
+    }
+    s_at[sub] = b2 - (incl - len);
+    s_end[sub] = incl;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int32_t all = s_end[G - 1];
+    for (int32_t e0 = sub; e0 - sub < all; e0 += 4 * G) {
+      int32_t x[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int32_t e = e0 + j * G;
+        int r = 0;
+#pragma unroll
+        for (int step = G / 2; step > 0; step >>= 1) r += s_end[r + step - 1] <= e ? step : 0;
+        x[j] = e < all ? g.ci2[s_at[r] + e] : -1;
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (x[j] == v || x[j] >= g.limit) x[j] = -1;
+      f(x);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    u = un;
+    un = unn;
+    b2 = bn;
+    e2 = en;
   }
-  st_dev(&alen[v], o - base);
 }
 
-// Two-hop lists of vertices with kFillThread < first-hop length <= kSetupHeavy:
-// a wavefront per vertex; each pass takes 64 first-hop entries, scans their
-// entry counts across the wavefront and writes them in first-hop order.
-template <int MODE>
-__global__ __launch_bounds__(kBlock) void inc_fill_wave_kernel(GraphView g, const int32_t* aoff,
-                                                               const int32_t* len, int32_t* A, int32_t* alen) {
-  const int32_t v = static_cast<int32_t>((blockIdx.x * kBlock + threadIdx.x) / kWave);
-  if (v >= g.n) return;
-  const int32_t q0 = g.rp[v], q1 = g.rp[v + 1];
-  if (q1 - q0 <= kFillThread || q1 - q0 > kSetupHeavy) return;
-  const int32_t end = ld_dev(&aoff[v]) + ld_dev(&len[v]);
-  int32_t out = ld_dev(&aoff[v]);
-  for (int32_t qb = q0; qb < q1; qb += kWave) {
-    const int32_t q = qb + lane_id();
-    int32_t u = -1, cnt = 0;
-    if (q < q1) {
-      u = g.ci[q];
-      cnt = (MODE == kD2 && u < g.limit) ? 1 : 0;
-      for (int32_t p = g.rp2[u]; p < g.rp2[u + 1]; ++p) {
-        const int32_t x = g.ci2[p];
-        cnt += x != v && x < g.limit;
-      }
-    }
-    int32_t incl = cnt;
+// Lists longer than this are made duplicate-free (inc_dedup kernels).
+constexpr int32_t kDedupMin = 4096;
+
+// The two-hop list of v by a group of G lanes, in walk order; at most len(v)
+// entries.  The number of entries written is the list length (alen), so that
+// a list never exposes an unwritten slot, even where the graph breaks the
+// input contract and the walk is shorter than its bound.
+template <int MODE, int G>
+__device__ __forceinline__ void inc_fill_one(const GraphView& g, int32_t v, int32_t q0, int32_t q1,
+                                             const int32_t* aoff, const int32_t* len, int32_t* A, int32_t* alen,
+                                             int32_t* longs, int32_t* n_longs, int32_t* s_row) {
+  const int sub = lane_id() & (G - 1);
+  const int first = lane_id() & ~(G - 1);
+  const uint64_t gm = (G == 64) ? ~0ull : ((1ull << G) - 1ull);
+  int32_t* out = A + aoff[v];
+  const int32_t cap = len[v];
+  int32_t n = 0;
+  walk_two_hop<MODE, G>(g, v, q0, q1, s_row, [&](const int32_t (&x)[4]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-      const int32_t y = __shfl_up(incl, off, kWave);
-      if (lane_id() >= off) incl += y;
+    for (int j = 0; j < 4; ++j) {
+      const uint64_t bal = (__ballot(x[j] >= 0) >> first) & gm;
+      const int32_t pos = n + static_cast<int32_t>(__popcll(bal & ((1ull << sub) - 1ull)));
+      if (x[j] >= 0 && pos < cap) out[pos] = x[j];
+      n += static_cast<int32_t>(__popcll(bal));
     }
-    int32_t o = out + incl - cnt;
-    if (u >= 0) {
-      if (MODE == kD2 && u < g.limit && o < end) st_dev(&A[o++], u);
-      for (int32_t p = g.rp2[u]; p < g.rp2[u + 1]; ++p) {
-        const int32_t x = g.ci2[p];
-        if (x != v && x < g.limit && o < end) st_dev(&A[o++], x);
-      }
-    }
-    out += __shfl(incl, kWave - 1, kWave);
+  });
+  if (sub == 0) {
+    n = min(n, cap);
+    alen[v] = n;
+    if (n > kDedupMin) longs[atomicAdd(n_longs, 1)] = v;
   }
-  if (lane_id() == 0) st_dev(&alen[v], min(out, end) - ld_dev(&aoff[v]));
+}
+
+// Two-hop lists of the vertices of first-hop length up to kSetupHeavy: a
+// wavefront takes four consecutive vertices, those of at most kFillGroup
+// first-hop entries with 16 lanes each at once, then the others one by one
+// with all lanes.  Bound by the latency of entry, row bounds and row, each
+// read ahead.  (A thread per short vertex, walking its rows entry by
+// entry, and a wavefront per longer one, counting and then writing a row per
+// lane, took 4.3 ms on the 4M x 1M pattern and 0.72 ms on ER n = 20,000 mean
+// degree 32.)
+template <int MODE>
+__global__ __launch_bounds__(kBlock) void inc_fill_kernel(GraphView g, const int32_t* aoff, const int32_t* len,
+                                                          int32_t* A, int32_t* alen, int32_t* longs,
+                                                          int32_t* n_longs) {
+  constexpr int kFillGroup = 16;
+  constexpr int per = kWave / kFillGroup;
+  __shared__ int32_t s_row[kWavesPerBlock][2 * kWave];
+  const int wave = threadIdx.x / kWave, grp = lane_id() / kFillGroup;
+  const int32_t base = static_cast<int32_t>((blockIdx.x * kWavesPerBlock + wave) * per);
+  const int32_t v = base + grp;
+  int32_t q0 = 0, q1 = 0;
+  if (v < g.n) {
+    q0 = g.rp[v];
+    q1 = g.rp[v + 1];
+  }
+  if (v < g.n && q1 - q0 <= kFillGroup)
+    inc_fill_one<MODE, kFillGroup>(g, v, q0, q1, aoff, len, A, alen, longs, n_longs, s_row[wave] + 2 * kFillGroup * grp);
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+  for (int i = 0; i < per; ++i) {
+    const int32_t a = __builtin_amdgcn_readlane(q0, i * kFillGroup), z = __builtin_amdgcn_readlane(q1, i * kFillGroup);
+    if (z - a > kFillGroup && z - a <= kSetupHeavy)
+      inc_fill_one<MODE, kWave>(g, base + i, a, z, aoff, len, A, alen, longs, n_longs, s_row[wave]);
+  }
 }
 
 // Two-hop lists of the heavy (deferred) vertices: a workgroup per vertex;
@@ -1129,7 +1196,8 @@ template <int MODE>
 __global__ __launch_bounds__(kBlock) void inc_fill_heavy_kernel(GraphView g, const int32_t* aoff,
                                                                 const int32_t* len, int32_t* A,
                                                                 const int32_t* deferred, const int32_t* nd_ptr,
-                                                                int32_t* grab, int32_t* alen) {
+                                                                int32_t* grab, int32_t* alen, int32_t* longs,
+                                                                int32_t* n_longs) {
   __shared__ int32_t s_i;
   __shared__ int32_t s_wt[kWavesPerBlock];
   const int32_t nd = ld_dev(nd_ptr);
@@ -1181,7 +1249,11 @@ __global__ __launch_bounds__(kBlock) void inc_fill_heavy_kernel(GraphView g, con
       out += tot;
       __syncthreads();
     }
-    if (tid == 0) st_dev(&alen[v], min(out, end) - base);
+    if (tid == 0) {
+      const int32_t n = min(out, end) - base;
+      st_dev(&alen[v], n);
+      if (n > kDedupMin) longs[atomicAdd(n_longs, 1)] = v;
+    }
   }
 }
 
@@ -1264,70 +1336,132 @@ void launch_inc_sizes(const GraphView& g, const int32_t* work, int32_t* len, int
 }
 // Duplicates of the materialized two-hop lists (a column pair sharing
 // several rows, a vertex reachable through several middle vertices) are
-// removed once per call from every list longer than kDedupMin entries: the
-// lists are sets, so the colorings do not change.  A workgroup walks one long
-// list at a time with its own bitmap of the id range; an entry is kept when
-// its atomic OR finds the bit clear.  The list is compacted in place (each
-// step's entries are read before the barrier that precedes its writes), then
-// the bits of the kept entries are cleared again.
-constexpr int32_t kDedupMin = 4096;
-
-__global__ __launch_bounds__(kBlock) void inc_dedup_kernel(int32_t n, const int32_t* aoff, int32_t* alen,
-                                                           int32_t* A, uint32_t* bitmaps, int32_t words,
-                                                           const int32_t* skip_rp) {
-  __shared__ int32_t s_wc[kWavesPerBlock];
-  const int tid = threadIdx.x;
-  const int wave = tid / kWave;
-  uint32_t* bm = bitmaps + static_cast<size_t>(blockIdx.x) * static_cast<size_t>(words);
-  constexpr int32_t step = kBlock * kIncBatch;
-  for (int32_t v = blockIdx.x; v < n; v += gridDim.x) {
-    const int32_t len = ld_dev(&alen[v]);
-    if (len <= kDedupMin) continue;
-    if (skip_rp && skip_rp[v + 1] - skip_rp[v] > kSetupHeavy) continue;  // built as sets already
-    int32_t* L = A + ld_dev(&aoff[v]);
+// removed once per call from every list longer than kDedupMin entries
+// (longs): the lists are sets, so the colorings do not change.  A workgroup
+// takes one long list at a time with a bitmap of the id range, in LDS where
+// that fits (WORDS > 0), else its own in memory; an entry is kept when its
+// atomic OR finds the bit clear.  The list is compacted in place (a step's
+// entries are read before the barrier that precedes its writes; positions
+// from ballots).
+template <int WORDS>
+__global__ __launch_bounds__(kSetThreads) void inc_dedup_kernel(const int32_t* longs, const int32_t* n_longs,
+                                                                const int32_t* aoff, int32_t* alen, int32_t* A,
+                                                                uint32_t* bitmaps, int32_t words) {
+  constexpr int kWaves = kSetThreads / kWave, N = 4;
+  __shared__ uint32_t s_bm[WORDS > 0 ? WORDS : 1];
+  __shared__ int32_t s_wc[2][kWaves];
+  const int tid = threadIdx.x, wave = tid / kWave;
+  uint32_t* bm = WORDS > 0 ? s_bm : bitmaps + static_cast<size_t>(blockIdx.x) * static_cast<size_t>(words);
+  const int32_t n = *n_longs;
+  for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const int32_t v = longs[i];
+    const int32_t len = alen[v];
+    int32_t* L = A + aoff[v];
+    if (WORDS > 0)
+      for (int w = tid; w < words; w += kSetThreads) bm[w] = 0u;
+    __syncthreads();
     int32_t kept = 0;
-    for (int32_t e0 = 0; e0 < len; e0 += step) {
-      int32_t x[kIncBatch];
-      bool keep[kIncBatch];
-      int32_t cnt = 0;
+    int par = 0;
+    for (int32_t e0 = 0; e0 < len; e0 += N * kSetThreads, par ^= 1) {
+      int32_t x[N], mine[N], tot = 0;
+      bool keep[N];
 #pragma unroll
-      for (int j = 0; j < kIncBatch; ++j) {
-        const int32_t e = e0 + j * kBlock + tid;
-        x[j] = e < len ? ld_dev(&L[e]) : -1;
+      for (int j = 0; j < N; ++j) {
+        const int32_t e = e0 + j * kSetThreads + tid;
+        x[j] = e < len ? L[e] : -1;
       }
 #pragma unroll
-      for (int j = 0; j < kIncBatch; ++j) {
-        keep[j] = false;
-        if (x[j] >= 0) {
-          const uint32_t bit = 1u << (x[j] & 31);
-          keep[j] = (atomicOr(&bm[x[j] >> 5], bit) & bit) == 0u;
-        }
-        cnt += keep[j] ? 1 : 0;
+      for (int j = 0; j < N; ++j) {
+        const uint32_t bit = 1u << (x[j] & 31);
+        keep[j] = x[j] >= 0 && (atomicOr(&bm[x[j] >> 5], bit) & bit) == 0u;
       }
-      int32_t incl = cnt;
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const uint64_t bal = __ballot(keep[j]);
+        mine[j] = tot + static_cast<int32_t>(lanes_below(bal));
+        tot += static_cast<int32_t>(__popcll(bal));
+      }
+      if (lane_id() == 0) s_wc[par][wave] = tot;
+      __syncthreads();
+      int32_t pos = kept;
+      for (int w = 0; w < kWaves; ++w) {
+        const int32_t c = s_wc[par][w];
+        if (w < wave) pos += c;
+        kept += c;
+      }
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        if (keep[j]) L[pos + mine[j]] = x[j];
+    }
+    __syncthreads();
+    if (WORDS == 0)  // the bits of the kept entries are cleared again
+      for (int32_t e = tid; e < kept; e += kSetThreads) atomicAnd(&bm[L[e] >> 5], 0u);
+    if (tid == 0) alen[v] = kept;
+    __syncthreads();
+  }
+}
+
+// The sets of heavy (deferred) vertices i0 .. i0+nb-1 with the bitmap in LDS:
+// one workgroup per CU takes units of up to kSetSlice first-hop entries (its
+// wavefronts 64 at a time) and, if that is the vertex's whole first hop,
+// writes the set out in id order; the units of a longer one OR their bits
+// into the vertex's bitmap in memory, which inc_bitmap_list_kernel turns into
+// the list.  (With a thread per first-hop entry and every bit set in memory,
+// the 2236 heavy columns of the 4M x 1M pattern took 5.2 ms.)
+template <int MODE, int WORDS>
+__global__ __launch_bounds__(kSetThreads) void inc_sets_kernel(GraphView g, const int32_t* deferred, int32_t i0,
+                                                               int32_t nb, uint32_t* gbm, int32_t words,
+                                                               const int32_t* aoff, int32_t* alen, int32_t* A) {
+  constexpr int kWaves = kSetThreads / kWave;
+  __shared__ uint32_t s_bm[WORDS];
+  __shared__ int32_t s_row[kWaves][2 * kWave];
+  __shared__ HeavyUnits<kSetThreads> s_units;
+  __shared__ int32_t s_n;
+  const int tid = threadIdx.x, wave = tid / kWave;
+  for_heavy_units<kSetThreads>(g.rp, deferred + i0, nb, kSetSlice, s_units,
+                               [&](int32_t i, int32_t v, int32_t a, int32_t z, int32_t slices)
+                                   __attribute__((always_inline)) {
+    for (int w = tid; w < words; w += kSetThreads) s_bm[w] = 0u;
+    if (tid == 0) s_n = 0;
+    __syncthreads();
+    // each wavefront a run of its own, so that its reads run ahead
+    const int32_t per = ((z - a + kSetThreads - 1) / kSetThreads) * kWave;
+    const int32_t q = a + wave * per;
+    if (q < z)
+      walk_two_hop<MODE, kWave>(g, v, q, min(q + per, z), s_row[wave],
+                                [&](const int32_t (&x)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (x[j] >= 0 && x[j] != v) atomicOr(&s_bm[x[j] >> 5], 1u << (x[j] & 31));
+      });
+    __syncthreads();
+    if (slices > 1) {
+      uint32_t* m = gbm + static_cast<size_t>(i) * static_cast<size_t>(words);
+      if (tid == 0) alen[v] = 0;
+      for (int w = tid; w < words; w += kSetThreads)
+        if (s_bm[w]) atomicOr(&m[w], s_bm[w]);
+      return;
+    }
+    int32_t* out = A + aoff[v];
+    for (int w0 = 0; w0 < words; w0 += kSetThreads) {
+      const int w = w0 + tid;
+      uint32_t x = w < words ? s_bm[w] : 0u;
+      const int32_t c = __popc(x);
+      int32_t incl = c;
 #pragma unroll
       for (int o = 1; o < kWave; o <<= 1) {
         const int32_t y = __shfl_up(incl, o, kWave);
         if (lane_id() >= o) incl += y;
       }
-      if (lane_id() == kWave - 1) s_wc[wave] = incl;
-      __syncthreads();
-      int32_t pos = kept + incl - cnt;
-      int32_t tot = 0;
-      for (int w = 0; w < kWavesPerBlock; ++w) {
-        if (w < wave) pos += s_wc[w];
-        tot += s_wc[w];
-      }
-#pragma unroll
-      for (int j = 0; j < kIncBatch; ++j)
-        if (keep[j]) st_dev(&L[pos++], x[j]);
-      kept += tot;
-      __syncthreads();
+      const int32_t tot = __shfl(incl, kWave - 1, kWave);
+      int32_t base = 0;
+      if (lane_id() == 0 && tot > 0) base = atomicAdd(&s_n, tot);
+      int32_t pos = __shfl(base, 0, kWave) + incl - c;
+      for (; x; x &= x - 1u) out[pos++] = 32 * w + __builtin_ctz(x);
     }
-    for (int32_t e = tid; e < kept; e += kBlock) st_dev(&bm[ld_dev(&L[e]) >> 5], 0u);
-    if (tid == 0) st_dev(&alen[v], kept);
     __syncthreads();
-  }
+    if (tid == 0) alen[v] = s_n;
+  });
 }
 
 // Two-hop sets of heavy (deferred) vertices built as bitmaps, for graphs
@@ -1357,10 +1491,13 @@ __global__ __launch_bounds__(kBlock) void inc_mark_kernel(GraphView g, const int
   }
 }
 
+// (rp, min_first): only of vertices with a longer first hop than min_first.
 __global__ __launch_bounds__(kBlock) void inc_bitmap_list_kernel(const int32_t* deferred, int32_t i0,
                                                                  const uint32_t* bm, int32_t words,
-                                                                 const int32_t* aoff, int32_t* alen, int32_t* A) {
+                                                                 const int32_t* aoff, int32_t* alen, int32_t* A,
+                                                                 const int32_t* rp, int32_t min_first) {
   const int32_t v = ld_dev(&deferred[i0 + static_cast<int32_t>(blockIdx.y)]);
+  if (rp[v + 1] - rp[v] <= min_first) return;
   const uint32_t* m = bm + static_cast<size_t>(blockIdx.y) * static_cast<size_t>(words);
   int32_t* out = A + ld_dev(&aoff[v]);
   for (int32_t w0 = static_cast<int32_t>(blockIdx.x * kBlock); w0 < words;
@@ -1389,37 +1526,59 @@ __global__ __launch_bounds__(kBlock) void inc_bitmap_list_kernel(const int32_t* 
 
 template <int MODE>
 void launch_inc_fill(const GraphView& g, const int32_t* aoff, const int32_t* len, int32_t* A, int32_t* alen,
-                     const int32_t* deferred, const int32_t* nd, int32_t* grab, bool heavy, hipStream_t st) {
+                     int32_t* longs, int32_t* n_longs, const int32_t* deferred, const int32_t* nd, int32_t* grab,
+                     bool heavy, hipStream_t st) {
   if (g.n <= 0) return;
-  hipLaunchKernelGGL(inc_fill_kernel<MODE>, dim3(blocks_for(g.n)), dim3(kBlock), 0, st, g, aoff, len, A, alen);
-  const int64_t wave_blocks = (static_cast<int64_t>(g.n) + kWavesPerBlock - 1) / kWavesPerBlock;
-  hipLaunchKernelGGL(inc_fill_wave_kernel<MODE>, dim3(static_cast<uint32_t>(wave_blocks)), dim3(kBlock), 0, st, g,
-                     aoff, len, A, alen);
+  constexpr int64_t per_block = kWavesPerBlock * 4;
+  hipLaunchKernelGGL(inc_fill_kernel<MODE>, dim3(static_cast<uint32_t>((g.n + per_block - 1) / per_block)),
+                     dim3(kBlock), 0, st, g, aoff, len, A, alen, longs, n_longs);
   if (heavy)
     hipLaunchKernelGGL(inc_fill_heavy_kernel<MODE>, dim3(std::min(blocks_for(g.n), 512)), dim3(kBlock), 0, st, g,
-                       aoff, len, A, deferred, nd, grab, alen);
+                       aoff, len, A, deferred, nd, grab, alen, longs, n_longs);
 }
 
 template <int MODE>
 void launch_inc_bitmap_sets(const GraphView& g, const int32_t* deferred, int32_t i0, int32_t nb, uint32_t* bm,
                             int32_t words, const int32_t* aoff, int32_t* alen, int32_t* A, hipStream_t st) {
   if (nb <= 0) return;
-  hipLaunchKernelGGL(inc_mark_kernel<MODE>, dim3(kSetsBlocksPerVertex, nb), dim3(kBlock), 0, st, g, deferred, i0, bm,
-                     words, alen);
-  const int wx = std::max(1, std::min(kSetsBlocksPerVertex, (words + kBlock - 1) / kBlock));
+  // the bitmap in LDS while it fits (the small size leaves room for several
+  // workgroups per CU); beyond, a thread per first-hop entry on memory
+  int32_t min_first = kSetSlice;
+  if (words <= kSetWordsSmall) {
+    hipLaunchKernelGGL((inc_sets_kernel<MODE, kSetWordsSmall>), dim3(1024), dim3(kSetThreads), 0, st, g,
+                       deferred, i0, nb, bm, words, aoff, alen, A);
+  } else if (words <= kSetWords) {
+    hipLaunchKernelGGL((inc_sets_kernel<MODE, kSetWords>), dim3(256), dim3(kSetThreads), 0, st, g, deferred,
+                       i0, nb, bm, words, aoff, alen, A);
+  } else {
+    min_first = 0;
+    hipLaunchKernelGGL(inc_mark_kernel<MODE>, dim3(kSetsBlocksPerVertex, nb), dim3(kBlock), 0, st, g, deferred, i0,
+                       bm, words, alen);
+  }
+  // with LDS bitmaps only the few vertices of several units are left to list
+  const int per_vertex = min_first > 0 ? kSetsBlocksPerVertex / 4 : kSetsBlocksPerVertex;
+  const int wx = std::max(1, std::min(per_vertex, (words + kBlock - 1) / kBlock));
   hipLaunchKernelGGL(inc_bitmap_list_kernel, dim3(wx, nb), dim3(kBlock), 0, st, deferred, i0, bm, words, aoff, alen,
-                     A);
+                     A, g.rp, min_first);
 }
 int dedup_grid(int32_t words) {
   const size_t per = sizeof(uint32_t) * static_cast<size_t>(words);
   const size_t cap = static_cast<size_t>(256) << 20;  // bitmaps of all workgroups together
   return static_cast<int>(std::max<size_t>(8, std::min<size_t>(256, cap / std::max<size_t>(per, 1))));
 }
+bool dedup_in_memory(int32_t words) { return words > kSetWords; }
 
-void launch_inc_dedup(int32_t n, const int32_t* aoff, int32_t* alen, int32_t* A, uint32_t* bitmaps, int32_t words,
-                      int grid, const int32_t* skip_rp, hipStream_t st) {
-  if (n > 0)
-    hipLaunchKernelGGL(inc_dedup_kernel, dim3(grid), dim3(kBlock), 0, st, n, aoff, alen, A, bitmaps, words, skip_rp);
+void launch_inc_dedup(const int32_t* longs, const int32_t* n_longs, const int32_t* aoff, int32_t* alen, int32_t* A,
+                      uint32_t* bitmaps, int32_t words, hipStream_t st) {
+  if (words <= kSetWordsSmall)
+    hipLaunchKernelGGL(inc_dedup_kernel<kSetWordsSmall>, dim3(512), dim3(kSetThreads), 0, st, longs, n_longs, aoff,
+                       alen, A, bitmaps, words);
+  else if (words <= kSetWords)
+    hipLaunchKernelGGL(inc_dedup_kernel<kSetWords>, dim3(256), dim3(kSetThreads), 0, st, longs, n_longs, aoff, alen, A,
+                       bitmaps, words);
+  else
+    hipLaunchKernelGGL(inc_dedup_kernel<0>, dim3(dedup_grid(words)), dim3(kSetThreads), 0, st, longs, n_longs, aoff,
+                       alen, A, bitmaps, words);
 }
 
 void launch_inc_init_push(const IncBufs& b, int32_t n, const int32_t* A0, hipStream_t st) {
@@ -1442,10 +1601,10 @@ template void launch_inc_bitmap_sets<kD2>(const GraphView&, const int32_t*, int3
                                           const int32_t*, int32_t*, int32_t*, hipStream_t);
 template void launch_inc_bitmap_sets<kPD2>(const GraphView&, const int32_t*, int32_t, int32_t, uint32_t*, int32_t,
                                            const int32_t*, int32_t*, int32_t*, hipStream_t);
-template void launch_inc_fill<kD2>(const GraphView&, const int32_t*, const int32_t*, int32_t*, int32_t*,
-                                   const int32_t*, const int32_t*, int32_t*, bool, hipStream_t);
-template void launch_inc_fill<kPD2>(const GraphView&, const int32_t*, const int32_t*, int32_t*, int32_t*,
-                                    const int32_t*, const int32_t*, int32_t*, bool, hipStream_t);
+template void launch_inc_fill<kD2>(const GraphView&, const int32_t*, const int32_t*, int32_t*, int32_t*, int32_t*,
+                                   int32_t*, const int32_t*, const int32_t*, int32_t*, bool, hipStream_t);
+template void launch_inc_fill<kPD2>(const GraphView&, const int32_t*, const int32_t*, int32_t*, int32_t*, int32_t*,
+                                    int32_t*, const int32_t*, const int32_t*, int32_t*, bool, hipStream_t);
 
 int exclusive_scan_i32(const int32_t* in, int32_t* out, int32_t n_plus_1, void* tmp, size_t* tmp_bytes,
                        hipStream_t st) {

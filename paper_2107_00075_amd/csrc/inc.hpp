@@ -110,13 +110,13 @@ void launch_inc_detect(const KeySource& k, const IncBufs& b, const BinLayout& L,
 template <int MODE>
 void launch_inc_sizes(const GraphView& g, const int32_t* work, int32_t* len, int32_t* words, int32_t* alen0,
                       unsigned long long* total, hipStream_t st);
-// Materializes the two-hop lists: one thread per vertex of first-hop length
-// up to kFillThread, a wavefront per vertex up to kSetupHeavy, and (heavy)
-// one workgroup per deferred vertex.
-constexpr int32_t kFillThread = 16;
+// Materializes the two-hop lists of the vertices of first-hop length up to
+// kSetupHeavy, and (heavy) one workgroup per deferred vertex; lists that may
+// hold many duplicates go to longs.
 template <int MODE>
 void launch_inc_fill(const GraphView& g, const int32_t* aoff, const int32_t* len, int32_t* A, int32_t* alen,
-                     const int32_t* deferred, const int32_t* nd, int32_t* grab, bool heavy, hipStream_t st);
+                     int32_t* longs, int32_t* n_longs, const int32_t* deferred, const int32_t* nd, int32_t* grab,
+                     bool heavy, hipStream_t st);
 // The lists of deferred vertices i0 .. i0+nb-1 as duplicate-free sets, through
 // bitmaps of `words` words each (bm: nb x words, zeroed by the caller); alen
 // receives the set sizes.
@@ -133,13 +133,13 @@ template <int MODE>
 void launch_inc_init_pull(const GraphView& g, int32_t nnz1, const IncBufs& b, hipStream_t st);
 // T8 cleared and the committed bits (n / 32 + 1 words) set from C.
 void launch_inc_state_init(int32_t n, const int32_t* C, uint8_t* T8, uint32_t* done, hipStream_t st);
-// Removes duplicates from the long two-hop lists (alen in: capacity, out:
-// distinct entries); bitmaps: grid x words zeroed uint32 (left zeroed).
+// Removes duplicates from the lists of longs (alen in: entries, out: distinct
+// entries); bitmaps: dedup_grid x words zeroed uint32 (left zeroed), needed
+// only where dedup_in_memory(words).
 int dedup_grid(int32_t words);
-// skip_rp (nullable): the first-hop row offsets; vertices deferred by their
-// first-hop length are skipped (their lists were built as sets).
-void launch_inc_dedup(int32_t n, const int32_t* aoff, int32_t* alen, int32_t* A, uint32_t* bitmaps, int32_t words,
-                      int grid, const int32_t* skip_rp, hipStream_t st);
+bool dedup_in_memory(int32_t words);
+void launch_inc_dedup(const int32_t* longs, const int32_t* n_longs, const int32_t* aoff, int32_t* alen, int32_t* A,
+                      uint32_t* bitmaps, int32_t words, hipStream_t st);
 int resident_inc_blocks();
 
 // Exclusive prefix sum of n+1 int32 values (the last input is 0, so out[n] is

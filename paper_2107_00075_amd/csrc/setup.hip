@@ -9,6 +9,26 @@
 
 namespace gcol {
 
+// Sum of 1 + (second-hop row length) over the first-hop entries beg, beg +
+// stride, ... below end, eight in flight.
+__device__ __forceinline__ int64_t hop_work(const GraphView& g, int32_t beg, int32_t end, int32_t stride) {
+  constexpr int N = 8;
+  int64_t w = 0;
+  for (int32_t q = beg; q < end; q += N * stride) {
+    int32_t u[N], a[N], z[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) u[j] = q + j * stride < end ? g.ci[q + j * stride] : -1;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      a[j] = u[j] >= 0 ? g.rp2[u[j]] : 0;
+      z[j] = u[j] >= 0 ? g.rp2[u[j] + 1] : -1;
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) w += 1 + (z[j] - a[j]);
+  }
+  return w;
+}
+
 // Adjacency entries one visit of v reads: D1 deg(v); D2 sum over u in N(v)
 // of 1 + deg(u); PD2 sum over the rows r of column v of 1 + deg(r) (the
 // row entry of the CSC, then the row's columns in the CSR).
@@ -16,12 +36,7 @@ template <int MODE>
 __device__ __forceinline__ int64_t vertex_work(const GraphView& g, int32_t v) {
   const int32_t b = g.rp[v], e = g.rp[v + 1];
   if (MODE == kD1) return e - b;
-  int64_t w = 0;
-  for (int32_t q = b; q < e; ++q) {
-    const int32_t u = g.ci[q];
-    w += 1 + (g.rp2[u + 1] - g.rp2[u]);
-  }
-  return w;
+  return hop_work(g, b, e, 1);
 }
 
 // Bookkeeping of one vertex once its work is known: work, bin, initial colors,
@@ -151,9 +166,10 @@ __device__ void flush_acc(const BinSetup& s, BinAcc& a) {
   }
 }
 
+constexpr int32_t kThreadHop = 16;  // first-hop entries a thread sums by itself
+
 // A grid-stride loop, one thread per vertex.  D2/PD2 vertices whose first
-// hop is longer than kSetupHeavy entries are deferred to heavy_work_kernel
-// (a workgroup each).
+// hop is longer than kSetupHeavy entries are deferred to heavy_work_kernel.
 template <int MODE>
 __global__ __launch_bounds__(kBlock) void bin_kernel(GraphView g, BinSetup s) {
   BinAcc acc;
@@ -177,57 +193,66 @@ __global__ __launch_bounds__(kBlock) void bin_kernel(GraphView g, BinSetup s) {
       }
     }
     active = active && !defer;
-    if (active) record_vertex(s, v, vertex_work<MODE>(g, v), acc);
+    if (MODE == kD1) {
+      if (active) record_vertex(s, v, vertex_work<MODE>(g, v), acc);
+    } else {
+      // a longer first hop is summed by the whole wavefront (a thread alone
+      // walked up to kSetupHeavy entries: 1.06 ms on the 4M x 1M pattern)
+      const int32_t q0 = active ? g.rp[v] : 0, q1 = active ? g.rp[v + 1] : 0;
+      const bool wide = q1 - q0 > kThreadHop;
+      int64_t w = wide ? 0 : hop_work(g, q0, q1, 1);
+      uint64_t bal = __ballot(wide);
+      while (bal) {
+        const int l = __builtin_ctzll(bal);
+        bal &= bal - 1ull;
+        const int32_t a = __builtin_amdgcn_readlane(q0, l), z = __builtin_amdgcn_readlane(q1, l);
+        int64_t x = hop_work(g, a + lane_id(), z, kWave);
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) x += __shfl_xor(x, off, kWave);
+        if (lane_id() == l) w = x;
+      }
+      if (active) record_vertex(s, v, w, acc);
+    }
   }
   flush_acc(s, acc);
 }
 
-// Deferred heavy vertices: each is cut into kHeavySlices equal ranges of its
-// first hop, handed out as units; a unit's workgroup adds its range's
-// contributions to the vertex's sum, and the workgroup that completes the
-// last range records the vertex.  (One workgroup per vertex left the
-// longest first hop on one workgroup: 2.6 ms on the 4M x 1M PD2 pattern.)
-constexpr int kHeavySlices = 16;
+// Deferred heavy vertices: units of up to kHeavySlice first-hop entries; a
+// vertex of one unit is recorded at once, the units of a longer one add their
+// sums up and the workgroup that completes the last records it.  The sums and
+// counters are device-scope, so the hand-over waits for the unit's own
+// accesses only.  (With sixteen equal ranges a vertex off one work counter and
+// a cache writeback and invalidation per range, the 2236 heavy columns of the
+// 4M x 1M PD2 pattern took 2.4 ms.)
+constexpr int32_t kHeavySlice = 4096;
 
 template <int MODE>
 __global__ __launch_bounds__(kBlock) void heavy_work_kernel(GraphView g, BinSetup s) {
-  __shared__ int32_t s_u, s_last;
+  __shared__ HeavyUnits<kBlock> s_units;
   __shared__ unsigned long long s_sum;
-  const int32_t nd = ld_dev(s.deferred_cnt);
-  const int64_t units = static_cast<int64_t>(nd) * kHeavySlices;
-  while (true) {
-    if (threadIdx.x == 0) {
-      s_u = atomicAdd(s.deferred_grab, 1);
-      s_sum = 0ull;
-    }
+  __shared__ int32_t s_last;
+  for_heavy_units<kBlock>(g.rp, s.deferred, ld_dev(s.deferred_cnt), kHeavySlice, s_units,
+                          [&](int32_t i, int32_t v, int32_t a, int32_t z, int32_t slices)
+                              __attribute__((always_inline)) {
+    if (threadIdx.x == 0) s_sum = 0ull;
     __syncthreads();
-    const int32_t u = s_u;
-    if (u >= units) break;
-    const int32_t i = u / kHeavySlices, j = u % kHeavySlices;
-    const int32_t v = ld_dev(&s.deferred[i]);
-    const int32_t q0 = g.rp[v], len = g.rp[v + 1] - q0;
-    const int32_t a = q0 + static_cast<int32_t>(static_cast<int64_t>(len) * j / kHeavySlices);
-    const int32_t z = q0 + static_cast<int32_t>(static_cast<int64_t>(len) * (j + 1) / kHeavySlices);
-    uint64_t w = 0;
-    for (int32_t q = a + static_cast<int32_t>(threadIdx.x); q < z; q += kBlock) {
-      const int32_t x = g.ci[q];
-      w += 1 + static_cast<uint64_t>(g.rp2[x + 1] - g.rp2[x]);
-    }
+    uint64_t w = static_cast<uint64_t>(hop_work(g, a + static_cast<int32_t>(threadIdx.x), z, kBlock));
 #pragma unroll
     for (int off = 1; off < kWave; off <<= 1) w += __shfl_xor(w, off, kWave);
     if (lane_id() == 0 && w) atomicAdd(&s_sum, static_cast<unsigned long long>(w));
     __syncthreads();
     if (threadIdx.x == 0) {
-      if (s_sum) atomicAdd(&s.deferred_work[i], s_sum);
-      __threadfence();
-      s_last = atomicAdd(&s.deferred_done[i], 1) == kHeavySlices - 1 ? 1 : 0;
-      __threadfence();
+      s_last = 1;
+      if (slices > 1) {
+        atomicAdd(&s.deferred_work[i], s_sum);
+        wait_own_accesses();
+        s_last = atomicAdd(&s.deferred_done[i], 1) == slices - 1 ? 1 : 0;
+        if (s_last) s_sum = ld_dev(&s.deferred_work[i]);
+      }
     }
     __syncthreads();
-    if (s_last && threadIdx.x < kWave)
-      account_vertex(s, v, static_cast<int64_t>(ld_dev(&s.deferred_work[i])), threadIdx.x == 0);
-    __syncthreads();
-  }
+    if (s_last && threadIdx.x < kWave) account_vertex(s, v, static_cast<int64_t>(s_sum), threadIdx.x == 0);
+  });
 }
 
 // Appends every uncolored vertex (C[v] == 0) to its bin's region of the

@@ -24,9 +24,8 @@ struct BinSetup {
   unsigned long long* total_work;    // out: work of the initial worklist
   int32_t* deferred;                 // out: heavy D2/PD2 vertices (workgroup setup)
   int32_t* deferred_cnt;             // out: their number
-  int32_t* deferred_grab;            // work counter of heavy_work_kernel
-  unsigned long long* deferred_work; // per deferred vertex: its work, summed over slices
-  int32_t* deferred_done;            // per deferred vertex: slices done
+  unsigned long long* deferred_work; // per deferred vertex: its work, summed over its units
+  int32_t* deferred_done;            // per deferred vertex: units done
 };
 
 template <int MODE>
