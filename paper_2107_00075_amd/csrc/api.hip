@@ -295,8 +295,8 @@ int run_phase(Call& c, const GraphView& g, const KeySource& k, const BinLayout& 
       const int pin = (local - 1) & 1, pout = local & 1;
       b.wl_in = wl[pin];
       b.wl_out = wl[pout];
-      b.cnt_in = S->cnt[pin];
-      b.cnt_out = S->cnt[pout];
+      b.cnt_in = S->half[pin].cnt;
+      b.cnt_out = S->half[pout].cnt;
       if (c.timing && c.record_event(0)) return COLOR_EHIP;
       launch_color_round<MODE>(g, k, b, L, round0 + local, grid, c.st);
       if (c.timing && c.record_event(1)) return COLOR_EHIP;
@@ -307,11 +307,11 @@ int run_phase(Call& c, const GraphView& g, const KeySource& k, const BinLayout& 
       c.detect_launches += 1;
     }
     if (hipGetLastError() != hipSuccess) return COLOR_EHIP;
-    if (hipMemcpyAsync(H->cnt[local & 1], S->cnt[local & 1], sizeof(int32_t) * 8, hipMemcpyDeviceToHost,
+    if (hipMemcpyAsync(H->half[local & 1].cnt, S->half[local & 1].cnt, sizeof(int32_t) * 8, hipMemcpyDeviceToHost,
                        c.st) != hipSuccess)
       return COLOR_EHIP;
     if (hipStreamSynchronize(c.st) != hipSuccess) return COLOR_EHIP;
-    for (int i = 0; i < kBins; ++i) known[i] = H->cnt[local & 1][i];
+    for (int i = 0; i < kBins; ++i) known[i] = H->half[local & 1].cnt[i];
     R = std::min(R * 2, 64);
   }
   return COLOR_OK;
@@ -340,8 +340,8 @@ int setup_bins(Call& c, const GraphView& g, const int32_t* init, int32_t* C, int
   s.T = w->T.as<int32_t>();
   s.work = w->work.as<int32_t>();
   s.bin = w->bin.as<int8_t>();
-  s.count_all = S->count_all;
-  s.count_unc = S->count_unc;
+  s.count_all = S->half[0].bins;
+  s.count_unc = S->half[1].bins;
   s.maxc = &S->maxc;
   s.max_split_work = &S->max_split_work;
   s.max_work = &S->max_work;
@@ -372,7 +372,7 @@ int setup_bins(Call& c, const GraphView& g, const int32_t* init, int32_t* C, int
   int32_t off = 0;
   for (int i = 0; i < kBins; ++i) {
     L.off[i] = off;
-    off += H->count_all[i];
+    off += H->half[0].bins[i];
   }
   for (int i = 0; i < 3; ++i) {
     L.lanes[i] = c.P.lanes[i];
@@ -380,7 +380,7 @@ int setup_bins(Call& c, const GraphView& g, const int32_t* init, int32_t* C, int
   }
   L.split_chunks = c.P.split_chunks;
   L.grab = 4;
-  const int32_t nsplit = H->count_all[kSplitBin];
+  const int32_t nsplit = H->half[0].bins[kSplitBin];
   const int64_t bound = std::min<int64_t>(H->max_split_work, n_total);
   int32_t capw = static_cast<int32_t>(bound / 32 + 2);
   if (nsplit > 0) {
@@ -401,14 +401,14 @@ int setup_bins(Call& c, const GraphView& g, const int32_t* init, int32_t* C, int
   rb.split_ctr = w->split_ctr.as<uint32_t>();
   rb.split_flag = w->split_flag.as<uint32_t>();
   rb.maxc = &S->maxc;
-  rb.visits = S->visits;
+  rb.visits = S->lines[0].visits;
   rb.trace = w->trace.as<int32_t>();
   rb.trace_cap = c.trace_cap;
   rb.rounds_done = &S->rounds_done;
 
-  launch_scatter(n, C, w->bin.as<int8_t>(), L, c.wl[0], S->cnt[0], w->split_vertex.as<int32_t>(), c.st);
+  launch_scatter(n, C, w->bin.as<int8_t>(), L, c.wl[0], S->half[0].cnt, w->split_vertex.as<int32_t>(), c.st);
   c.launches += 1;
-  for (int i = 0; i < kBins; ++i) known[i] = H->count_unc[i];
+  for (int i = 0; i < kBins; ++i) known[i] = H->half[1].bins[i];
   return hipGetLastError() == hipSuccess ? COLOR_OK : COLOR_EHIP;
 }
 
@@ -430,6 +430,17 @@ void launch_zero_words(void* p, size_t words, hipStream_t st) {
   if (words == 0) return;
   hipLaunchKernelGGL(zero_words_kernel, dim3(static_cast<unsigned>((words + 255) / 256)), dim3(256), 0, st,
                      static_cast<uint32_t*>(p), words);
+}
+
+// The grid-barrier words and the tail flags, before a cooperative launch.
+__global__ void clear_bar_kernel(Scalars* S) {
+  const int i = threadIdx.x;
+  if (i < kBarWords / 32 * 16) S->lines[i / 16].bar[i % 16] = 0u;
+  if (i == 0) S->tail_err = S->tail_left = 0;
+}
+
+static void launch_clear_bar(Scalars* S, hipStream_t st) {
+  hipLaunchKernelGGL(clear_bar_kernel, dim3(1), dim3(256), 0, st, S);
 }
 
 int begin_call(Call& c, int mode, const color_params* user, color_stats* stats, void* stream, int32_t n,
@@ -475,14 +486,20 @@ int begin_call(Call& c, int mode, const color_params* user, color_stats* stats, 
   return hipGetLastError() == hipSuccess ? COLOR_OK : COLOR_EHIP;
 }
 
+// num_colors: num_colors_hint, or (negative) read back: kColorsAuxMax the
+// scalar aux_max, else the largest committed color.
+constexpr int32_t kColorsAuxMax = -2;
+
 int finish_call(Call& c, color_stats* stats, int32_t num_colors_hint, int rc) {
   if (hipMemcpyAsync(c.H, c.S, sizeof(Scalars), hipMemcpyDeviceToHost, c.st) != hipSuccess) return COLOR_EHIP;
   if (hipStreamSynchronize(c.st) != hipSuccess) return COLOR_EHIP;
   if (stats) {
-    stats->num_colors = num_colors_hint >= 0 ? num_colors_hint : c.H->maxc;
+    stats->num_colors = num_colors_hint >= 0                ? num_colors_hint
+                        : num_colors_hint == kColorsAuxMax ? c.H->aux_max
+                                                           : c.H->maxc;
     stats->rounds = c.H->rounds_done;
-    stats->vertex_visits = static_cast<int64_t>(c.H->visits[0]);
-    stats->edge_visits = static_cast<int64_t>(c.H->visits[1]);
+    stats->vertex_visits = static_cast<int64_t>(c.H->visits(0));
+    stats->edge_visits = static_cast<int64_t>(c.H->visits(1));
     stats->boundary_conflicts = static_cast<int64_t>(c.H->conflicts);
     stats->remote_losers = static_cast<int64_t>(c.H->remote);
     stats->kernel_launches = c.launches;
@@ -493,12 +510,12 @@ int finish_call(Call& c, color_stats* stats, int32_t num_colors_hint, int rc) {
     stats->engine = c.engine;
     stats->tail_rounds = c.tail_rounds;
     stats->tail_kernel_ns = 0;
-    stats->tail_bytes = static_cast<int64_t>(c.H->visits[6] + c.H->visits[7]);
+    stats->tail_bytes = static_cast<int64_t>(c.H->visits(6) + c.H->visits(7));
     stats->tail_fallbacks = c.tail_fallbacks;
-    stats->list_visits = static_cast<int64_t>(c.H->visits[2]);
-    stats->color_bytes = static_cast<int64_t>(c.H->visits[3]);
-    stats->detect_bytes = static_cast<int64_t>(c.H->visits[4]);
-    stats->pushes = static_cast<int64_t>(c.H->visits[5]);
+    stats->list_visits = static_cast<int64_t>(c.H->visits(2));
+    stats->color_bytes = static_cast<int64_t>(c.H->visits(3));
+    stats->detect_bytes = static_cast<int64_t>(c.H->visits(4));
+    stats->pushes = static_cast<int64_t>(c.H->visits(5));
     if (c.timing) {
       // event i opens a kernel of kind event_kind[i] that event i+1 closes
       for (size_t i = 0; i + 1 < c.n_events; ++i) {
@@ -661,7 +678,7 @@ int run_incremental(Call& c, const GraphView& g, const KeySource& k, const int32
   ib.F = w->inc_F.as<uint32_t>();
   ib.Fx = ib.F + n;
   ib.maxc = &S->maxc;
-  ib.acc = S->visits;
+  ib.acc = S->lines[0].visits;
   ib.trace = w->trace.as<int32_t>();
   ib.trace_cap = c.trace_cap;
   ib.rounds_done = &S->rounds_done;
@@ -737,8 +754,8 @@ int run_incremental(Call& c, const GraphView& g, const KeySource& k, const int32
     const int pin = (r - 1) & 1, pout = r & 1;
     b.wl_in = wl[pin];
     b.wl_out = wl[pout];
-    b.cnt_in = S->cnt[pin];
-    b.cnt_out = S->cnt[pout];
+    b.cnt_in = S->half[pin].cnt;
+    b.cnt_out = S->half[pout].cnt;
     // without initial colors round 1's losers leave the lists unsplit (the
     // read-only adjacency or two-hop lists); round 2 reads those and writes
     // the first compacted, key-split lists, which later rounds compact in place
@@ -761,14 +778,11 @@ int run_incremental(Call& c, const GraphView& g, const KeySource& k, const int32
   int64_t prev_total = 0;
   int prev_local = 0;
   const int cap = max_rounds > 0 ? max_rounds : INT_MAX;
-  static_assert(offsetof(Scalars, tail_left) == offsetof(Scalars, bar) + sizeof(Scalars::bar) + sizeof(int32_t),
-                "barrier words and tail flags are cleared together");
   // What a cooperative launch left: its error bits and flag, the rounds done
   // and the next worklist's counts.
   auto after_launch = [&]() -> int {
     c.launches += 1;
-    if (hipMemcpyAsync(&H->tail_err, &S->tail_err, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, c.st) != hipSuccess ||
-        hipMemcpyAsync(H, S, offsetof(Scalars, max_split_work), hipMemcpyDeviceToHost, c.st) != hipSuccess)
+    if (hipMemcpyAsync(H, S, offsetof(Scalars, max_split_work), hipMemcpyDeviceToHost, c.st) != hipSuccess)
       return COLOR_EHIP;
     return hipStreamSynchronize(c.st) == hipSuccess ? COLOR_OK : COLOR_EHIP;
   };
@@ -783,9 +797,9 @@ int run_incremental(Call& c, const GraphView& g, const KeySource& k, const int32
       core_on = w->inc_core.ensure(core_scratch_bytes(left), false, c.st) == COLOR_OK;
       if (core_on) {
         const IncBufs b = round_bufs(local + 1);
-        if (hipMemsetAsync(S->bar, 0, sizeof(S->bar) + 2 * sizeof(int32_t), c.st) != hipSuccess) return COLOR_EHIP;
+        launch_clear_bar(S, c.st);
         if (c.timing && c.record_event(2)) return COLOR_EHIP;
-        if (launch_core(k, b, IL, known, left, b.A_in == b.A_out, local + 1, cap, w->inc_core.p, S->bar, &S->tail_err,
+        if (launch_core(k, b, IL, known, left, b.A_in == b.A_out, local + 1, cap, w->inc_core.p, S->lines[0].bar, &S->tail_err,
                         &S->tail_left, c.P.tail_checkin_us, c.st)) {
           if (c.timing && c.record_event(-1)) return COLOR_EHIP;
           c.launches += core_launches(left) - 1;
@@ -824,14 +838,14 @@ int run_incremental(Call& c, const GraphView& g, const KeySource& k, const int32
       set.base.bytes_slot = 6;
       set.wl0 = wl[0];
       set.wl1 = wl[1];
-      set.cnt0 = S->cnt[0];
-      set.cnt1 = S->cnt[1];
+      set.cnt0 = S->half[0].cnt;
+      set.cnt1 = S->half[1].cnt;
       set.A0 = A0;
       set.uniform1 = init ? 0 : 1;
       set.defer1 = init ? 0 : 1;
-      if (hipMemsetAsync(S->bar, 0, sizeof(S->bar) + 2 * sizeof(int32_t), c.st) != hipSuccess) return COLOR_EHIP;
+      launch_clear_bar(S, c.st);
       if (c.timing && c.record_event(2)) return COLOR_EHIP;
-      if (launch_inc_tail(k, set, IL, local + 1, cap, core_on ? static_cast<int32_t>(core_at) : 0, S->bar,
+      if (launch_inc_tail(k, set, IL, local + 1, cap, core_on ? static_cast<int32_t>(core_at) : 0, S->lines[0].bar,
                           &S->tail_err, &S->tail_left, static_cast<int>(std::max<int64_t>(1, g)),
                           c.P.tail_checkin_us, c.st)) {
         if (c.timing && c.record_event(-1)) return COLOR_EHIP;
@@ -848,7 +862,7 @@ int run_incremental(Call& c, const GraphView& g, const KeySource& k, const int32
         c.tail_rounds += done - local;
         local = done;
         if (H->tail_left) return COLOR_ENOCONVERGE;
-        for (int i = 0; i < kBins; ++i) known[i] = H->cnt[local & 1][i];
+        for (int i = 0; i < kBins; ++i) known[i] = H->half[local & 1].cnt[i];
         continue;
       }
       // cooperative launch refused: per-round launches from here on
@@ -887,11 +901,11 @@ int run_incremental(Call& c, const GraphView& g, const KeySource& k, const int32
       c.detect_launches += 1;
     }
     if (hipGetLastError() != hipSuccess) return COLOR_EHIP;
-    if (hipMemcpyAsync(H->cnt[local & 1], S->cnt[local & 1], sizeof(int32_t) * 8, hipMemcpyDeviceToHost, c.st) !=
+    if (hipMemcpyAsync(H->half[local & 1].cnt, S->half[local & 1].cnt, sizeof(int32_t) * 8, hipMemcpyDeviceToHost, c.st) !=
         hipSuccess)
       return COLOR_EHIP;
     if (hipStreamSynchronize(c.st) != hipSuccess) return COLOR_EHIP;
-    for (int i = 0; i < kBins; ++i) known[i] = H->cnt[local & 1][i];
+    for (int i = 0; i < kBins; ++i) known[i] = H->half[local & 1].cnt[i];
     // a round cap inside the tail threshold is reached by the tail kernel
     R = std::min(R * 2, 64);
   }
@@ -1226,11 +1240,22 @@ static int ghost_step_once(int32_t n_owned, int32_t n_ghost, int32_t layers, int
     if ((e = degree_rank(c, m, row_ptr, n_owned, ghost_degree, k))) return e;
   }
   // phase 1: ghost-blind rounds on the owned-induced subgraph (with
-  // init_owned: only over the owned vertices it leaves uncolored), built
-  // once: the owned rows without their ghost entries, on either engine
+  // init_owned: only over the owned vertices it leaves uncolored, so none
+  // where it colors all of them, as in every step of a rank but its first),
+  // built once: the owned rows without their ghost entries, on either engine
+  int32_t* loser = w->aux0.as<int32_t>();
+  int32_t* gflag = w->aux1.as<int32_t>();
+  launch_ghost_begin(n_owned, n_ghost, init_owned, Cint, w->T.as<int32_t>(), loser, gflag, &c.S->maxc,
+                     &c.S->uncolored, c.st);
+  c.launches += 1;
+  if (hipMemcpyAsync(&c.H->uncolored, &c.S->uncolored, sizeof(c.S->uncolored), hipMemcpyDeviceToHost, c.st) !=
+      hipSuccess)
+    return COLOR_EHIP;
   int32_t owned_nnz = 0;
   if ((e = read_nnz(c, row_ptr, n_owned, &owned_nnz))) return e;
-  {
+  int rc = COLOR_OK, r1 = 0;
+  c.engine = COLOR_ENGINE_PULL;
+  if (!init_owned || c.H->uncolored > 0) {
     const size_t n1 = static_cast<size_t>(n_owned) + 1;
     const size_t e1 = static_cast<size_t>(owned_nnz) + 1;
     size_t scan_bytes = 0;
@@ -1251,39 +1276,26 @@ static int ghost_step_once(int32_t n_owned, int32_t n_ghost, int32_t layers, int
     launch_owned_subgraph(n_owned, owned_nnz, row_ptr, col_idx, flag, pos, rp1, w->own_ci.as<int32_t>(), nullptr, 0,
                           c.st);
     c.launches += 3;
+    GraphView g1{n_owned, n_owned, w->own_rp.as<int32_t>(), w->own_ci.as<int32_t>(), w->own_rp.as<int32_t>(),
+                 w->own_ci.as<int32_t>()};
+    rc = run_engine<kD1>(c, g1, k, init_owned, Cint, m);
+    if (rc != COLOR_OK) return rc == COLOR_ENOCONVERGE ? finish_call(c, stats, -1, rc) : rc;
+    if (hipMemcpyAsync(&c.H->rounds_done, &c.S->rounds_done, sizeof(int32_t), hipMemcpyDeviceToHost, c.st) !=
+        hipSuccess)
+      return COLOR_EHIP;
+    if (hipStreamSynchronize(c.st) != hipSuccess) return COLOR_EHIP;
+    r1 = c.H->rounds_done;
   }
-  GraphView g1{n_owned, n_owned, w->own_rp.as<int32_t>(), w->own_ci.as<int32_t>(), w->own_rp.as<int32_t>(),
-               w->own_ci.as<int32_t>()};
-  int rc = run_engine<kD1>(c, g1, k, init_owned, Cint, m);
-  if (rc != COLOR_OK) return rc == COLOR_ENOCONVERGE ? finish_call(c, stats, -1, rc) : rc;
   // phases 2 and 3 read the full local rows
   GraphView g{n_owned, n_owned, row_ptr, col_idx, row_ptr, col_idx};
-  if (hipMemcpyAsync(&c.H->rounds_done, &c.S->rounds_done, sizeof(int32_t), hipMemcpyDeviceToHost, c.st) !=
-      hipSuccess)
-    return COLOR_EHIP;
-  if (hipStreamSynchronize(c.st) != hipSuccess) return COLOR_EHIP;
-  const int r1 = c.H->rounds_done;
   // phase 2: boundary conflicts against the ghosts' fixed colors
-  int32_t* loser = w->aux0.as<int32_t>();
-  int32_t* gflag = w->aux1.as<int32_t>();
-  if (hipMemsetAsync(gflag, 0, sizeof(int32_t) * static_cast<size_t>(std::max(n_ghost, 1)), c.st) != hipSuccess)
-    return COLOR_EHIP;
-  launch_zero_words(loser, static_cast<size_t>(n_owned), c.st);
   launch_boundary(n_owned, owned_nnz, row_ptr, col_idx, Cint, ghost_colors, k, loser, gflag, &c.S->conflicts, c.st);
-  launch_boundary_uncolor(n_owned, loser, Cint, c.st);
-  // phase 3: ghosts become fixed committed colors; losers are recolored
-  launch_ghost_fill(n_owned, n_ghost, ghost_colors, Cint, w->T.as<int32_t>(), &c.S->maxc, c.st);
-  c.launches += 3;
-  // the phase-3 bin setup counts afresh: per-bin totals, maxima and the
-  // worklist counts, whose ping-pong halves still hold phase 1's last rounds
-  static_assert(offsetof(Scalars, count_unc) == offsetof(Scalars, count_all) + sizeof(Scalars::count_all),
-                "per-bin counts are cleared together");
-  launch_zero_words(c.S->count_all, 16, c.st);
-  launch_zero_words(c.S->cnt, sizeof(c.S->cnt) / 4, c.st);
-  launch_zero_words(&c.S->max_split_work, 1, c.st);
-  launch_zero_words(&c.S->max_work, 1, c.st);
-  launch_zero_words(&c.S->total_work, 2, c.st);
-  c.launches += 5;
+  // phase 3: ghosts become fixed committed colors; losers are recolored.  The
+  // bin setup counts afresh: per-bin totals, maxima and the worklist counts,
+  // whose ping-pong halves still hold phase 1's last rounds
+  launch_recolor_begin(n_owned, n_ghost, loser, ghost_colors, Cint, w->T.as<int32_t>(), &c.S->maxc,
+                       reinterpret_cast<uint32_t*>(c.S->half), kPhaseWords, c.st);
+  c.launches += 2;
   if (!grec) {
     // the owned losers on the full rows, ghosts as fixed constraints
     g.limit = m;
@@ -1331,15 +1343,10 @@ static int ghost_step_once(int32_t n_owned, int32_t n_ghost, int32_t layers, int
     rc = run_phase<kD1>(c, g3, k, L3, rb3, known3, r1, c.P.max_rounds);
   }
   if (rc != COLOR_OK && rc != COLOR_ENOCONVERGE) return rc;
-  launch_flags_out(n_ghost, gflag, remote_loser, &c.S->remote, c.st);
-  launch_copy_i32(n_owned, Cint, owned_colors, c.st);
-  launch_max_i32(n_owned, Cint, &c.S->aux_max, c.st);
-  c.launches += 3;
+  launch_ghost_out(n_owned, n_ghost, Cint, gflag, owned_colors, remote_loser, &c.S->aux_max, &c.S->remote, c.st);
+  c.launches += 1;
   if (hipGetLastError() != hipSuccess) return COLOR_EHIP;
-  if (hipMemcpyAsync(&c.H->aux_max, &c.S->aux_max, sizeof(int32_t), hipMemcpyDeviceToHost, c.st) != hipSuccess)
-    return COLOR_EHIP;
-  if (hipStreamSynchronize(c.st) != hipSuccess) return COLOR_EHIP;
-  return finish_call(c, stats, c.H->aux_max, rc);
+  return finish_call(c, stats, kColorsAuxMax, rc);
 }
 
 // A step whose tail kernel's grid barrier gave up starts over with
@@ -1431,35 +1438,22 @@ static int ghost2_step_once(int32_t n_owned, int32_t n_ghost, const int32_t* rp1
                            w->pair_set.as<unsigned long long>(), slots - 1, &c.S->conflicts, c.st);
     c.launches += 2;
   }
-  launch_boundary_uncolor(n_owned, loser, Cint, c.st);
   // phase 3: ghosts carry their fixed colors; the losers are recolored on
   // either engine (the incremental engine's lists keep the owned members,
   // the ghosts' colors enter the losers' bitsets once) after a fresh bin
   // setup: the per-bin totals, maxima, heavy-vertex counters and worklist
   // counts still hold phase 1's
-  launch_ghost_fill(n_owned, n_ghost, ghost_colors, Cint, w->T.as<int32_t>(), &c.S->maxc, c.st);
+  launch_recolor_begin(n_owned, n_ghost, loser, ghost_colors, Cint, w->T.as<int32_t>(), &c.S->maxc,
+                       reinterpret_cast<uint32_t*>(c.S->half), kPhaseWords, c.st);
   c.launches += 2;
-  static_assert(offsetof(Scalars, long_cnt) == offsetof(Scalars, max_work) + 3 * sizeof(int32_t),
-                "max_work, deferred_cnt, deferred_grab and long_cnt are cleared together");
-  launch_zero_words(c.S->count_all, 16, c.st);
-  launch_zero_words(c.S->cnt, sizeof(c.S->cnt) / 4, c.st);
-  launch_zero_words(&c.S->max_split_work, 1, c.st);
-  launch_zero_words(&c.S->max_work, 4, c.st);
-  launch_zero_words(&c.S->total_work, 2, c.st);
-  c.launches += 5;
   GraphView g3{n_owned, n_owned, rp1, ci1, rp2, ci2};
   g3.ids = m;
   rc = run_engine<MODE>(c, g3, k, Cint, Cint, m, r1);
   if (rc != COLOR_OK && rc != COLOR_ENOCONVERGE) return rc;
-  launch_flags_out(n_ghost, gflag, remote_loser, &c.S->remote, c.st);
-  launch_copy_i32(n_owned, Cint, owned_colors, c.st);
-  launch_max_i32(n_owned, Cint, &c.S->aux_max, c.st);
-  c.launches += 3;
+  launch_ghost_out(n_owned, n_ghost, Cint, gflag, owned_colors, remote_loser, &c.S->aux_max, &c.S->remote, c.st);
+  c.launches += 1;
   if (hipGetLastError() != hipSuccess) return COLOR_EHIP;
-  if (hipMemcpyAsync(&c.H->aux_max, &c.S->aux_max, sizeof(int32_t), hipMemcpyDeviceToHost, c.st) != hipSuccess)
-    return COLOR_EHIP;
-  if (hipStreamSynchronize(c.st) != hipSuccess) return COLOR_EHIP;
-  return finish_call(c, stats, c.H->aux_max, rc);
+  return finish_call(c, stats, kColorsAuxMax, rc);
 }
 
 // A step whose tail kernel's grid barrier gave up (phase 1 on the

@@ -30,32 +30,58 @@ struct DevBuf {
 };
 
 // Device-resident scalars of one call (one allocation, cleared per call).
+// Device-scope atomics on one 64-byte block are served one after another,
+// about 10 ns each, and every workgroup of a launch adds to several of these:
+// what a launch updates from many workgroups has a block of its own, and the
+// statistics have one for each of eight groups of workgroups.  (With the
+// counters of a launch in one block, 2048 workgroups x 2 updates were the
+// 39 us of the bin setup on a 2 M-vertex mesh.)
 struct Scalars {
-  int32_t cnt[2][8];            // per-bin worklist sizes, ping-pong
-  int32_t tile_ctr[2];          // dynamic unit counters of the color / detect kernels
   int32_t maxc;                 // largest committed color
   int32_t rounds_done;          // last round with a non-empty worklist
-  int32_t max_split_work;       // largest work of an uncolored split vertex
+  int32_t tail_err;             // tail and core kernels: error bits (a barrier gave up)
+  int32_t tail_left;            // tail and core kernels: 1 if stopped at the round cap with vertices left
   int32_t err;                  // validation error bits
   int32_t aux_max;
-  int32_t light_ctr;            // light-chunk counter of the incremental detect kernel
-  int32_t count_all[8];
-  int32_t count_unc[8];
-  unsigned long long visits[8]; // [0] sum |W_r|, [1] sum work(W_r), [2] list entries, [3] color bytes,
-                                // [4] detect bytes, [5] pushes, [6] + [7] tail-kernel bytes
   unsigned long long list_total; // incremental engine: entries of all lists
-  int32_t max_work;              // largest work of an uncolored vertex
-  int32_t deferred_cnt;          // heavy D2/PD2 vertices set up by workgroups
-  int32_t deferred_grab;         // their work counter (list fill)
-  int32_t long_cnt;              // two-hop lists to make duplicate-free
-  uint32_t bar[kBarWords];       // tail kernel: grid-barrier words
-  int32_t tail_err;              // tail kernel: error bits (a barrier gave up)
-  int32_t tail_left;             // tail kernel: 1 if it stopped at the round cap with vertices left
-  unsigned long long total_work;
+  unsigned long long uncolored;  // ghost step: owned vertices without an initial color
+  alignas(64) int32_t tile_ctr[2];  // dynamic unit counters of the color / detect kernels
   unsigned long long conflicts; // ghost phase-2 conflicts
   unsigned long long remote;    // ghost remote losers
   unsigned long long hits;      // D2/PD2 ghost step: conflicting two-hop walk entries
+  // the state of one setup and its rounds, cleared together (kPhaseWords)
+  // between the phases of a ghost step: half .. total_work
+  struct alignas(128) Half {
+    int32_t cnt[16];               // per-bin worklist sizes, ping-pong: one is read with plain loads
+                                   // while the other is added to, so each in a cache line of its own
+    alignas(64) int32_t bins[16];  // setup: vertices per bin (half 0: all, half 1: uncolored)
+  } half[2];
+  int32_t max_split_work;       // largest work of an uncolored split vertex
+  int32_t max_work;             // largest work of an uncolored vertex
+  int32_t deferred_cnt;         // heavy D2/PD2 vertices set up by workgroups
+  int32_t deferred_grab;        // their work counter (list fill)
+  int32_t long_cnt;             // two-hop lists to make duplicate-free
+  unsigned long long total_work;
+  alignas(64) int32_t light_ctr;  // light-chunk counter of the incremental detect kernel
+  // tail kernel: a grid-barrier word; statistics (see IncBufs::acc)
+  struct alignas(128) Line {
+    uint32_t bar[16];
+    unsigned long long visits[8];
+  } lines[kBarWords / 32];
+  // a statistic, summed over its slots
+  unsigned long long visits(int i) const {
+    unsigned long long x = 0;
+    for (int s = 0; s < kAccSlots; ++s) x += lines[s].visits[i];
+    return x;
+  }
 };
+static_assert(sizeof(Scalars::Line) == 128 && kAccStride * sizeof(unsigned long long) == sizeof(Scalars::Line) &&
+                  kAccSlots <= kBarWords / 32,
+              "barrier words are 32 words apart, statistics slots kAccStride");
+static_assert(sizeof(Scalars) == 2048, "the fixed workspaces hold 2048 bytes of scalars");
+
+constexpr int kPhaseWords = static_cast<int>(
+    (offsetof(Scalars, total_work) + sizeof(Scalars::total_work) - offsetof(Scalars, half)) / sizeof(int32_t));
 
 // Per-device workspace of the single-graph entry points.
 struct Workspace {

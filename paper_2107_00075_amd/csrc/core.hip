@@ -198,50 +198,91 @@ __global__ __launch_bounds__(kCoreThreads) void core_rank_kernel(KeySource k, Co
   }
 }
 
-// A workgroup per vertex: its active list (both parts) as a row of bits over
-// the numbers, built in LDS; its tentative color; the forbidden colors from
-// that on.  Entries that have committed are left out.
-__global__ __launch_bounds__(kBlock) void core_build_kernel(IncBufs b, CoreSet out, const int32_t* lists, int split,
-                                                            int32_t stride) {
-  __shared__ uint32_t s_row[768];
-  const int tid = threadIdx.x;
-  const int32_t g = blockIdx.x;
-  const int32_t v = out.v[g];
-  for (int w = tid; w < stride; w += kBlock) s_row[w] = 0u;
+// Entries [0, all) of a vertex's active list (both parts) into its row of
+// bits over the numbers, by `stride` threads from `first`, eight entries per
+// thread in flight.  Entries that have committed are left out.
+__device__ __forceinline__ void build_row(const IncBufs& b, const int32_t* lists, int split, int32_t v, int first,
+                                          int stride, uint32_t* row) {
+  constexpr int N = 8;
   const int32_t hlen = b.alen_in[v], llen = split ? b.llen[v] : 0;
   const int32_t* H = lists + b.aoff[v];
   const int32_t* Lo = lists + b.aoff[v + 1] - llen;
   const int32_t all = hlen + llen;
-  __syncthreads();
-  for (int32_t e0 = tid; e0 < all; e0 += 4 * kBlock) {
-    int32_t u[4];
-    bool live[4];
+  for (int32_t e0 = first; e0 - first < all; e0 += N * stride) {
+    int32_t u[N];
+    bool live[N];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int32_t e = e0 + j * kBlock;
+    for (int j = 0; j < N; ++j) {
+      const int32_t e = e0 + j * stride;
       u[j] = e < all ? (e < hlen ? H[e] : Lo[e - hlen]) : -1;
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) live[j] = u[j] >= 0 && !((b.done[u[j] >> 5] >> (u[j] & 31)) & 1u);
+    for (int j = 0; j < N; ++j) live[j] = u[j] >= 0 && !((b.done[u[j] >> 5] >> (u[j] & 31)) & 1u);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) u[j] = live[j] ? b.T[u[j]] : 0;
+    for (int j = 0; j < N; ++j) u[j] = live[j] ? b.T[u[j]] : 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (live[j]) atomicOr(&s_row[u[j] >> 5], 1u << (u[j] & 31));
+    for (int j = 0; j < N; ++j)
+      if (live[j]) atomicOr(&row[u[j] >> 5], 1u << (u[j] & 31));
   }
-  if (tid == 0) {
-    const int32_t t = core_free_from(b, v, 1);
-    out.t[g] = t;
-    out.fw[g] = core_window(b, v, t);
-    if (all) {
-      atomicAdd(&b.acc[2], static_cast<unsigned long long>(all));
-      // list entry, committed bits, number; the row
-      atomicAdd(&b.acc[7], 12ull * static_cast<unsigned long long>(all) + 4ull * static_cast<unsigned long long>(stride));
+}
+
+// A wavefront per vertex (its workgroup together for a list longer than
+// kWaveList): the row, built in LDS; the tentative color; the forbidden colors
+// from that on.  Bound by the chain list, committed bit, number.  (A workgroup
+// per vertex, with two statistics atomics on one cache block each, took 263 us
+// for 24576 vertices of RMAT scale 17.)
+constexpr int32_t kWaveList = 2048;
+
+__global__ __launch_bounds__(kBlock) void core_build_kernel(IncBufs b, CoreSet out, const int32_t* lists, int split,
+                                                            int32_t stride, int32_t n) {
+  __shared__ uint32_t s_rows[kWavesPerBlock][768];
+  __shared__ int32_t s_long[kWavesPerBlock];  // the vertex if its list is long, else -1
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+  const int32_t g = blockIdx.x * kWavesPerBlock + wave;
+  uint32_t* s_row = s_rows[wave];
+  for (int w = lane; w < stride; w += kWave) s_row[w] = 0u;
+  if (lane == 0) s_long[wave] = -1;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  if (g < n) {
+    const int32_t v = out.v[g];
+    const int64_t all = static_cast<int64_t>(b.alen_in[v]) + (split ? b.llen[v] : 0);
+    if (lane == 0) {
+      const int32_t t = core_free_from(b, v, 1);
+      out.t[g] = t;
+      out.fw[g] = core_window(b, v, t);
+      if (all > kWaveList) s_long[wave] = v;
     }
+    if (all <= kWaveList) build_row(b, lists, split, v, lane, kWave, s_row);
   }
   __syncthreads();
-  uint32_t* r = out.rows + static_cast<size_t>(g) * static_cast<size_t>(stride);
-  for (int w = tid; w < stride; w += kBlock) r[w] = s_row[w];
+#pragma unroll 1
+  for (int i = 0; i < kWavesPerBlock; ++i)
+    if (s_long[i] >= 0) build_row(b, lists, split, s_long[i], tid, kBlock, s_rows[i]);
+  __syncthreads();
+  if (g < n) {
+    uint32_t* r = out.rows + static_cast<size_t>(g) * static_cast<size_t>(stride);
+    for (int w = lane; w < stride; w += kWave) r[w] = s_row[w];
+  }
+  const int32_t base = blockIdx.x * kWavesPerBlock;
+  if (base % kBlock == 0) {  // the statistics of kBlock vertices at once
+    unsigned long long sum = 0;
+    if (base + tid < n) {
+      const int32_t x = out.v[base + tid];
+      sum = static_cast<unsigned long long>(b.alen_in[x]) + static_cast<unsigned long long>(split ? b.llen[x] : 0);
+    }
+    // list entry, committed bits, number; the row
+    unsigned long long bytes = sum ? 12ull * sum + 4ull * static_cast<unsigned long long>(stride) : 0ull;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+      sum += __shfl_xor(sum, off, kWave);
+      bytes += __shfl_xor(bytes, off, kWave);
+    }
+    if (lane_id() == 0 && sum) {
+      atomicAdd(&acc_slot(b.acc)[2], sum);
+      atomicAdd(&acc_slot(b.acc)[7], bytes);
+    }
+  }
 }
 
 namespace {
@@ -352,8 +393,8 @@ __device__ __forceinline__ void core_account(const IncBufs& b, int32_t v, int32_
     maxc = max(maxc, __shfl_xor(maxc, o, kWave));
   }
   if (lane_id() == 0) {
-    if (rounds) atomicAdd(&b.acc[0], rounds);
-    if (work) atomicAdd(&b.acc[1], work);
+    if (rounds) atomicAdd(&acc_slot(b.acc)[0], rounds);
+    if (work) atomicAdd(&acc_slot(b.acc)[1], work);
     if (maxc > 0) atomicMax(b.maxc, maxc);
   }
 }
@@ -757,8 +798,8 @@ __device__ __forceinline__ CoreEnd core_stage(const IncBufs& b, const CoreSet& i
       core_account(b, have ? sh.v[tid] : -1, have ? sh.t[tid] : 0, have ? sh.won[tid] : 0, round0, r - 1);
     }
     if (tid == 0) {
-      atomicAdd(&b.acc[6], static_cast<unsigned long long>(bytes_a));
-      atomicAdd(&b.acc[7], static_cast<unsigned long long>(bytes_b));
+      atomicAdd(&acc_slot(b.acc)[6], static_cast<unsigned long long>(bytes_a));
+      atomicAdd(&acc_slot(b.acc)[7], static_cast<unsigned long long>(bytes_b));
     }
   }
   return end;
@@ -921,7 +962,7 @@ __device__ __forceinline__ CoreEnd core_small(const IncBufs& b, const CoreSet& i
     if (!fast) __syncthreads();  // every committed color has been read
   }
   core_account(b, v, t, won, round0, r - 1);
-  if (tid == 0) atomicAdd(&b.acc[7], static_cast<unsigned long long>(n) * (4ull * row_words(kSmallMax) + 20ull));
+  if (tid == 0) atomicAdd(&acc_slot(b.acc)[7], static_cast<unsigned long long>(n) * (4ull * row_words(kSmallMax) + 20ull));
   return end;
 }
 
@@ -1133,8 +1174,8 @@ bool launch_core(const KeySource& k, const IncBufs& b, const BinLayout& L, const
   else
     hipLaunchKernelGGL(core_rank_kernel<false>, rank_grid, dim3(kCoreThreads), 0, st, k, q, n, x.set[0].v, b.T, clear,
                        words);
-  hipLaunchKernelGGL(core_build_kernel, dim3(n), dim3(kBlock), 0, st, b, x.set[0], b.A_in, split ? 1 : 0,
-                     row_words(n));
+  hipLaunchKernelGGL(core_build_kernel, dim3((n + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kBlock), 0, st, b,
+                     x.set[0], b.A_in, split ? 1 : 0, row_words(n), n);
   IncBufs bb = b;
   if (n > kMidMax) {
     void* args[] = {&bb, &x.set[0], &x.x[0], &x.set[1], &head, &n, &round0, &round_cap, &bar, &err, &left, &deadline,

@@ -10,6 +10,8 @@ namespace gcol {
 constexpr int kWave = 64;
 constexpr int kBlock = 256;          // workgroup of the round kernels: 4 wavefronts
 constexpr int kWavesPerBlock = kBlock / kWave;
+constexpr int kAccSlots = 8;         // copies of the launch statistics, kAccStride 64-bit words apart
+constexpr int kAccStride = 16;
 
 // Problem kinds (the coloring variants of Section 2.1).
 enum Mode : int { kD1 = 1, kD2 = 2, kPD2 = 3 };
@@ -100,7 +102,7 @@ struct KeySource {
 };
 
 __device__ __forceinline__ uint64_t key_of(const KeySource& k, int32_t v) {
-  if (k.rank) return ld_dev(&k.rank[v]);
+  if (k.rank) return k.rank[v];
   const uint32_t g = k.gid ? static_cast<uint32_t>(k.gid[v]) : static_cast<uint32_t>(v);
   const uint32_t p = k.prio ? k.prio[v] : fmix32(g ^ k.hs);
   return (static_cast<uint64_t>(p) << 32) | g;
@@ -171,6 +173,11 @@ __device__ __forceinline__ int32_t atomic_load_i32(const int32_t* p) {
 // a plain store there could leave a dirty partial line in one XCD's L2.
 __device__ __forceinline__ void atomic_reset_u32(uint32_t* p) { (void)atomicExch(p, 0u); }
 __device__ __forceinline__ void atomic_reset_i32(int32_t* p) { (void)atomicExch(p, 0); }
+
+// The statistics slot of this workgroup (kAccSlots of them, kAccStride apart).
+__device__ __forceinline__ unsigned long long* acc_slot(unsigned long long* acc) {
+  return acc + kAccStride * (blockIdx.x % kAccSlots);
+}
 
 // Waits until the caller's accesses to memory have completed.  Mutable state
 // that only device-scope accesses (performed beyond the L2s) touch is handed

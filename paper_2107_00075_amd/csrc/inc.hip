@@ -59,10 +59,11 @@ __device__ __forceinline__ int inc_bin_of(const BinLayout& L, int32_t len) {
   return len <= L.hi[0] ? 0 : len <= L.hi[1] ? 1 : len <= L.hi[2] ? 2 : kBlockBin;
 }
 
+template <int MUT>
 __device__ __forceinline__ void make_inc_map_from(const int32_t* cnt, const BinLayout& L, IncMap& m) {
   int32_t lt = 0, tot = 0;
   for (int i = 0; i < kBins; ++i) {
-    m.cnt[i] = ld_dev(&cnt[i]);
+    m.cnt[i] = ld_mut<MUT>(&cnt[i]);
     tot += m.cnt[i];
   }
   for (int i = 0; i < 3; ++i) {
@@ -75,8 +76,9 @@ __device__ __forceinline__ void make_inc_map_from(const int32_t* cnt, const BinL
   m.total = tot;
 }
 
+template <int MUT>
 __device__ __forceinline__ void make_inc_map(const IncBufs& b, const BinLayout& L, IncMap& m) {
-  make_inc_map_from(b.cnt_in, L, m);
+  make_inc_map_from<MUT>(b.cnt_in, L, m);
 }
 
 __device__ __forceinline__ int32_t xcd_block() {
@@ -223,16 +225,28 @@ struct IncColorShared {
 struct IncPre {
   IncMap M;
   int32_t maxc;
+  unsigned long long acc[5];  // the launch's statistics so far (color 3, detect 2), added once at its end
 };
+
+__device__ __forceinline__ void flush_color_acc(const IncBufs& b, const unsigned long long* a) {
+  if (a[0]) atomicAdd(&acc_slot(b.acc)[1], a[0]);
+  if (a[1]) atomicAdd(&acc_slot(b.acc)[2], a[1]);
+  if (a[2]) atomicAdd(&acc_slot(b.acc)[b.bytes_slot], a[2]);
+}
+__device__ __forceinline__ void flush_detect_acc(const IncBufs& b, const unsigned long long* a) {
+  if (a[0]) atomicAdd(&acc_slot(b.acc)[b.bytes_slot + 1], a[0]);
+  if (a[1]) atomicAdd(&acc_slot(b.acc)[5], a[1]);
+}
 
 template <int MUT>
 __device__ __forceinline__ void inc_color_phase(const IncBufs& b, const BinLayout& L, int round,
-                                                IncColorShared& sh, const IncPre* pre = nullptr) {
+                                                IncColorShared& sh, const IncPre* pre = nullptr,
+                                                unsigned long long* carry = nullptr) {
   IncMap& M = sh.M;
   unsigned long long* s_acc = sh.acc;
   if (threadIdx.x == 0) {
     if (pre) M = pre->M;
-    else make_inc_map(b, L, M);
+    else make_inc_map<MUT>(b, L, M);
     s_acc[0] = s_acc[1] = s_acc[2] = 0ull;
     if (blockIdx.x == 0) {
       for (int i = 0; i < kBins; ++i) atomic_reset_i32(&b.cnt_out[i]);
@@ -242,12 +256,12 @@ __device__ __forceinline__ void inc_color_phase(const IncBufs& b, const BinLayou
         const int gr = round + b.round_base;
         atomicMax(b.rounds_done, gr);
         if (b.trace && gr <= b.trace_cap) st_dev(&b.trace[gr - 1], M.total);
-        atomicAdd(&b.acc[0], static_cast<unsigned long long>(M.total));
+        atomicAdd(&acc_slot(b.acc)[0], static_cast<unsigned long long>(M.total));
       }
     }
   }
   __syncthreads();
-  const int32_t mc = pre ? pre->maxc : ld_dev(b.maxc);
+  const int32_t mc = pre ? pre->maxc : ld_mut<MUT>(b.maxc);
   const int32_t wmax = mc / 32 + 1;  // words that can hold a committed color
   uint64_t work = 0, lists = 0, bytes = 0;
   const int32_t stride = gridDim.x * kBlock;
@@ -303,9 +317,11 @@ __device__ __forceinline__ void inc_color_phase(const IncBufs& b, const BinLayou
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    if (s_acc[0]) atomicAdd(&b.acc[1], s_acc[0]);
-    if (s_acc[1]) atomicAdd(&b.acc[2], s_acc[1]);
-    if (s_acc[2]) atomicAdd(&b.acc[b.bytes_slot], s_acc[2]);
+    if (MUT != 0) {
+      for (int i = 0; i < 3; ++i) carry[i] += s_acc[i];
+    } else {
+      flush_color_acc(b, s_acc);
+    }
   }
 }
 
@@ -756,7 +772,8 @@ struct IncDetectShared {
 
 template <int MUT>
 __device__ __forceinline__ void inc_detect_phase(const KeySource& k, const IncBufs& b, const BinLayout& L,
-                                                 int round, IncDetectShared& sh, const IncPre* pre = nullptr) {
+                                                 int round, IncDetectShared& sh, const IncPre* pre = nullptr,
+                                                 unsigned long long* carry = nullptr) {
   int32_t& s_unit = sh.unit;
   int32_t& s_max = sh.max;
   int32_t* s_ent = sh.ent;
@@ -766,7 +783,7 @@ __device__ __forceinline__ void inc_detect_phase(const KeySource& k, const IncBu
   IncMap& M = sh.M;
   if (threadIdx.x == 0) {
     if (pre) M = pre->M;
-    else make_inc_map(b, L, M);
+    else make_inc_map<MUT>(b, L, M);
     s_max = 0;
     s_acc[0] = s_acc[1] = 0ull;
   }
@@ -924,8 +941,11 @@ __device__ __forceinline__ void inc_detect_phase(const KeySource& k, const IncBu
   __syncthreads();
   if (threadIdx.x == 0) {
     if (s_max > 0) atomicMax(b.maxc, s_max);
-    if (s_acc[0]) atomicAdd(&b.acc[b.bytes_slot + 1], s_acc[0]);
-    if (s_acc[1]) atomicAdd(&b.acc[5], s_acc[1]);
+    if (MUT != 0) {
+      for (int i = 0; i < 2; ++i) carry[i] += s_acc[i];
+    } else {
+      flush_detect_acc(b, s_acc);
+    }
   }
 }
 
@@ -958,7 +978,10 @@ __global__ __launch_bounds__(kBlock) void inc_tail_kernel(KeySource k, IncRoundS
   __shared__ int32_t s_ok;
   __shared__ IncPre s_pre;  // next round's map and largest color, read once per round
   if (!tail_checkin(&bar[kBarCheckin], &bar[kBarState], err, checkin_ticks, &s_ok)) return;
-  for (int r = round0; r <= round_cap; ++r) {
+  if (threadIdx.x == 0)
+    for (int i = 0; i < 5; ++i) s_pre.acc[i] = 0ull;
+  bool done = false;
+  for (int r = round0; r <= round_cap && !done; ++r) {
     IncBufs b = set.base;
     const bool odd = (r & 1) != 0;
     b.wl_in = odd ? set.wl0 : set.wl1;
@@ -969,19 +992,22 @@ __global__ __launch_bounds__(kBlock) void inc_tail_kernel(KeySource k, IncRoundS
     b.uniform = r == 1 ? set.uniform1 : 0;
     b.defer_split = r == 1 ? set.defer1 : 0;
     const bool first = r == round0;
-    inc_color_phase<1>(b, L, r, sh.c, first ? nullptr : &s_pre);
+    inc_color_phase<1>(b, L, r, sh.c, first ? nullptr : &s_pre, s_pre.acc);
     if (!grid_sync(bar, err, deadline, &s_ok)) return;
-    inc_detect_phase<1>(k, b, L, r, sh.d, first ? nullptr : &s_pre);
+    inc_detect_phase<1>(k, b, L, r, sh.d, first ? nullptr : &s_pre, s_pre.acc + 3);
     if (!grid_sync(bar, err, deadline, &s_ok)) return;
     if (threadIdx.x == 0) {
-      make_inc_map_from(b.cnt_out, L, s_pre.M);  // the next round's worklist counts
+      make_inc_map_from<1>(b.cnt_out, L, s_pre.M);  // the next round's worklist counts
       s_pre.maxc = ld_dev(b.maxc);
     }
     __syncthreads();
-    const bool done = s_pre.M.total <= stop_at;
-    if (done) return;
+    done = s_pre.M.total <= stop_at;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) st_dev(left, 1);
+  if (threadIdx.x == 0) {
+    flush_color_acc(set.base, s_pre.acc);
+    flush_detect_acc(set.base, s_pre.acc + 3);
+    if (blockIdx.x == 0 && !done) st_dev(left, 1);
+  }
 }
 
 int tail_blocks_resident() {
@@ -1041,25 +1067,26 @@ template <int MODE>
 __global__ __launch_bounds__(kBlock) void inc_sizes_kernel(GraphView g, const int32_t* work, int32_t* len,
                                                            int32_t* words, int32_t* alen0,
                                                            unsigned long long* total) {
-  const int32_t v = blockIdx.x * kBlock + threadIdx.x;
-  int64_t l = 0;
-  if (v < g.n) {
-    const int64_t d1 = g.rp[v + 1] - g.rp[v];
-    l = MODE == kD1 ? d1 : static_cast<int64_t>(ld_dev(&work[v])) - (MODE == kPD2 ? 2 : 1) * d1;
-    if (l < 0) l = 0;
-  }
   __shared__ unsigned long long s_t;
   if (threadIdx.x == 0) s_t = 0ull;
   __syncthreads();
-  uint64_t t = wsum(static_cast<uint64_t>(l));
+  uint64_t t = 0;
+  for (int64_t i = blockIdx.x * static_cast<int64_t>(kBlock) + threadIdx.x; i < g.n;
+       i += static_cast<int64_t>(gridDim.x) * kBlock) {
+    const int32_t v = static_cast<int32_t>(i);
+    const int64_t d1 = g.rp[v + 1] - g.rp[v];
+    int64_t l = MODE == kD1 ? d1 : static_cast<int64_t>(ld_mut<0>(&work[v])) - (MODE == kPD2 ? 2 : 1) * d1;
+    if (l < 0) l = 0;
+    t += static_cast<uint64_t>(l);
+    const int32_t lc = static_cast<int32_t>(l > INT_MAX ? INT_MAX : l);
+    st_dev(&len[v], lc);
+    st_dev(&alen0[v], lc);
+    st_dev(&words[v], static_cast<int32_t>(min<int64_t>(l, max(g.n, g.ids)) / 32));
+  }
+  t = wsum(t);
   if (lane_id() == 0 && t) atomicAdd(&s_t, static_cast<unsigned long long>(t));
   __syncthreads();
   if (threadIdx.x == 0 && s_t) atomicAdd(total, s_t);
-  if (v >= g.n) return;
-  const int32_t lc = static_cast<int32_t>(l > INT_MAX ? INT_MAX : l);
-  st_dev(&len[v], lc);
-  st_dev(&alen0[v], lc);
-  st_dev(&words[v], static_cast<int32_t>(min<int64_t>(l, max(g.n, g.ids)) / 32));
 }
 
 // Walks the second-hop rows of the first-hop entries [q0, q1) of v with a
@@ -1331,7 +1358,7 @@ template <int MODE>
 void launch_inc_sizes(const GraphView& g, const int32_t* work, int32_t* len, int32_t* words, int32_t* alen0,
                       unsigned long long* total, hipStream_t st) {
   if (g.n > 0)
-    hipLaunchKernelGGL(inc_sizes_kernel<MODE>, dim3(blocks_for(g.n)), dim3(kBlock), 0, st, g, work, len, words,
+    hipLaunchKernelGGL(inc_sizes_kernel<MODE>, dim3(std::min(blocks_for(g.n), 1024)), dim3(kBlock), 0, st, g, work, len, words,
                        alen0, total);
 }
 // Duplicates of the materialized two-hop lists (a column pair sharing

@@ -35,7 +35,7 @@ struct IncBufs {
   uint32_t* F;                 // forbidden-color bitsets, word 0 (colors 1..32) of every vertex
   uint32_t* Fx;                // their further words (bit c-1 = color c throughout)
   int32_t* maxc;               // largest committed color
-  unsigned long long* acc;     // [0] sum |W|, [1] sum work, [2] list entries, [3] color bytes,
+  unsigned long long* acc;     // slots (acc_slot) of [0] sum |W|, [1] sum work, [2] list entries, [3] color bytes,
                                // [4] detect bytes, [5] pushes, [6] and [7] color and detect bytes
                                // of the tail kernel
   int32_t bytes_slot = 3;      // where this launch adds its color bytes (detect: the next slot)

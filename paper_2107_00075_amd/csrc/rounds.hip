@@ -57,7 +57,7 @@ struct RoundMap {
 
 __device__ __forceinline__ void make_round_map(const RoundBufs& b, const BinLayout& L, RoundMap& m) {
   int32_t lt = 0;
-  for (int i = 0; i < kBins; ++i) m.cnt[i] = atomic_load_i32(&b.cnt_in[i]);
+  for (int i = 0; i < kBins; ++i) m.cnt[i] = ld_mut<0>(&b.cnt_in[i]);
   for (int i = 0; i < 3; ++i) {
     m.csize[i] = round_chunk_size(m.cnt[i], L.lanes[i], static_cast<int32_t>(gridDim.x));
     m.chunks[i] = (m.cnt[i] + m.csize[i] - 1) / m.csize[i];
@@ -130,12 +130,11 @@ __device__ __forceinline__ void color_split_chunk(const GraphView& g, const Roun
     const uint32_t x = ovf[w];
     if (x) atomicOr(&gm[2 + w], x);
   }
-  __threadfence();
+  wait_own_accesses();  // (all device-scope: a cache writeback and invalidation is not needed)
   __syncthreads();
   if (tid == 0) s_misc[1] = (atomicAdd(&b.split_ctr[si], 1u) == static_cast<uint32_t>(nch - 1));
   __syncthreads();
   if (s_misc[1]) {  // last chunk to arrive: pick the color
-    __threadfence();
     const int32_t mc = atomic_load_i32(b.maxc);
     const int32_t nwords = min(b.capw, mc / 32 + 1);
     if (tid == 0) s_misc[0] = INT_MAX;
@@ -181,7 +180,7 @@ __global__ __launch_bounds__(kBlock) void color_round_kernel(GraphView g, KeySou
       if (total > 0) {
         atomicMax(b.rounds_done, round);
         if (b.trace && round <= b.trace_cap) st_dev(&b.trace[round - 1], static_cast<int32_t>(total));
-        atomicAdd(&b.visits[0], static_cast<unsigned long long>(total));
+        atomicAdd(&acc_slot(b.visits)[0], static_cast<unsigned long long>(total));
       }
     }
   }
@@ -228,7 +227,7 @@ __global__ __launch_bounds__(kBlock) void color_round_kernel(GraphView g, KeySou
   work_acc = wave_sum_u64(work_acc);
   if (lane_id() == 0 && work_acc) atomicAdd(&s_work, static_cast<unsigned long long>(work_acc));
   __syncthreads();
-  if (threadIdx.x == 0 && s_work) atomicAdd(&b.visits[1], s_work);
+  if (threadIdx.x == 0 && s_work) atomicAdd(&acc_slot(b.visits)[1], s_work);
 }
 
 template <int MODE>
@@ -255,13 +254,11 @@ __device__ __forceinline__ void detect_split_chunk(const GraphView& g, const Key
                     });
   }
   lose = __syncthreads_or(lose);
-  if (tid == 0 && lose) atomicOr(&b.split_flag[si], 1u);
-  __threadfence();
-  __syncthreads();
   if (tid == 0) {
+    if (lose) atomicOr(&b.split_flag[si], 1u);
+    wait_own_accesses();
     const bool last = atomicAdd(&b.split_ctr[si], 1u) == static_cast<uint32_t>(nch - 1);
     if (last) {
-      __threadfence();
       const uint32_t f = atomic_load_u32(&b.split_flag[si]);
       if (!f) {
         st_dev(&b.C[v], tv);

@@ -55,7 +55,7 @@ struct RoundBufs {
   uint32_t* split_ctr;        // per split index: arrival counter of its chunks
   uint32_t* split_flag;       // per split index: "lost" flag of the detect phase
   int32_t* maxc;              // largest committed color
-  unsigned long long* visits; // [0] sum |W_r|, [1] sum work(W_r)
+  unsigned long long* visits; // slots (acc_slot) of [0] sum |W_r|, [1] sum work(W_r)
   int32_t* trace;             // |W_r| per round (nullable)
   int32_t trace_cap;
   int32_t* rounds_done;       // last round with a non-empty worklist

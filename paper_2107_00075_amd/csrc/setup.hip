@@ -271,8 +271,8 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(int32_t n, const int32_
   const int32_t hi = min(n, lo + per_block);
   int32_t my[kBins] = {0, 0, 0, 0, 0};
   for (int32_t v = lo + tid; v < hi; v += kBlock) {
-    const bool active = ld_dev(&C[v]) == 0;
-    const int bin = active ? static_cast<int>(ld_dev(&binv[v])) : -1;
+    const bool active = ld_mut<0>(&C[v]) == 0;
+    const int bin = active ? static_cast<int>(ld_mut<0>(&binv[v])) : -1;
 #pragma unroll
     for (int i = 0; i < kBins; ++i) my[i] += bin == i ? 1 : 0;
   }
@@ -292,8 +292,8 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(int32_t n, const int32_
   __syncthreads();
   for (int32_t base = lo; base < hi; base += kBlock) {
     const int32_t v = base + tid;
-    const bool active = v < hi && ld_dev(&C[v]) == 0;
-    const int bin = active ? static_cast<int>(ld_dev(&binv[v])) : -1;
+    const bool active = v < hi && ld_mut<0>(&C[v]) == 0;
+    const int bin = active ? static_cast<int>(ld_mut<0>(&binv[v])) : -1;
     int32_t rank = 0;
 #pragma unroll
     for (int i = 0; i < kBins; ++i) {
@@ -392,30 +392,58 @@ __global__ __launch_bounds__(kBlock) void priority_kernel(int32_t n, const int32
 // Ghost phase 2 (Algorithm 3 with Algorithm 4 on the ghosts' fixed colors):
 // every owned-ghost edge with equal colors is a conflict; the owned endpoint
 // loses when the ghost's key is greater, otherwise the ghost is flagged.  All
-// pairs are judged on the phase-1 colors (a thread per owned-row entry, so a
-// hub's row spreads over many threads); losers are uncolored afterwards by
-// boundary_uncolor_kernel.  loser must be zeroed first.
+// pairs are judged on the phase-1 colors; losers are uncolored afterwards by
+// recolor_begin_kernel.  loser and gflag must be zeroed first.  A workgroup
+// takes kBoundaryEntries consecutive owned-row entries, so that a hub's row
+// spreads over many, with the offsets of their rows in LDS.  (A binary search
+// of all rows in memory per entry took 103 us on a sixteenth of RMAT
+// scale 22.)
+constexpr int kBoundaryPer = 8;
+constexpr int kBoundaryEntries = kBoundaryPer * kBlock;
+constexpr int kBoundaryRows = 2048;
 
 __global__ __launch_bounds__(kBlock) void boundary_kernel(int32_t n_owned, const int32_t* rp,
                                                           const int32_t* ci, const int32_t* C,
                                                           const int32_t* ghost_colors, KeySource k,
                                                           int32_t* loser, int32_t* gflag,
                                                           unsigned long long* conflicts) {
-  const int32_t e = blockIdx.x * kBlock + threadIdx.x;
-  uint32_t found = 0;
-  if (e < rp[n_owned]) {
-    const int32_t u = ci[e];
-    if (u >= n_owned) {
-      const int32_t v = row_of(rp, n_owned, e);
-      if (ghost_colors[u - n_owned] == ld_dev(&C[v])) {
-        found = 1;
-        if (key_of(k, u) > key_of(k, v)) st_dev(&loser[v], 1);
-        else st_dev(&gflag[u - n_owned], 1);
-      }
-    }
+  __shared__ int32_t s_rp[kBoundaryRows];
+  __shared__ int32_t s_found;
+  constexpr int N = kBoundaryPer;
+  const int tid = threadIdx.x;
+  const int32_t nnz = rp[n_owned];
+  const int32_t e0 = blockIdx.x * kBoundaryEntries;
+  if (e0 >= nnz) return;
+  const int32_t e1 = nnz - e0 < kBoundaryEntries ? nnz : e0 + kBoundaryEntries;
+  int32_t u[N], gc[N], v[N], cv[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) u[j] = e0 + j * kBlock + tid < e1 ? ci[e0 + j * kBlock + tid] : 0;
+  const int32_t lo = row_of(rp, n_owned, e0);
+  const int32_t rows = row_of(rp, n_owned, e1 - 1) - lo + 1;
+  const bool lds = rows <= kBoundaryRows;  // beyond (mostly empty rows): searched in memory
+  if (tid == 0) s_found = 0;
+  for (int i = tid; lds && i < rows; i += kBlock) s_rp[i] = rp[lo + i];
+#pragma unroll
+  for (int j = 0; j < N; ++j) gc[j] = u[j] >= n_owned ? ghost_colors[u[j] - n_owned] : 0;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+    v[j] = lds ? row_of(s_rp, rows, e0 + j * kBlock + tid) : row_of(rp + lo, rows, e0 + j * kBlock + tid);
+#pragma unroll
+  for (int j = 0; j < N; ++j) cv[j] = u[j] >= n_owned ? ld_dev(&C[lo + v[j]]) : 0;
+  int32_t found = 0;
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    if (u[j] < n_owned || gc[j] != cv[j]) continue;
+    ++found;
+    if (key_of(k, u[j]) > key_of(k, lo + v[j])) st_dev(&loser[lo + v[j]], 1);
+    else st_dev(&gflag[u[j] - n_owned], 1);
   }
-  const uint64_t tot = __popcll(__ballot(found != 0));
-  if (lane_id() == 0 && tot) atomicAdd(conflicts, static_cast<unsigned long long>(tot));
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) found += __shfl_xor(found, off, kWave);
+  if (lane_id() == 0 && found) atomicAdd(&s_found, found);
+  __syncthreads();
+  if (tid == 0 && s_found) atomicAdd(conflicts, static_cast<unsigned long long>(s_found));
 }
 
 // Distance-2 / partial distance-2 ghost phase 2 (Algorithm 5 over the owned
@@ -482,58 +510,102 @@ __global__ __launch_bounds__(kBlock) void fill_u64_kernel(unsigned long long* p,
   if (i < n) p[i] = x;
 }
 
-__global__ __launch_bounds__(kBlock) void boundary_uncolor_kernel(int32_t n_owned, const int32_t* loser,
-                                                                  int32_t* C) {
-  const int32_t v = blockIdx.x * kBlock + threadIdx.x;
-  if (v < n_owned && ld_dev(&loser[v])) st_dev(&C[v], 0);
-}
-
-// Ghost colors become fixed committed colors for phase 3.
-__global__ __launch_bounds__(kBlock) void ghost_fill_kernel(int32_t n_owned, int32_t n_ghost,
-                                                            const int32_t* ghost_colors, int32_t* C,
-                                                            int32_t* T, int32_t* maxc) {
-  const int32_t j = blockIdx.x * kBlock + threadIdx.x;
-  int32_t c = 0;
-  if (j < n_ghost) {
-    c = ghost_colors[j];
-    st_dev(&C[n_owned + j], c);
-    st_dev(&T[n_owned + j], c);
+// Block totals of a grid-stride ghost kernel: one atomic per workgroup (one
+// per wavefront on the same word took 159 us for 3.9 million ghosts).
+__device__ __forceinline__ void flush_max_count(int32_t mx, uint32_t count, int32_t* max_out,
+                                                unsigned long long* count_out) {
+  __shared__ int32_t s_max;
+  __shared__ uint32_t s_count;
+  if (threadIdx.x == 0) {
+    s_max = 0;
+    s_count = 0u;
   }
+  __syncthreads();
 #pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) c = max(c, __shfl_xor(c, off, kWave));
-  if (lane_id() == 0 && c > 0) atomicMax(maxc, c);
+  for (int off = 1; off < kWave; off <<= 1) {
+    mx = max(mx, __shfl_xor(mx, off, kWave));
+    count += __shfl_xor(count, off, kWave);
+  }
+  if (lane_id() == 0) {
+    if (mx > 0) atomicMax(&s_max, mx);
+    if (count) atomicAdd(&s_count, count);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (s_max > 0) atomicMax(max_out, s_max);
+    if (s_count) atomicAdd(count_out, static_cast<unsigned long long>(s_count));
+  }
 }
 
-// Largest value of an int32 array (wave-reduced, one atomic per wavefront).
-__global__ __launch_bounds__(kBlock) void max_i32_kernel(int32_t n, const int32_t* a, int32_t* out) {
-  int32_t x = 0;
-  for (int64_t i = blockIdx.x * static_cast<int64_t>(kBlock) + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * kBlock)
-    x = max(x, ld_dev(&a[i]));
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) x = max(x, __shfl_xor(x, off, kWave));
-  if (lane_id() == 0 && x > 0) atomicMax(out, x);
+__global__ __launch_bounds__(kBlock) void ghost_begin_kernel(int32_t n_owned, int32_t n_ghost, const int32_t* init,
+                                                             int32_t* C, int32_t* T, int32_t* loser, int32_t* gflag,
+                                                             int32_t* maxc, unsigned long long* uncolored) {
+  int32_t mx = 0;
+  uint32_t zeros = 0;
+  const int64_t items = max(n_owned, n_ghost), stride = static_cast<int64_t>(gridDim.x) * kBlock;
+  for (int64_t i = blockIdx.x * static_cast<int64_t>(kBlock) + threadIdx.x; i < items; i += stride) {
+    if (i < n_ghost) st_dev(&gflag[i], 0);
+    if (i >= n_owned) continue;
+    st_dev(&loser[i], 0);
+    if (init) {
+      const int32_t c = init[i];
+      st_dev(&C[i], c);
+      st_dev(&T[i], c);
+      mx = max(mx, c);
+      zeros += c == 0;
+    }
+  }
+  flush_max_count(mx, zeros, maxc, uncolored);
 }
 
-__global__ __launch_bounds__(kBlock) void flags_out_kernel(int32_t n, const int32_t* gflag, uint8_t* out,
-                                                           unsigned long long* count) {
-  const int32_t j = blockIdx.x * kBlock + threadIdx.x;
-  const bool f = j < n && ld_dev(&gflag[j]) != 0;
-  if (j < n && out) out[j] = f ? 1 : 0;
-  const uint64_t bal = __ballot(f);
-  if (lane_id() == 0 && bal) atomicAdd(count, static_cast<unsigned long long>(__popcll(bal)));
+__global__ __launch_bounds__(kBlock) void recolor_begin_kernel(int32_t n_owned, int32_t n_ghost, const int32_t* loser,
+                                                               const int32_t* ghost_colors, int32_t* C, int32_t* T,
+                                                               int32_t* maxc, uint32_t* zero, int zero_words) {
+  int32_t mx = 0;
+  const int64_t items = max(max(n_owned, n_ghost), zero_words), stride = static_cast<int64_t>(gridDim.x) * kBlock;
+  for (int64_t i = blockIdx.x * static_cast<int64_t>(kBlock) + threadIdx.x; i < items; i += stride) {
+    if (i < zero_words) st_dev(&zero[i], 0u);
+    if (i < n_owned && ld_dev(&loser[i])) st_dev(&C[i], 0);
+    if (i < n_ghost) {
+      const int32_t c = ghost_colors[i];
+      st_dev(&C[n_owned + i], c);
+      st_dev(&T[n_owned + i], c);
+      mx = max(mx, c);
+    }
+  }
+  flush_max_count(mx, 0u, maxc, nullptr);
 }
 
-__global__ __launch_bounds__(kBlock) void copy_i32_kernel(int32_t n, const int32_t* src, int32_t* dst) {
-  const int32_t i = blockIdx.x * kBlock + threadIdx.x;
-  if (i < n) st_dev(&dst[i], ld_dev(&src[i]));
+__global__ __launch_bounds__(kBlock) void ghost_out_kernel(int32_t n_owned, int32_t n_ghost, const int32_t* C,
+                                                           const int32_t* gflag, int32_t* owned_colors,
+                                                           uint8_t* remote_loser, int32_t* max_color,
+                                                           unsigned long long* remote) {
+  int32_t mx = 0;
+  uint32_t flags = 0;
+  const int64_t items = max(n_owned, n_ghost), stride = static_cast<int64_t>(gridDim.x) * kBlock;
+  for (int64_t i = blockIdx.x * static_cast<int64_t>(kBlock) + threadIdx.x; i < items; i += stride) {
+    if (i < n_owned) {
+      const int32_t c = ld_dev(&C[i]);
+      st_dev(&owned_colors[i], c);
+      mx = max(mx, c);
+    }
+    if (i < n_ghost) {
+      const bool f = ld_dev(&gflag[i]) != 0;
+      if (remote_loser) remote_loser[i] = f ? 1 : 0;
+      flags += f;
+    }
+  }
+  flush_max_count(mx, flags, max_color, remote);
 }
 
 static inline int blocks_for(int64_t n) { return static_cast<int>((n + kBlock - 1) / kBlock); }
 
-// Grid cap of the grid-stride setup kernels (their per-workgroup totals
-// become device atomics).
-constexpr int kSetupGrid = 2048;
+// Grid caps of the setup kernels.  Every workgroup of the bin setup adds its
+// totals to the same few words, about 10 ns each: 512 workgroups take 30 us on
+// a 2 M-vertex mesh, 2048 39 us; the worklist scatter (one word) is no faster
+// with fewer.
+constexpr int kSetupGrid = 512;
+constexpr int kScatterGrid = 2048;
 
 template <int MODE>
 void launch_bin(const GraphView& g, const BinSetup& s, hipStream_t st) {
@@ -549,7 +621,7 @@ template void launch_bin<kPD2>(const GraphView&, const BinSetup&, hipStream_t);
 void launch_scatter(int32_t n, const int32_t* C, const int8_t* bin, const BinLayout& L, int32_t* wl,
                     int32_t* cnt, int32_t* split_vertex, hipStream_t st) {
   if (n <= 0) return;
-  const int blocks = std::min(blocks_for(n), kSetupGrid);
+  const int blocks = std::min(blocks_for(n), kScatterGrid);
   const int64_t per = (static_cast<int64_t>(n) + blocks - 1) / blocks;
   const int32_t per_block = static_cast<int32_t>((per + kBlock - 1) / kBlock * kBlock);
   hipLaunchKernelGGL(scatter_kernel, dim3(blocks), dim3(kBlock), 0, st, n, C, bin, L, wl, cnt, split_vertex,
@@ -574,14 +646,29 @@ void launch_boundary(int32_t n_owned, int32_t owned_nnz, const int32_t* rp, cons
                      const int32_t* ghost_colors, const KeySource& k, int32_t* loser, int32_t* gflag,
                      unsigned long long* conflicts, hipStream_t st) {
   if (n_owned > 0 && owned_nnz > 0)
-    hipLaunchKernelGGL(boundary_kernel, dim3(blocks_for(owned_nnz)), dim3(kBlock), 0, st, n_owned, rp, ci, C,
+    hipLaunchKernelGGL(boundary_kernel, dim3((owned_nnz - 1) / kBoundaryEntries + 1), dim3(kBlock), 0, st, n_owned, rp, ci, C,
                        ghost_colors, k, loser, gflag, conflicts);
 }
 
-void launch_boundary_uncolor(int32_t n_owned, const int32_t* loser, int32_t* C, hipStream_t st) {
-  if (n_owned > 0)
-    hipLaunchKernelGGL(boundary_uncolor_kernel, dim3(blocks_for(n_owned)), dim3(kBlock), 0, st, n_owned,
-                       loser, C);
+// The grid-stride ghost kernels: a workgroup per 1024 items, up to 1024.
+static inline int ghost_grid(int64_t n) { return static_cast<int>(std::min<int64_t>((n + 1023) / 1024, 1024)); }
+
+void launch_ghost_begin(int32_t n_owned, int32_t n_ghost, const int32_t* init, int32_t* C, int32_t* T, int32_t* loser,
+                        int32_t* gflag, int32_t* maxc, unsigned long long* uncolored, hipStream_t st) {
+  hipLaunchKernelGGL(ghost_begin_kernel, dim3(ghost_grid(std::max(n_owned, n_ghost))), dim3(kBlock), 0, st, n_owned,
+                     n_ghost, init, C, T, loser, gflag, maxc, uncolored);
+}
+
+void launch_recolor_begin(int32_t n_owned, int32_t n_ghost, const int32_t* loser, const int32_t* gc, int32_t* C,
+                          int32_t* T, int32_t* maxc, uint32_t* zero, int zero_words, hipStream_t st) {
+  hipLaunchKernelGGL(recolor_begin_kernel, dim3(ghost_grid(std::max(std::max(n_owned, n_ghost), zero_words))),
+                     dim3(kBlock), 0, st, n_owned, n_ghost, loser, gc, C, T, maxc, zero, zero_words);
+}
+
+void launch_ghost_out(int32_t n_owned, int32_t n_ghost, const int32_t* C, const int32_t* gflag, int32_t* owned_colors,
+                      uint8_t* remote_loser, int32_t* max_color, unsigned long long* remote, hipStream_t st) {
+  hipLaunchKernelGGL(ghost_out_kernel, dim3(ghost_grid(std::max(n_owned, n_ghost))), dim3(kBlock), 0, st, n_owned,
+                     n_ghost, C, gflag, owned_colors, remote_loser, max_color, remote);
 }
 
 // Ghost phase 1 reads the owned-induced subgraph: the owned rows without
@@ -707,27 +794,5 @@ template void launch_boundary2<kD2>(const GraphView&, int32_t, int32_t, const in
 template void launch_boundary2<kPD2>(const GraphView&, int32_t, int32_t, const int32_t*, const int32_t*,
                                      const KeySource&, int32_t*, int32_t*, unsigned long long*, unsigned long long*,
                                      uint64_t, unsigned long long*, hipStream_t);
-
-void launch_ghost_fill(int32_t n_owned, int32_t n_ghost, const int32_t* gc, int32_t* C, int32_t* T,
-                       int32_t* maxc, hipStream_t st) {
-  if (n_ghost > 0)
-    hipLaunchKernelGGL(ghost_fill_kernel, dim3(blocks_for(n_ghost)), dim3(kBlock), 0, st, n_owned, n_ghost,
-                       gc, C, T, maxc);
-}
-
-void launch_max_i32(int32_t n, const int32_t* a, int32_t* out, hipStream_t st) {
-  if (n > 0)
-    hipLaunchKernelGGL(max_i32_kernel, dim3(std::min(blocks_for(n), 1024)), dim3(kBlock), 0, st, n, a, out);
-}
-
-void launch_flags_out(int32_t n, const int32_t* gflag, uint8_t* out, unsigned long long* count,
-                      hipStream_t st) {
-  if (n > 0)
-    hipLaunchKernelGGL(flags_out_kernel, dim3(blocks_for(n)), dim3(kBlock), 0, st, n, gflag, out, count);
-}
-
-void launch_copy_i32(int32_t n, const int32_t* src, int32_t* dst, hipStream_t st) {
-  if (n > 0) hipLaunchKernelGGL(copy_i32_kernel, dim3(blocks_for(n)), dim3(kBlock), 0, st, n, src, dst);
-}
 
 }  // namespace gcol

@@ -36,7 +36,11 @@ void launch_validate(int32_t n_rows, int32_t n_cols, const int32_t* rp, const in
                      const int32_t* rpT, const int32_t* ciT, int32_t n_trows, int square, int32_t* err,
                      hipStream_t st);
 void launch_priority(int32_t n, const int32_t* gid, uint32_t hs, uint32_t* out, hipStream_t st);
-// D1 ghost phase 2 (a thread per owned-row entry; loser zeroed first).
+// Begin of a D1 ghost step: loser and gflag zeroed; with init also the owned
+// colors and tentative colors, their maximum and (+=) the number of zeros.
+void launch_ghost_begin(int32_t n_owned, int32_t n_ghost, const int32_t* init, int32_t* C, int32_t* T, int32_t* loser,
+                        int32_t* gflag, int32_t* maxc, unsigned long long* uncolored, hipStream_t st);
+// D1 ghost phase 2 (loser and gflag zeroed first).
 void launch_boundary(int32_t n_owned, int32_t owned_nnz, const int32_t* rp, const int32_t* ci, const int32_t* C,
                      const int32_t* ghost_colors, const KeySource& k, int32_t* loser, int32_t* gflag,
                      unsigned long long* conflicts, hipStream_t st);
@@ -50,9 +54,10 @@ void launch_boundary2(const GraphView& g, int32_t n_owned, int32_t nnz1, const i
                       const KeySource& k, int32_t* loser, int32_t* gflag, unsigned long long* hits,
                       unsigned long long* set, uint64_t set_mask, unsigned long long* conflicts, hipStream_t st);
 void launch_fill_u64(unsigned long long* p, uint64_t n, unsigned long long x, hipStream_t st);
-void launch_boundary_uncolor(int32_t n_owned, const int32_t* loser, int32_t* C, hipStream_t st);
-void launch_ghost_fill(int32_t n_owned, int32_t n_ghost, const int32_t* gc, int32_t* C, int32_t* T,
-                       int32_t* maxc, hipStream_t st);
+// Begin of the recoloring: owned losers uncolored, ghosts' colors committed
+// (maxc: their maximum), and the words at zero cleared.
+void launch_recolor_begin(int32_t n_owned, int32_t n_ghost, const int32_t* loser, const int32_t* gc, int32_t* C,
+                          int32_t* T, int32_t* maxc, uint32_t* zero, int zero_words, hipStream_t st);
 // Tentative ghost recoloring: a ghost whose color is not known yet.
 constexpr int32_t kGhostUnknown = 0x7fffffff;
 // One ghost layer: the local CSR over owned + ghost ids, a ghost's row being
@@ -69,14 +74,11 @@ void launch_ghost_rows(int32_t n_owned, int32_t n_ghost, int32_t owned_nnz, cons
 int launch_owned_subgraph(int32_t n_owned, int32_t owned_nnz, const int32_t* rp, const int32_t* ci, int32_t* flag,
                           int32_t* pos, int32_t* rp1, int32_t* ci1_or_null, void* scan_tmp, size_t scan_bytes,
                           hipStream_t st);
-// then, with ci1, copies the entries.  Returns nonzero if the scan failed.
-int launch_owned_subgraph(int32_t n_owned, const int32_t* rp, const int32_t* ci, int32_t* cnt, int32_t* rp1,
-                          int32_t* ci1_or_null, void* scan_tmp, size_t scan_bytes, hipStream_t st);
 void launch_ghost_recolor_init(int32_t n_owned, int32_t n3, const int32_t* C, const int32_t* gc, const int32_t* gflag,
                                int32_t* init, hipStream_t st);
-void launch_max_i32(int32_t n, const int32_t* a, int32_t* out, hipStream_t st);
-void launch_flags_out(int32_t n, const int32_t* gflag, uint8_t* out, unsigned long long* count,
-                      hipStream_t st);
-void launch_copy_i32(int32_t n, const int32_t* src, int32_t* dst, hipStream_t st);
+// End of a ghost step: the owned colors and their maximum, the ghosts' flags
+// (remote_loser may be null) and their number.
+void launch_ghost_out(int32_t n_owned, int32_t n_ghost, const int32_t* C, const int32_t* gflag, int32_t* owned_colors,
+                      uint8_t* remote_loser, int32_t* max_color, unsigned long long* remote, hipStream_t st);
 
 }  // namespace gcol
