@@ -18,12 +18,15 @@
 //  * Phase A of a round publishes, per color c in use, the bits of the
 //    vertices whose tentative color is c.  A vertex loses iff its row meets
 //    the bits of its own color below its own number.
-//  * Phase B publishes, per color, the bits of the vertices that committed it
-//    (cumulative over the stage).  A loser keeps its tentative color unless
-//    its row meets the committed bits of it; then it moves to the next color
-//    that neither those bits nor its forbidden bitset as of the launch hold.
+//  * Phase B publishes the bits of the vertices that committed in the round
+//    and their colors, packed.  A workgroup reads of each such vertex's row
+//    only the words of its own vertices (the rows are symmetric) and adds the
+//    color to the forbidden colors of the neighbours it has, a window of 64
+//    colors from about the tentative color on.  A loser then moves to the
+//    first color from its tentative color on that its window does not hold.
 //    That is its first fit in the next round: forbidden colors only grow, so
-//    a tentative color never decreases.
+//    a tentative color never decreases; and a color committed in a round is
+//    less than kCoreSlots above every tentative color, inside the window.
 //  * Every published 64-bit word carries the round number in its upper half
 //    and 32 vertices' bits in its lower half, so a reader polls the data
 //    itself: one store and one load per exchange, with no flag, counter or
@@ -90,8 +93,13 @@ struct CoreSet {
   uint32_t* rows;
 };
 
-// A stage's exchange words: [slot][word] of phases A and B, their summary
-// words [word], and a flag per workgroup set at the hand-over.
+// A stage's exchange words: [slot][word] of phase A and [kCoreColorWords][word]
+// of phase B (the slots of the committed colors, six to a word), their summary
+// words [word] (phase B: the vertices that committed), and a flag per
+// workgroup set at the hand-over.
+constexpr int kCoreColors = 6;                          // 5-bit slots in a word
+constexpr int kCoreColorWords = (32 + kCoreColors - 1) / kCoreColors;
+
 struct CoreExchange {
   uint64_t* A;
   uint64_t* B;
@@ -295,9 +303,9 @@ struct CoreShared {
   int32_t v[32 * U];      // vertex, -1: none
   int32_t t[32 * U];      // tentative (then committed) color
   int32_t won[32 * U];    // round it committed in, 0: not yet
-  int32_t fb[32 * U];     // forbidden colors as of the stage: bit d of fw stands for color fb + d
+  int32_t fb[32 * U];     // forbidden colors: bit d of fw stands for color fb + d, t - 32 <= fb <= t
   uint64_t fw[32 * U];
-  int32_t tmin[U];
+  uint32_t hit[kCoreSlots][U];  // phase B: the vertices with a neighbour that committed the slot's color
   uint32_t slots[U];
   uint32_t near_row[32 * U][U];      // higher-key neighbours inside the workgroup
   uint32_t near_bits[kCoreSlots][U]; // phase A's words of the workgroup itself
@@ -407,17 +415,16 @@ __device__ __forceinline__ int core_word_of(int lane, int q) {
   return (q / B) * (kWave * B) + lane * B + q % B;
 }
 
-// Whether row and mask share a bit in their first W words (whole wavefront).
-__device__ __forceinline__ bool core_meets(const uint32_t* row, const uint32_t* mask, int32_t W, int lane) {
-  uint32_t hit = 0;
-  for (int32_t w = lane; w < W; w += kWave) hit |= ld_dev(&row[w]) & mask[w];
-  return __ballot(hit != 0u) != 0ull;
-}
-
 // One stage of several workgroups over n vertices from round r on, until at
 // most stop_at are left.  U: 32-bit row words (32 vertices each) a workgroup
 // of NT threads owns; K: row words per lane; the stage's first ceil(n / 32 U)
 // workgroups take part.
+//
+// Bound by the two exchanges (publish, wait, read: 3.5-5 us each with 256
+// workgroups, about 2 us with 64) and the detect's LDS reads (3 us).  A round
+// takes 14-18 us with 256 workgroups and 7 us with 64; with the committed bits
+// of every color in use read in phase B and every loser's row tested against
+// them, 25-30 and 8.5 us.
 template <int U, int K, int NT>
 __device__ __forceinline__ CoreEnd core_stage(const IncBufs& b, const CoreSet& in, const CoreExchange& x,
                                               const CoreSet& out, int32_t n, int32_t stop_at, int& r, int round_cap,
@@ -429,8 +436,12 @@ __device__ __forceinline__ CoreEnd core_stage(const IncBufs& b, const CoreSet& i
   constexpr int B = K < 4 ? K : 4;
   constexpr int D = K < 4 ? 4 : 8;     // exchange words in flight per thread
   const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int32_t blk = static_cast<int32_t>(blockIdx.x);
-  const int32_t W = U * ((n + P - 1) / P);
+  // consecutive vertices on one XCD (workgroups go round the eight), as they
+  // read the same cache lines of a committed vertex's row
+  const int32_t blocks = (n + P - 1) / P;
+  const int32_t xcd = static_cast<int32_t>(blockIdx.x) % 8;
+  const int32_t blk = xcd * (blocks / 8) + min(xcd, blocks % 8) + static_cast<int32_t>(blockIdx.x) / 8;
+  const int32_t W = U * blocks;
   const int round0 = r;
 
   if (tid < P) {
@@ -486,10 +497,9 @@ __device__ __forceinline__ CoreEnd core_stage(const IncBufs& b, const CoreSet& i
   uint32_t mine = 0;
   for (int s = 0; s < kCoreSlots; ++s) mine |= (s % subs) == rs ? 1u << s : 0u;
   const int32_t my_word = blk * U + wave;  // published by wavefronts 0 .. U-1
-  uint32_t comm = 0;                        // slot `lane`: committed bits of my_word for color comm_c
-  int32_t comm_c = 0;
-  int32_t gmin = 0, gmax = 0, tlo = INT_MAX;
-  uint64_t bytes_a = 0, bytes_b = 0;
+  int32_t gmin = 0, gmax = 0;
+  uint64_t bytes_a = 0;
+  uint32_t seen = 0;  // committed vertices whose rows this thread read
   CoreEnd end = kCoreDone;
   for (;; ++r) {
     const uint32_t tag = static_cast<uint32_t>(r);
@@ -523,19 +533,13 @@ __device__ __forceinline__ CoreEnd core_stage(const IncBufs& b, const CoreSet& i
         const uint32_t p = count | (count ? (wide ? 0u : static_cast<uint32_t>(mn)) << 6 : 0u) |
                            (count ? (wide ? 63u : static_cast<uint32_t>(mx - mn)) << 26 : 0u);
         st_dev(&x.ma[my_word], hi | p);
-        sh.tmin[wave] = mn;
         sh.slots[wave] = slots;
       }
     }
     __syncthreads();
     uint32_t slots = 0;
-    const int32_t gmax_prev = gmax, tlo_prev = tlo;
-    tlo = INT_MAX;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      slots |= sh.slots[u];
-      tlo = min(tlo, sh.tmin[u]);
-    }
+    for (int u = 0; u < U; ++u) slots |= sh.slots[u];
     // only higher keys matter: the words below the workgroup's own
     int32_t cnt = 0, mn = INT_MAX, mx = 0;
     for (int32_t rw = tid & (wp - 1); rw < W; rw += wp) {
@@ -588,13 +592,6 @@ __device__ __forceinline__ CoreEnd core_stage(const IncBufs& b, const CoreSet& i
           sh.fail = 1;
         sh.live[w] = y;
       }
-      // the committed bits of the colors its own vertices may come to, as
-      // phase B of the round before left them
-      const uint32_t want = r > round0 ? core_slots(tlo_prev, gmax_prev) : 0u;
-      for (int32_t rw = tid & (wp - 1); rw < W; rw += wp)
-        if (!core_fetch<D>(x.B, want & mine, W, rw, tag - 1u, nullptr, nullptr, deadline,
-                           [&](int s, uint32_t y) { s_mask[s * S + rw] = y; }))
-          sh.fail = 1;
       __syncthreads();
       if (sh.fail) {
         end = kCoreFail;
@@ -627,13 +624,10 @@ __device__ __forceinline__ CoreEnd core_stage(const IncBufs& b, const CoreSet& i
         const int32_t own = blk * U + i / 32, ti = sh.t[i];
         const int32_t me = sh.before[own] + static_cast<int32_t>(__popc(sh.live[own] & ((1u << (i & 31)) - 1u)));
         const uint32_t* src = in.rows + static_cast<size_t>(blk * P + i) * S;
-        // its forbidden colors: the bitset's, and those its committed
-        // neighbours of earlier stages (in the window it came with) and of
-        // this one took
-        uint64_t fw = core_window(b, sh.v[i], ti);
-        if (ti - sh.fb[i] < 64) fw |= sh.fw[i] >> (ti - sh.fb[i]);
-        for (int32_t c = ti + 1; r > round0 && c <= gmax_prev; ++c)
-          if (core_meets(src, s_mask + (c & (kCoreSlots - 1)) * S, W, lane)) fw |= 1ull << (c - ti);
+        // its forbidden colors: the bitset's, and those its neighbours
+        // committed in the core stages
+        const int32_t ahead = ti - sh.fb[i];
+        const uint64_t fw = core_window(b, sh.v[i], ti) | (ahead < 64 ? sh.fw[i] >> ahead : 0ull);
         // its row over the vertices left
         uint32_t* p = sh.pack[wave];
         for (int w = lane; w < stride; w += kWave) p[w] = 0u;
@@ -671,6 +665,7 @@ __device__ __forceinline__ CoreEnd core_stage(const IncBufs& b, const CoreSet& i
       sh.gmin[par ^ 1] = INT_MAX;
       sh.gmax[par ^ 1] = 0;
     }
+    for (int q = tid; q < kCoreSlots * U; q += NT) sh.hit[q / U][q % U] = 0u;
     // ---- detect: a vertex of higher key with the same tentative color
     // (two vertices at a time, so that their reads overlap)
 #pragma unroll
@@ -693,113 +688,160 @@ __device__ __forceinline__ CoreEnd core_stage(const IncBufs& b, const CoreSet& i
       if (lane < 2 && (wins >> lane) & 1u) sh.won[wave * V + j + lane] = r;
     }
     __syncthreads();
-    // ---- phase B: the committed bits of every color still in use
+    // ---- phase B: the vertices that committed and their colors' slots
     if (wave < U) {
       const int i = 32 * wave + (lane & 31);
-      const int32_t c = gmin + ((lane - gmin) & (kCoreSlots - 1));  // the slot's color
-      if (comm_c != c) {
-        comm = 0;
-        comm_c = c;
-      }
-      const bool won = lane < 32 && sh.won[i] == r;
       const int32_t ti = sh.t[i];
-      uint64_t rem = __ballot(won);
-      while (rem) {
-        const int32_t cw = __builtin_amdgcn_readlane(ti, static_cast<int>(__builtin_ctzll(rem)));
-        const uint64_t m = __ballot(won && ti == cw);
-        if (lane == (cw & (kCoreSlots - 1))) comm |= static_cast<uint32_t>(m);
-        rem &= ~m;
+      const uint64_t m = __ballot(lane < 32 && sh.won[i] == r);
+      uint32_t val = 0;
+      int k = 0;
+      for (uint64_t z = m; z; z &= z - 1ull, ++k) {
+        const uint32_t c = static_cast<uint32_t>(__builtin_amdgcn_readlane(ti, static_cast<int>(__builtin_ctzll(z))));
+        if (lane == k / kCoreColors) val |= (c & (kCoreSlots - 1)) << (5 * (k % kCoreColors));
       }
-      if (lane < 32 && c <= gmax) st_dev(&x.B[lane * W + my_word], hi | comm);
-      if (lane == 32) st_dev(&x.mb[my_word], hi);
+      if (lane == 0 || (lane < kCoreColorWords && lane * kCoreColors < k)) st_dev(&x.B[lane * W + my_word], hi | val);
+      if (lane == 32) st_dev(&x.mb[my_word], hi | static_cast<uint32_t>(m));
     }
-    // colors tlo .. gmax: no vertex of the workgroup is below them, and no
-    // vertex has committed a color above them
-    const uint32_t want = core_slots(tlo, gmax);
-    for (int32_t rw = tid & (wp - 1); rw < W; rw += wp) {
-      uint32_t p;
-      if (!core_fetch<D>(x.B, want & mine, W, rw, tag, rs == 0 ? &x.mb[rw] : nullptr, &p, deadline,
-                         [&](int s, uint32_t y) { s_mask[s * S + rw] = y; }))
-        sh.fail = 1;
+    constexpr int R = (S + NT - 1) / NT;  // words per thread
+    static_assert(R <= 2, "the word loop picks the first or the last");
+    uint32_t won_bits[R], colors[R];
+    {
+      uint64_t t0 = 0;
+      for (int spin = 0;; ++spin) {
+        uint64_t z[R], y[R];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+          const int32_t rw = tid + i * NT;
+          z[i] = rw < W ? ld_dev(&x.mb[rw]) : hi;
+          y[i] = rw < W ? ld_dev(&x.B[rw]) : hi;
+        }
+        bool ready = true;
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+          ready = ready && static_cast<uint32_t>(z[i] >> 32) == tag && static_cast<uint32_t>(y[i] >> 32) == tag;
+          won_bits[i] = static_cast<uint32_t>(z[i]);
+          colors[i] = static_cast<uint32_t>(y[i]);
+        }
+        if (ready) break;
+        if (spin >= 64) {
+          __builtin_amdgcn_s_sleep(1);
+          const uint64_t now = static_cast<uint64_t>(wall_clock64());
+          if (t0 == 0) t0 = now;
+          else if (now - t0 > deadline) {
+            sh.fail = 1;
+#pragma unroll
+            for (int i = 0; i < R; ++i) won_bits[i] = 0;
+            break;
+          }
+        }
+      }
     }
-    bytes_b += 8ull * static_cast<uint64_t>(W + U * (gmax - gmin + 1)) +
-               8ull * static_cast<uint64_t>(__popc(want)) * static_cast<uint64_t>(W);
+    // Each committed vertex's neighbours here, its row's words of the
+    // workgroup's own vertices, are added to the neighbours of its color.
+#pragma unroll 1
+    for (int i = 0; i < R; ++i) {
+      uint32_t bits = i == 0 ? won_bits[0] : won_bits[R - 1];
+      if (bits == 0u) continue;
+      const int32_t rw = tid + i * NT;
+      const int count = __popc(bits);
+      uint32_t more[kCoreColorWords - 1] = {};  // the colors beyond the first word's
+      if (count > kCoreColors) {
+        uint64_t t0 = 0;
+        for (int spin = 0;; ++spin) {
+          bool ready = true;
+#pragma unroll
+          for (int q = 1; q < kCoreColorWords; ++q) {
+            const uint64_t y = q * kCoreColors < count ? ld_dev(&x.B[q * W + rw]) : hi;
+            ready = ready && static_cast<uint32_t>(y >> 32) == tag;
+            more[q - 1] = static_cast<uint32_t>(y);
+          }
+          if (ready) break;
+          if (spin >= 64) {
+            __builtin_amdgcn_s_sleep(1);
+            const uint64_t now = static_cast<uint64_t>(wall_clock64());
+            if (t0 == 0) t0 = now;
+            else if (now - t0 > deadline) {
+              sh.fail = 1;
+              break;
+            }
+          }
+        }
+      }
+      uint32_t packed = i == 0 ? colors[0] : colors[R - 1];
+      int left = kCoreColors;  // colors left in packed
+      while (bits) {
+        // N at a time, so that their reads overlap
+        constexpr int N = 4;
+        uint32_t own[N][U];
+        int32_t slot[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+#pragma unroll
+          for (int u = 0; u < U; ++u) own[j][u] = 0u;
+          slot[j] = 0;
+          if (bits == 0u) continue;
+          const uint32_t* src = in.rows + static_cast<size_t>(32 * rw + __builtin_ctz(bits)) * S + blk * U;
+#pragma unroll
+          for (int u = 0; u < U; ++u) own[j][u] = src[u];
+          bits &= bits - 1u;
+          if (left == 0) {
+            packed = more[0];
+#pragma unroll
+            for (int q = 0; q + 1 < kCoreColorWords - 1; ++q) more[q] = more[q + 1];
+            left = kCoreColors;
+          }
+          slot[j] = static_cast<int32_t>(packed & 31u);
+          packed >>= 5;
+          --left;
+        }
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (own[j][u]) atomicOr(&sh.hit[slot[j]][u], own[j][u]);
+      }
+      seen += static_cast<uint32_t>(count);
+    }
     __syncthreads();
     if (sh.fail) {
       end = kCoreFail;
       break;
     }
     // ---- the losers' next first fit
-    uint32_t far = 0;  // vertices whose window of forbidden colors ends first
-#pragma unroll
-    for (int j = 0; j < V; j += 2) {
-      uint32_t two = (act >> j) & 3u;
-      if (two == 0u) continue;
-      int32_t c[2], fb[2];
-      uint64_t fw[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        c[h] = t[j + h];
-        fb[h] = sh.fb[wave * V + j + h];
-        fw[h] = sh.fw[wave * V + j + h];
-        if (c[h] > gmax) two &= ~(1u << h);
+    if (tid < P && sh.v[tid] >= 0 && sh.won[tid] == 0) {
+      const int32_t c = sh.t[tid], fb = sh.fb[tid];
+      uint64_t fw = sh.fw[tid];
+      uint32_t add = 0;  // bit d: a neighbour has committed color c + d in this round
+      for (int32_t y = c; y <= gmax; ++y) add |= ((sh.hit[y & (kCoreSlots - 1)][tid / 32] >> (tid & 31)) & 1u) << (y - c);
+      if (add) {
+        fw |= static_cast<uint64_t>(add) << (c - fb);
+        sh.fw[tid] = fw;
       }
-      while (two) {
-        uint32_t hit[2] = {0, 0};
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const uint32_t* m = s_mask + (c[h] & (kCoreSlots - 1)) * S + lane * B;
-#pragma unroll
-          for (int q = 0; q < K; ++q) hit[h] |= row[j + h][q] & m[(q / B) * (kWave * B) + q % B];
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const bool held = __ballot(hit[h] != 0u) != 0ull;
-          if (!(two & (1u << h))) continue;
-          const int32_t d = c[h] + 1 - fb[h];
-          const uint64_t rest = d < 64 ? ~fw[h] >> d : 0ull;
-          if (held && rest != 0ull) c[h] = __builtin_amdgcn_readfirstlane(c[h] + 1 + __builtin_ctzll(rest));
-          if (held && rest == 0ull) far |= 1u << (j + h);
-          if (!held || rest == 0ull || c[h] > gmax) two &= ~(1u << h);
+      const uint64_t rest = ~fw >> (c - fb);
+      const int32_t next = rest ? c + static_cast<int32_t>(__builtin_ctzll(rest)) : core_free_from(b, sh.v[tid], fb + 64);
+      if (next != c) {
+        sh.t[tid] = next;
+        const int32_t ahead = next - fb;
+        if (ahead > 32) {  // the window goes on from here
+          sh.fb[tid] = next;
+          sh.fw[tid] = (ahead < 64 ? fw >> ahead : 0ull) | core_window(b, sh.v[tid], next);
         }
       }
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        if (!(act & (1u << (j + h)))) continue;
-        t[j + h] = c[h];
-        if (lane == 0) sh.t[wave * V + j + h] = c[h];
-      }
-    }
-    if (far) {
-      // (rarely) the row from memory, the rest of the forbidden bitset, and a
-      // window from the new color on
-#pragma unroll 1
-      for (int j = 0; j < V; ++j) {
-        if (!(far & (1u << j))) continue;
-        const int i = wave * V + j;
-        int32_t c = sh.t[i];
-        while (c <= gmax && core_meets(in.rows + static_cast<size_t>(blk * P + i) * S,
-                                       s_mask + (c & (kCoreSlots - 1)) * S, W, lane))
-          c = __builtin_amdgcn_readfirstlane(core_next(b, sh.v[i], c, sh.fb[i], sh.fw[i]));
-        const uint64_t fw = core_window(b, sh.v[i], c);
-        if (lane == 0) {
-          sh.t[i] = sh.fb[i] = c;
-          sh.fw[i] = fw;
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < V; ++j) t[j] = __builtin_amdgcn_readfirstlane(sh.t[wave * V + j]);
     }
     __syncthreads();
+#pragma unroll
+    for (int j = 0; j < V; ++j) t[j] = __builtin_amdgcn_readfirstlane(sh.t[wave * V + j]);
   }
   if (end != kCoreFail && end != kCoreSpread) {
     if (wave * kWave < P) {
       const bool have = tid < P;
       core_account(b, have ? sh.v[tid] : -1, have ? sh.t[tid] : 0, have ? sh.won[tid] : 0, round0, r - 1);
     }
+    const int32_t rows = wave_reduce(static_cast<int32_t>(seen), 0, [](int32_t p, int32_t q) { return p + q; });
+    if (lane == 0 && rows) atomicAdd(&acc_slot(b.acc)[7], 4ull * U * static_cast<unsigned long long>(rows));
     if (tid == 0) {
       atomicAdd(&acc_slot(b.acc)[6], static_cast<unsigned long long>(bytes_a));
-      atomicAdd(&acc_slot(b.acc)[7], static_cast<unsigned long long>(bytes_b));
+      atomicAdd(&acc_slot(b.acc)[7], 16ull * static_cast<unsigned long long>(W) * static_cast<unsigned long long>(r - round0));
     }
   }
   return end;
@@ -1003,7 +1045,7 @@ __global__ __launch_bounds__(NT) void core_wide_kernel(IncBufs b, CoreSet in, Co
                                                        CoreHeader* head, int32_t n, int round0, int round_cap,
                                                        uint32_t* bar, int32_t* err, int32_t* left, uint64_t deadline,
                                                        uint64_t checkin_ticks) {
-  __shared__ uint32_t s_mask[kCoreSlots * kWave * K];
+  __shared__ alignas(16) uint32_t s_mask[kCoreSlots * kWave * K];
   __shared__ CoreShared<U, NT> sh;
   __shared__ int32_t s_ok;
   if (!tail_checkin(&bar[kBarCheckin], &bar[kBarState], err, checkin_ticks, &s_ok)) return;
@@ -1033,7 +1075,7 @@ __global__ __launch_bounds__(NT) void core_wide_kernel(IncBufs b, CoreSet in, Co
 __global__ __launch_bounds__(kCoreThreads) void core_kernel(IncBufs b, CoreScratch x, const CoreHeader* head, int32_t n,
                                                             int round0, int round_cap, uint32_t* bar, int32_t* err,
                                                             int32_t* left, uint64_t deadline, uint64_t checkin_ticks) {
-  __shared__ uint32_t s_mask[kCoreSlots * kWave * 2];
+  __shared__ alignas(16) uint32_t s_mask[kCoreSlots * kWave * 2];
   __shared__ union {
     CoreShared<2, kCoreThreads> mid;
     SmallShared small;
@@ -1116,7 +1158,7 @@ size_t layout(char* base, int32_t n, CoreScratch* x, CoreHeader** head, uint64_t
   for (int s = 0; s < kSets - 1; ++s) {
     const size_t w = static_cast<size_t>(s == 0 ? first_words(n) : n > kMidMax ? kMidMax / 32 : 0);
     x->x[s].A = reinterpret_cast<uint64_t*>(take(8 * w * kCoreSlots));
-    x->x[s].B = reinterpret_cast<uint64_t*>(take(8 * w * kCoreSlots));
+    x->x[s].B = reinterpret_cast<uint64_t*>(take(8 * w * kCoreColorWords));
     x->x[s].ma = reinterpret_cast<uint64_t*>(take(8 * w));
     x->x[s].mb = reinterpret_cast<uint64_t*>(take(8 * w));
     x->x[s].flag = reinterpret_cast<uint64_t*>(take(8 * 256));
