@@ -88,3 +88,26 @@ def test_heavy_columns_and_id_range(gc, n_cols, hop):
     b = pattern(n_rows, n_cols, np.concatenate((*rows, np.repeat(np.arange(n_rows), 2), few)),
                 np.concatenate((*cols, more, rng.choice(pool, len(few)))))
     check_pd2(gc, b, 4)
+
+
+# hubs adjacent to each other and to tens of thousands of vertices: they lose
+# for many rounds with lists on both sides of the length that is compacted a
+# window at a time, in the per-round kernels and in the tail kernel
+@pytest.mark.parametrize("flags, tail", [("COLOR_FLAG_NO_TAIL", 0), (None, 1 << 30), (None, 0)])
+@pytest.mark.parametrize("leaves", [16000, 17000, 50000])
+def test_long_lists(gc, leaves, flags, tail):
+    rng = np.random.default_rng(leaves)
+    n, hubs = 80000, 24
+    u = np.concatenate((np.repeat(np.arange(hubs), leaves), np.repeat(np.arange(hubs), hubs), rng.integers(0, n, 200000)))
+    v = np.concatenate([rng.choice(n, leaves, replace=False) for _ in range(hubs)]
+                       + [np.tile(np.arange(hubs), hubs), rng.integers(0, n, 200000)])
+    perm = rng.permutation(n)
+    g = gg.csr_from_pairs(n, perm[u], perm[v], True)
+    ref = oracle.color_d1(g, seed=6)
+    got, st = gc.color_d1(dev(g.row_ptr), dev(g.col), seed=6, trace_cap=4096,
+                          params=gc.Params(engine=gc.ENGINE_INCREMENTAL, tail_threshold=tail,
+                                           flags=getattr(gc, flags) if flags else 0))
+    torch.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy(), ref.colors)
+    assert st.rounds == ref.rounds > 10 and st.worklist == ref.worklist
+    assert st.vertex_visits == ref.vertex_visits and st.edge_visits == ref.edge_visits
