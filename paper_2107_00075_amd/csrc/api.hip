@@ -297,6 +297,15 @@ int run_phase(Call& c, const GraphView& g, const KeySource& k, const BinLayout& 
       b.wl_out = wl[pout];
       b.cnt_in = S->half[pin].cnt;
       b.cnt_out = S->half[pout].cnt;
+      if (base.uniform && local == 1) {
+        if (c.timing && c.record_event(1)) return COLOR_EHIP;
+        launch_first_round<MODE>(g, k, b, L, round0 + local, grid, static_cast<int32_t>(total), c.st);
+        if (c.timing && c.record_event(-1)) return COLOR_EHIP;
+        c.launches += 2;
+        c.color_launches += 1;
+        c.detect_launches += 1;
+        continue;
+      }
       if (c.timing && c.record_event(0)) return COLOR_EHIP;
       launch_color_round<MODE>(g, k, b, L, round0 + local, grid, c.st);
       if (c.timing && c.record_event(1)) return COLOR_EHIP;
@@ -405,6 +414,9 @@ int setup_bins(Call& c, const GraphView& g, const int32_t* init, int32_t* C, int
   rb.trace = w->trace.as<int32_t>();
   rb.trace_cap = c.trace_cap;
   rb.rounds_done = &S->rounds_done;
+  // (a work that does not fit 32 bits is counted as INT_MAX)
+  rb.uniform = init == nullptr && H->max_work < INT_MAX;
+  rb.first_work = H->total_work;
 
   launch_scatter(n, C, w->bin.as<int8_t>(), L, c.wl[0], S->half[0].cnt, w->split_vertex.as<int32_t>(), c.st);
   c.launches += 1;

@@ -253,15 +253,15 @@ __device__ __forceinline__ void round_units(BatchJob* J, const JobView& V, const
           default: color_chunk_group<MODE, 64, LD, 1>(g, b, wl, cnt, work_acc); break;
         }
       } else {
-        const int32_t oo = sh.off[bin];
+        const DirectOut out{&b.cnt_out[bin], b.wl_out + sh.off[bin]};
         switch (G) {
-          case 1: detect_chunk_group<MODE, 1, LD, 1>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
-          case 2: detect_chunk_group<MODE, 2, LD, 1>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
-          case 4: detect_chunk_group<MODE, 4, LD, 1>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
-          case 8: detect_chunk_group<MODE, 8, LD, 1>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
-          case 16: detect_chunk_group<MODE, 16, LD, 1>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
-          case 32: detect_chunk_group<MODE, 32, LD, 1>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
-          default: detect_chunk_group<MODE, 64, LD, 1>(g, k, b, bin, wl, cnt, oo, sh.ent, sh.wc, maxc_acc); break;
+          case 1: detect_chunk_group<MODE, 1, LD, 1>(g, k, b, wl, cnt, out, sh.ent, sh.wc, maxc_acc); break;
+          case 2: detect_chunk_group<MODE, 2, LD, 1>(g, k, b, wl, cnt, out, sh.ent, sh.wc, maxc_acc); break;
+          case 4: detect_chunk_group<MODE, 4, LD, 1>(g, k, b, wl, cnt, out, sh.ent, sh.wc, maxc_acc); break;
+          case 8: detect_chunk_group<MODE, 8, LD, 1>(g, k, b, wl, cnt, out, sh.ent, sh.wc, maxc_acc); break;
+          case 16: detect_chunk_group<MODE, 16, LD, 1>(g, k, b, wl, cnt, out, sh.ent, sh.wc, maxc_acc); break;
+          case 32: detect_chunk_group<MODE, 32, LD, 1>(g, k, b, wl, cnt, out, sh.ent, sh.wc, maxc_acc); break;
+          default: detect_chunk_group<MODE, 64, LD, 1>(g, k, b, wl, cnt, out, sh.ent, sh.wc, maxc_acc); break;
         }
       }
     } else {

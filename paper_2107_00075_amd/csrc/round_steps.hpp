@@ -195,11 +195,22 @@ __device__ __forceinline__ void color_vertex_block(const GraphView& g, const Rou
 // ---------------------------------------------------------------------------
 // detect + commit + compact: group of G lanes per vertex, one chunk
 // ---------------------------------------------------------------------------
-// Losers of the chunk are collected in LDS and appended to W_{r+1} with one
-// device atomic per chunk (workgroup prefix over the wavefront ballots).
-template <int MODE, int G, int LD = 0, int MUT = 0>
-__device__ __forceinline__ void detect_chunk_group(const GraphView& g, const KeySource& k, const RoundBufs& b, int bin,
-                                   const int32_t* wl, int32_t count, int32_t off_out, int32_t* s_ent,
+// Losers of the chunk are collected in LDS (workgroup prefix over the
+// wavefront ballots) and given to `out`: out.reserve(n), by one thread, is the
+// position of the first, out.put(pos, v) stores one.
+
+// Straight to the next worklist, with one device atomic per chunk.
+struct DirectOut {
+  int32_t* cnt;
+  int32_t* wl;
+  __device__ __forceinline__ int32_t reserve(int32_t n) const { return atomicAdd(cnt, n); }
+  __device__ __forceinline__ void put(int32_t pos, int32_t v) const { st_dev(&wl[pos], v); }
+};
+
+// UNI: every tentative color is 1 and none is read (launch_first_round).
+template <int MODE, int G, int LD = 0, int MUT = 0, bool UNI = false, typename Out>
+__device__ __forceinline__ void detect_chunk_group(const GraphView& g, const KeySource& k, const RoundBufs& b,
+                                   const int32_t* wl, int32_t count, const Out& out, int32_t* s_ent,
                                    int32_t* s_wc, int32_t& maxc_acc) {
   constexpr int per_pass = kBlock / G;
   const int sub = threadIdx.x % G;
@@ -207,7 +218,7 @@ __device__ __forceinline__ void detect_chunk_group(const GraphView& g, const Key
   int32_t idx = threadIdx.x / G;
   if (idx < count) {
     int32_t v = ld_mut<MUT>(&wl[idx]);
-    int32_t beg = gld<LD>(&g.rp[v]), end = gld<LD>(&g.rp[v + 1]), tv = ld_mut<MUT>(&T[v]);
+    int32_t beg = gld<LD>(&g.rp[v]), end = gld<LD>(&g.rp[v + 1]), tv = UNI ? 1 : ld_mut<MUT>(&T[v]);
     while (true) {
       const int32_t next = idx + per_pass;
       const int32_t vn = next < count ? ld_mut<MUT>(&wl[next]) : v;
@@ -215,7 +226,10 @@ __device__ __forceinline__ void detect_chunk_group(const GraphView& g, const Key
       bool lose = false;
       // keys first: only higher keys can win
       scan_nbhd<MODE, LD>(g, v, beg, end, sub, G,
-                          [&](int32_t u) __attribute__((always_inline)) { return key_of(k, u) > kv ? ld_mut<MUT>(&T[u]) : 0; },
+                          [&](int32_t u) __attribute__((always_inline)) {
+                            if (UNI) return u < g.n && key_of(k, u) > kv ? 1 : 0;
+                            return key_of(k, u) > kv ? ld_mut<MUT>(&T[u]) : 0;
+                          },
                           [&](int32_t c) __attribute__((always_inline)) {
                             lose = lose || c == tv;
                             return lose;
@@ -235,7 +249,7 @@ __device__ __forceinline__ void detect_chunk_group(const GraphView& g, const Key
       v = vn;
       beg = gld<LD>(&g.rp[v]);
       end = gld<LD>(&g.rp[v + 1]);
-      tv = ld_mut<MUT>(&T[v]);
+      tv = UNI ? 1 : ld_mut<MUT>(&T[v]);
     }
   }
   __syncthreads();
@@ -252,23 +266,26 @@ __device__ __forceinline__ void detect_chunk_group(const GraphView& g, const Key
       s_wc[w] = tot;
       tot += c;
     }
-    s_wc[kWavesPerBlock] = tot ? atomicAdd(&b.cnt_out[bin], tot) : 0;
+    s_wc[kWavesPerBlock] = tot ? out.reserve(tot) : 0;
   }
   __syncthreads();
-  if (x >= 0) st_dev(&b.wl_out[off_out + s_wc[kWavesPerBlock] + s_wc[wave] + static_cast<int32_t>(lanes_below(bal))], x);
+  if (x >= 0) out.put(s_wc[kWavesPerBlock] + s_wc[wave] + static_cast<int32_t>(lanes_below(bal)), x);
   __syncthreads();
 }
 
-template <int MODE, int LD = 0, int MUT = 0>
+template <int MODE, int LD = 0, int MUT = 0, bool UNI = false>
 __device__ __forceinline__ void detect_vertex_block(const GraphView& g, const KeySource& k, const RoundBufs& b,
                                     int32_t v, int32_t off, int32_t& maxc_acc) {
   const int tid = threadIdx.x;
   const int32_t* __restrict__ T = b.T;
-  const int32_t tv = ld_mut<MUT>(&T[v]);
+  const int32_t tv = UNI ? 1 : ld_mut<MUT>(&T[v]);
   const uint64_t kv = key_of(k, v);
   bool lose = false;
   scan_nbhd<MODE, LD>(g, v, gld<LD>(&g.rp[v]), gld<LD>(&g.rp[v + 1]), tid, kBlock,
-                      [&](int32_t u) __attribute__((always_inline)) { return key_of(k, u) > kv ? ld_mut<MUT>(&T[u]) : 0; },
+                      [&](int32_t u) __attribute__((always_inline)) {
+                        if (UNI) return u < g.n && key_of(k, u) > kv ? 1 : 0;
+                        return key_of(k, u) > kv ? ld_mut<MUT>(&T[u]) : 0;
+                      },
                       [&](int32_t c) __attribute__((always_inline)) {
                         lose = lose || c == tv;
                         return lose;

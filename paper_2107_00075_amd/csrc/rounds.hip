@@ -230,7 +230,7 @@ __global__ __launch_bounds__(kBlock) void color_round_kernel(GraphView g, KeySou
   if (threadIdx.x == 0 && s_work) atomicAdd(&acc_slot(b.visits)[1], s_work);
 }
 
-template <int MODE>
+template <int MODE, bool UNI>
 __device__ __forceinline__ void detect_split_chunk(const GraphView& g, const KeySource& k, const RoundBufs& b,
                                    const BinLayout& L, int32_t si, int chunk, int32_t* s_misc,
                                    int32_t& maxc_acc) {
@@ -242,12 +242,15 @@ __device__ __forceinline__ void detect_split_chunk(const GraphView& g, const Key
   const int32_t cb = rb + static_cast<int32_t>(len * chunk / nch);
   const int32_t ce = rb + static_cast<int32_t>(len * (chunk + 1) / nch);
   const int32_t* __restrict__ T = b.T;
-  const int32_t tv = ld_mut<0>(&T[v]);
+  const int32_t tv = UNI ? 1 : ld_mut<0>(&T[v]);
   const uint64_t kv = key_of(k, v);
   bool lose = false;
   if (atomic_load_u32(&b.split_flag[si]) == 0u) {  // another chunk may already have decided
     scan_nbhd<MODE>(g, v, cb, ce, tid, kBlock,
-                    [&](int32_t u) __attribute__((always_inline)) { return key_of(k, u) > kv ? ld_mut<0>(&T[u]) : 0; },
+                    [&](int32_t u) __attribute__((always_inline)) {
+                      if (UNI) return u < g.n && key_of(k, u) > kv ? 1 : 0;
+                      return key_of(k, u) > kv ? ld_mut<0>(&T[u]) : 0;
+                    },
                     [&](int32_t c) __attribute__((always_inline)) {
                       lose = lose || c == tv;
                       return lose;
@@ -274,7 +277,38 @@ __device__ __forceinline__ void detect_split_chunk(const GraphView& g, const Key
   __syncthreads();
 }
 
-template <int MODE>
+// The workgroup's losers of a bin on their way to the next worklist: one
+// counter atomic per some hundred.  (One per chunk of up to 256 vertices, at
+// about 10 ns each one after another, was 80 of the 124 us of round 1 on a 2
+// M-vertex mesh.)
+constexpr int kLosers = 1024;
+struct LoserBuf {
+  int32_t v[kLosers];
+  int32_t n, bin, base;
+};
+struct BufferedOut {
+  LoserBuf* o;
+  __device__ __forceinline__ int32_t reserve(int32_t n) const {
+    const int32_t at = o->n;
+    o->n = at + n;
+    return at;
+  }
+  __device__ __forceinline__ void put(int32_t pos, int32_t v) const { o->v[pos] = v; }
+};
+
+__device__ __forceinline__ void flush_losers(const RoundBufs& b, const BinLayout& L, LoserBuf& o) {
+  const int32_t n = o.n;
+  if (n == 0) return;
+  if (threadIdx.x == 0) o.base = atomicAdd(&b.cnt_out[o.bin], n);
+  __syncthreads();
+  int32_t* to = b.wl_out + L.off[o.bin] + o.base;
+  for (int i = threadIdx.x; i < n; i += kBlock) st_dev(&to[i], o.v[i]);
+  __syncthreads();
+  if (threadIdx.x == 0) o.n = 0;
+  __syncthreads();
+}
+
+template <int MODE, bool UNI>
 __global__ __launch_bounds__(kBlock) void detect_round_kernel(GraphView g, KeySource k, RoundBufs b,
                                                               BinLayout L, int round) {
   __shared__ int32_t s_misc[4];
@@ -282,11 +316,14 @@ __global__ __launch_bounds__(kBlock) void detect_round_kernel(GraphView g, KeySo
   __shared__ int32_t s_max;
   __shared__ int32_t s_ent[kBlock];
   __shared__ int32_t s_wc[kWavesPerBlock + 1];
+  __shared__ LoserBuf s_out;
   __shared__ RoundMap M;
   (void)round;
   if (threadIdx.x == 0) {
     make_round_map(b, L, M);
     s_max = 0;
+    s_out.n = 0;
+    s_out.bin = -1;
     if (blockIdx.x == 0) atomic_reset_i32(&b.tile_ctr[0]);
   }
   __syncthreads();
@@ -299,17 +336,25 @@ __global__ __launch_bounds__(kBlock) void detect_round_kernel(GraphView g, KeySo
     int32_t first, count;
     light_chunk(M, c, bin, first, count);
     const int32_t* wl = b.wl_in + L.off[bin] + first;
-    const int32_t oo = L.off[bin];
-    switch (L.lanes[bin]) {
-      case 1: detect_chunk_group<MODE, 1>(g, k, b, bin, wl, count, oo, s_ent, s_wc, maxc_acc); break;
-      case 2: detect_chunk_group<MODE, 2>(g, k, b, bin, wl, count, oo, s_ent, s_wc, maxc_acc); break;
-      case 4: detect_chunk_group<MODE, 4>(g, k, b, bin, wl, count, oo, s_ent, s_wc, maxc_acc); break;
-      case 8: detect_chunk_group<MODE, 8>(g, k, b, bin, wl, count, oo, s_ent, s_wc, maxc_acc); break;
-      case 16: detect_chunk_group<MODE, 16>(g, k, b, bin, wl, count, oo, s_ent, s_wc, maxc_acc); break;
-      case 32: detect_chunk_group<MODE, 32>(g, k, b, bin, wl, count, oo, s_ent, s_wc, maxc_acc); break;
-      default: detect_chunk_group<MODE, 64>(g, k, b, bin, wl, count, oo, s_ent, s_wc, maxc_acc); break;
+    if (bin != s_out.bin) {  // (a workgroup's chunks are consecutive: few bins)
+      flush_losers(b, L, s_out);
+      __syncthreads();
+      if (threadIdx.x == 0) s_out.bin = bin;
+      __syncthreads();
     }
+    const BufferedOut out{&s_out};
+    switch (L.lanes[bin]) {
+      case 1: detect_chunk_group<MODE, 1, 0, 0, UNI>(g, k, b, wl, count, out, s_ent, s_wc, maxc_acc); break;
+      case 2: detect_chunk_group<MODE, 2, 0, 0, UNI>(g, k, b, wl, count, out, s_ent, s_wc, maxc_acc); break;
+      case 4: detect_chunk_group<MODE, 4, 0, 0, UNI>(g, k, b, wl, count, out, s_ent, s_wc, maxc_acc); break;
+      case 8: detect_chunk_group<MODE, 8, 0, 0, UNI>(g, k, b, wl, count, out, s_ent, s_wc, maxc_acc); break;
+      case 16: detect_chunk_group<MODE, 16, 0, 0, UNI>(g, k, b, wl, count, out, s_ent, s_wc, maxc_acc); break;
+      case 32: detect_chunk_group<MODE, 32, 0, 0, UNI>(g, k, b, wl, count, out, s_ent, s_wc, maxc_acc); break;
+      default: detect_chunk_group<MODE, 64, 0, 0, UNI>(g, k, b, wl, count, out, s_ent, s_wc, maxc_acc); break;
+    }
+    if (s_out.n > kLosers - kBlock) flush_losers(b, L, s_out);
   }
+  flush_losers(b, L, s_out);
   if (M.heavy_total > 0) {
     while (true) {
       if (threadIdx.x == 0) s_unit = atomicAdd(&b.tile_ctr[1], 1);
@@ -319,11 +364,11 @@ __global__ __launch_bounds__(kBlock) void detect_round_kernel(GraphView g, KeySo
       if (u >= M.heavy_total) break;
       if (u < M.heavy_block) {
         const int32_t v = ld_mut<0>(&b.wl_in[L.off[kBlockBin] + u]);
-        detect_vertex_block<MODE>(g, k, b, v, L.off[kBlockBin], maxc_acc);
+        detect_vertex_block<MODE, 0, 0, UNI>(g, k, b, v, L.off[kBlockBin], maxc_acc);
       } else {
         const int32_t us = u - M.heavy_block;
         const int32_t si = ld_mut<0>(&b.wl_in[L.off[kSplitBin] + us / L.split_chunks]);
-        detect_split_chunk<MODE>(g, k, b, L, si, us % L.split_chunks, s_misc, maxc_acc);
+        detect_split_chunk<MODE, UNI>(g, k, b, L, si, us % L.split_chunks, s_misc, maxc_acc);
       }
     }
   }
@@ -340,7 +385,7 @@ static int resident_blocks_of() {
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 2048;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, color_round_kernel<MODE>, kBlock, 0) != hipSuccess)
     return 2048;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&d, detect_round_kernel<MODE>, kBlock, 0) != hipSuccess)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&d, detect_round_kernel<MODE, false>, kBlock, 0) != hipSuccess)
     return 2048;
   const int per_cu = std::max(1, std::min(a, d));
   return std::max(8, (per_cu * cus) / 8 * 8);
@@ -363,10 +408,34 @@ void launch_color_round(const GraphView& g, const KeySource& k, const RoundBufs&
   hipLaunchKernelGGL(color_round_kernel<MODE>, dim3(grid), dim3(kBlock), 0, st, g, k, b, L, round);
 }
 
+__global__ void first_books_kernel(RoundBufs b, int32_t total, int round) {
+  const int i = threadIdx.x;
+  if (i < kBins) atomic_reset_i32(&b.cnt_out[i]);
+  if (i != 0) return;
+  atomic_reset_i32(&b.tile_ctr[1]);
+  atomicMax(b.rounds_done, round);
+  if (b.trace && round <= b.trace_cap) st_dev(&b.trace[round - 1], total);
+  atomicAdd(&b.visits[0], static_cast<unsigned long long>(total));
+  atomicAdd(&b.visits[1], b.first_work);
+}
+
+template <int MODE>
+void launch_first_round(const GraphView& g, const KeySource& k, const RoundBufs& b, const BinLayout& L, int round,
+                        int grid, int32_t total, hipStream_t st) {
+  hipLaunchKernelGGL(first_books_kernel, dim3(1), dim3(kWave), 0, st, b, total, round);
+  hipLaunchKernelGGL((detect_round_kernel<MODE, true>), dim3(grid), dim3(kBlock), 0, st, g, k, b, L, round);
+}
+template void launch_first_round<kD1>(const GraphView&, const KeySource&, const RoundBufs&, const BinLayout&, int, int,
+                                      int32_t, hipStream_t);
+template void launch_first_round<kD2>(const GraphView&, const KeySource&, const RoundBufs&, const BinLayout&, int, int,
+                                      int32_t, hipStream_t);
+template void launch_first_round<kPD2>(const GraphView&, const KeySource&, const RoundBufs&, const BinLayout&, int, int,
+                                       int32_t, hipStream_t);
+
 template <int MODE>
 void launch_detect_round(const GraphView& g, const KeySource& k, const RoundBufs& b,
                          const BinLayout& L, int round, int grid, hipStream_t st) {
-  hipLaunchKernelGGL(detect_round_kernel<MODE>, dim3(grid), dim3(kBlock), 0, st, g, k, b, L, round);
+  hipLaunchKernelGGL((detect_round_kernel<MODE, false>), dim3(grid), dim3(kBlock), 0, st, g, k, b, L, round);
 }
 
 template void launch_color_round<kD1>(const GraphView&, const KeySource&, const RoundBufs&,

@@ -59,6 +59,8 @@ struct RoundBufs {
   int32_t* trace;             // |W_r| per round (nullable)
   int32_t trace_cap;
   int32_t* rounds_done;       // last round with a non-empty worklist
+  int32_t uniform = 0;        // the first round starts from no colors at all (launch_first_round)
+  unsigned long long first_work = 0;  // sum of work over its worklist
 };
 
 template <int MODE>
@@ -67,6 +69,15 @@ void launch_color_round(const GraphView& g, const KeySource& k, const RoundBufs&
 template <int MODE>
 void launch_detect_round(const GraphView& g, const KeySource& k, const RoundBufs& b,
                          const BinLayout& L, int round, int grid, hipStream_t st);
+// The first round of a graph without any color: every vertex's first fit is
+// color 1, so the color kernel's pass over the neighbourhoods is left out (one
+// workgroup keeps the round's books: total vertices in the worklist), and a
+// vertex loses iff a worklist neighbour has a higher key, so the detect kernel
+// gathers no tentative colors.  T is neither written nor read: a vertex that
+// commits keeps 0 there, which ties with no tentative color.
+template <int MODE>
+void launch_first_round(const GraphView& g, const KeySource& k, const RoundBufs& b, const BinLayout& L, int round,
+                        int grid, int32_t total, hipStream_t st);
 
 // Worklist entries per chunk of a bin of cnt vertices with `lanes` lanes each:
 // as few passes of kBlock / lanes vertices as give every workgroup of the
