@@ -126,13 +126,13 @@ typedef struct color_stats {
     int32_t color_launches;
     int32_t detect_launches;
     int32_t engine;              /* COLOR_ENGINE_* that ran */
-    int32_t tail_rounds;         /* INCREMENTAL: rounds run by the cooperative tail kernel */
+    int32_t tail_rounds;         /* INCREMENTAL: rounds run by cooperative launches (tail and core kernels) */
     int64_t list_visits;         /* INCREMENTAL: active-list entries scanned by the detect kernels */
     int64_t pushes;              /* INCREMENTAL: forbidden-color bits pushed */
     int64_t color_bytes;         /* algorithmic bytes of the per-round color kernels (INCREMENTAL; PULL: 0) */
     int64_t detect_bytes;        /* algorithmic bytes of the per-round detect kernels (INCREMENTAL; PULL: 0) */
-    int64_t tail_kernel_ns;      /* COLOR_FLAG_KERNEL_TIMING: HIP-event duration of the tail kernel */
-    int64_t tail_bytes;          /* algorithmic bytes of the tail kernel's rounds (color + detect) */
+    int64_t tail_kernel_ns;      /* COLOR_FLAG_KERNEL_TIMING: HIP-event duration of these launches */
+    int64_t tail_bytes;          /* algorithmic bytes of these launches' rounds (color + detect) */
     int32_t tail_fallbacks;      /* INCREMENTAL: tail launches whose workgroups were not all resident
                                     (they ran nothing; the rounds went on as per-round launches) */
 } color_stats;
@@ -148,9 +148,10 @@ typedef struct color_params {
     int32_t max_rounds;     /* stop after this many rounds: COLOR_ENOCONVERGE (0: n + 1, which
                                no run reaches: each round commits at least one vertex) */
     int32_t rounds_per_poll;/* rounds enqueued between host checks of the worklist size */
-    int32_t tail_threshold; /* INCREMENTAL: worklist size at or below which one cooperative launch
-                               runs all remaining rounds (grid barriers between the steps;
-                               default 32768).  Its workgroups wait on each other, so they
+    int32_t tail_threshold; /* INCREMENTAL: worklist size at or below which cooperative launches
+                               run all remaining rounds (the tail kernel, grid barriers between
+                               the steps; from 24576 vertices on the core kernels, on rows of
+                               adjacency bits; default 32768).  Its workgroups wait on each other, so they
                                must all be resident: before writing anything they check in
                                and wait up to tail_checkin_us for each other; if they are not
                                all resident by then (other streams keep the device full), the
