@@ -371,6 +371,13 @@ __device__ __forceinline__ int32_t wave_reduce(int32_t x, int32_t none, F&& f) {
   return __builtin_amdgcn_readlane(x, kWave - 1);
 }
 
+// Orders a wavefront's accesses to LDS before this point and after it, where
+// lanes take over words from each other.
+__device__ __forceinline__ void wave_step() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // The slots of colors lo .. hi (hi - lo < kCoreSlots).
 __device__ __forceinline__ uint32_t core_slots(int32_t lo, int32_t hi) {
   if (lo > hi) return 0u;
@@ -631,6 +638,7 @@ __device__ __forceinline__ CoreEnd core_stage(const IncBufs& b, const CoreSet& i
         // its row over the vertices left
         uint32_t* p = sh.pack[wave];
         for (int w = lane; w < stride; w += kWave) p[w] = 0u;
+        wave_step();
         for (int w = lane; w < W; w += kWave) {
           const uint32_t live = sh.live[w];
           for (uint32_t z = ld_dev(&src[w]) & live; z; z &= z - 1u) {
@@ -638,8 +646,10 @@ __device__ __forceinline__ CoreEnd core_stage(const IncBufs& b, const CoreSet& i
             atomicOr(&p[g >> 5], 1u << (g & 31));
           }
         }
+        wave_step();
         uint32_t* dst = out.rows + static_cast<size_t>(me) * stride;
         for (int w = lane; w < stride; w += kWave) st_dev(&dst[w], p[w]);
+        wave_step();
         if (lane == 0) {
           st_dev(&out.v[me], sh.v[i]);
           st_dev(&out.t[me], ti);
