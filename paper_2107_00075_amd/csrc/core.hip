@@ -932,6 +932,11 @@ __device__ __forceinline__ CoreEnd core_small(const IncBufs& b, const CoreSet& i
     if (tid == 0) {
       const int gr = r + b.round_base;
       if (b.trace && gr <= b.trace_cap) st_dev(&b.trace[gr - 1], total);
+      // for the next round's phase A, which other wavefronts may reach as
+      // soon as they have passed this round's second barrier
+      sh.total[par ^ 1] = 0;
+      sh.gmin[par ^ 1] = INT_MAX;
+      sh.gmax[par ^ 1] = 0;
     }
     const bool fast = gmax - gmin < kCoreSlots;
     // ---- detect
@@ -987,11 +992,6 @@ __device__ __forceinline__ CoreEnd core_small(const IncBufs& b, const CoreSet& i
       comm_ok = false;
     }
     __syncthreads();
-    if (tid == 0) {
-      sh.total[par ^ 1] = 0;
-      sh.gmin[par ^ 1] = INT_MAX;
-      sh.gmax[par ^ 1] = 0;
-    }
     // ---- next first fit
     if (act) {
       while (t <= gmax) {

@@ -1,5 +1,7 @@
 """The core kernels' source, run on the CPU by the host emulation of the
-device operations, against the oracle."""
+device operations, against the oracle.  The emulation runs the wavefronts of a
+workgroup in any order between two barriers, which no run on the device can be
+made to do."""
 import numpy as np
 import pytest
 
@@ -24,3 +26,16 @@ def check(lib, g, seed=1, prio=None, init=None, max_rounds=0, order=1):
 @pytest.mark.parametrize("n", [1025, 1500])
 def test_hand_over(lib, n):
     check(lib, gg.erdos_renyi(n, 24.0, n), 3, order=0)
+
+
+# one wavefront to all sixteen of the one-workgroup stage, and the stage before
+@pytest.mark.parametrize("n", [64, 65, 300, 1024, 1025])
+@pytest.mark.parametrize("order", [0, 1, 2, 3, 4, 5])
+def test_wavefront_orders(lib, n, order):
+    check(lib, gg.erdos_renyi(n, 24.0, n), 3, order=order)
+
+
+@pytest.mark.parametrize("cap", [1, 4, 9])
+def test_round_cap_in_any_order(lib, cap):
+    for order in range(4):
+        check(lib, gg.erdos_renyi(700, 24.0, 7), 3, max_rounds=cap, order=order)
