@@ -858,17 +858,26 @@ __device__ __forceinline__ CoreEnd core_stage(const IncBufs& b, const CoreSet& i
 }
 
 struct SmallShared {
-  // phase A: bits of the tentative colors; phase B: committed bits (rows
-  // padded so that neighbouring slots start on other banks)
+  // phase A: bits of the tentative colors; phase B: committed bits, in a slot
+  // per lane (rows padded so that neighbouring slots start on other banks)
   alignas(16) uint64_t a[kCoreSlots][kCoreWaves + 2];
-  alignas(16) uint64_t c[kCoreSlots][kCoreWaves + 2];
+  alignas(16) uint64_t c[kWave][kCoreWaves + 2];
   int32_t t[kSmallMax];                    // tentative color, or minus the committed one
   int32_t gmin[2], gmax[2], total[2];
 };
 
 // The one-workgroup stage: a thread per vertex, its row of 1024 bits in
 // registers, the slot masks in LDS.  Rounds whose tentative colors span more
-// than the slots compare the colors of the row's vertices one by one.
+// than their slots compare the colors of the row's vertices one by one.
+//
+// What the stage's vertices have committed is in the slots only (fw and the
+// bitset hold what was committed before), and a loser tests every color it
+// steps over up to `top`, the largest tentative color of any round so far: no
+// committed color of the stage is above it.  The largest tentative color of
+// the round will not do, as it falls when its holders commit.  All committed
+// colors that still matter, gmin .. top, have slots while these span at most
+// kWave colors (a slot's color leaves the window only below gmin, which never
+// falls); else the next first fit compares colors one by one too.
 __device__ __forceinline__ CoreEnd core_small(const IncBufs& b, const CoreSet& in, int32_t n, int& r, int round_cap,
                                               SmallShared& sh) {
   constexpr int R = kSmallMax / 64;
@@ -895,6 +904,7 @@ __device__ __forceinline__ CoreEnd core_small(const IncBufs& b, const CoreSet& i
   uint64_t comm = 0;
   int32_t comm_c = 0;
   bool comm_ok = true;
+  int32_t top = 0;
   CoreEnd end = kCoreDone;
   __syncthreads();
   for (;; ++r) {
@@ -939,6 +949,8 @@ __device__ __forceinline__ CoreEnd core_small(const IncBufs& b, const CoreSet& i
       sh.gmax[par ^ 1] = 0;
     }
     const bool fast = gmax - gmin < kCoreSlots;
+    top = max(top, gmax);
+    const bool slots = top - gmin < kWave;
     // ---- detect
     bool wins = false;
     if (on) {
@@ -964,14 +976,14 @@ __device__ __forceinline__ CoreEnd core_small(const IncBufs& b, const CoreSet& i
     if (wins) {
       act = false;
       won = r;
-      if (!fast) sh.t[tid] = -t;
+      if (!slots) sh.t[tid] = -t;
     }
-    if (fast) {
-      const int32_t c = gmin + ((lane - gmin) & (kCoreSlots - 1));
+    if (slots) {
+      const int32_t c = gmin + ((lane - gmin) & (kWave - 1));
       if (!comm_ok) {  // rounds without slots came before: count afresh
         comm = 0;
-        for (int s = 0; s < kCoreSlots; ++s) {
-          const int32_t cs = gmin + ((s - gmin) & (kCoreSlots - 1));
+        for (int s = 0; s < kWave; ++s) {
+          const int32_t cs = gmin + ((s - gmin) & (kWave - 1));
           const uint64_t m = __ballot(won != 0 && t == cs);
           if (lane == s) comm = m;
         }
@@ -982,22 +994,22 @@ __device__ __forceinline__ CoreEnd core_small(const IncBufs& b, const CoreSet& i
         while (rem) {
           const int32_t cw = __builtin_amdgcn_readlane(t, static_cast<int>(__builtin_ctzll(rem)));
           const uint64_t m = __ballot(wins && t == cw);
-          if (lane == (cw & (kCoreSlots - 1))) comm |= m;
+          if (lane == (cw & (kWave - 1))) comm |= m;
           rem &= ~m;
         }
       }
       comm_c = c;
-      if (lane < kCoreSlots) sh.c[lane][wave] = comm;
+      sh.c[lane][wave] = comm;
     } else {
       comm_ok = false;
     }
     __syncthreads();
     // ---- next first fit
     if (act) {
-      while (t <= gmax) {
+      while (t <= top) {
         bool hit = false;
-        if (fast) {
-          const uint64_t* m = sh.c[t & (kCoreSlots - 1)];
+        if (slots) {
+          const uint64_t* m = sh.c[t & (kWave - 1)];
           uint64_t y = 0;
 #pragma unroll
           for (int p = 0; p < R; ++p) y |= row[p] & m[p];
@@ -1011,7 +1023,7 @@ __device__ __forceinline__ CoreEnd core_small(const IncBufs& b, const CoreSet& i
         t = core_next(b, v, t, fb, fw);
       }
     }
-    if (!fast) __syncthreads();  // every committed color has been read
+    if (!slots) __syncthreads();  // every committed color has been read
   }
   core_account(b, v, t, won, round0, r - 1);
   if (tid == 0) atomicAdd(&acc_slot(b.acc)[7], static_cast<unsigned long long>(n) * (4ull * row_words(kSmallMax) + 20ull));

@@ -5,6 +5,7 @@ made to do."""
 import numpy as np
 import pytest
 
+import core_cases
 import emu_lib
 import graphgen as gg
 import oracle
@@ -39,3 +40,30 @@ def test_wavefront_orders(lib, n, order):
 def test_round_cap_in_any_order(lib, cap):
     for order in range(4):
         check(lib, gg.erdos_renyi(700, 24.0, 7), 3, max_rounds=cap, order=order)
+
+
+@pytest.mark.parametrize("path,top,low", core_cases.CLIMBS)
+def test_colors_above_the_active_ones(lib, path, top, low):
+    """A color that was committed while the active vertices' colors reached it
+    is still there when they have fallen below it and climb past it."""
+    g, prio = core_cases.climb(path, top, low)
+    check(lib, g, prio=prio)
+    check(lib, core_cases.climb_by_hash(path, top, low, 200, 1), seed=1)
+
+
+@pytest.mark.parametrize("path,top,low", [(60, 30, 40), (60, 12, 15)])
+def test_colors_above_the_active_ones_after_a_hand_over(lib, path, top, low):
+    g, prio = core_cases.beside(*core_cases.climb(path, top, low), 1400, 2)
+    check(lib, g, prio=prio)
+
+
+def test_five_vertices(lib):
+    g, init, prio = core_cases.five()
+    check(lib, g, init=init, prio=prio)
+
+
+@pytest.mark.parametrize("m,p,steps", core_cases.ANCHORED)
+def test_dense_with_uneven_forbidden_colors(lib, m, p, steps):
+    for seed in range(6 if m < 500 else 1):
+        g, init = core_cases.anchored(m, p, 0.3, steps, seed)
+        check(lib, g, init=init, order=seed)
