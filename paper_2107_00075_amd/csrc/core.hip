@@ -1104,7 +1104,8 @@ __global__ __launch_bounds__(kCoreThreads) void core_kernel(IncBufs b, CoreScrat
   } sh;
   __shared__ int32_t s_ok;
   if (head) {
-    if (!head->handed) return;
+    // (a workgroup whose wait gave up has not written its part of set 1)
+    if (!head->handed || (ld_dev(err) & kErrTailBarrier)) return;
     n = head->left;
     round0 = head->round;
   }

@@ -74,3 +74,40 @@ extern "C" int core_run(int32_t n, const int32_t* rp, const int32_t* ci, uint32_
   for (int s = 0; s < kAccSlots; ++s) *visits += static_cast<int64_t>(acc[s * kAccStride]);
   return err;
 }
+
+// The second launch of a call of two, after a first one that ended with the
+// error bits err and whose workgroup 0 handed n isolated vertices over.
+// colors receives what it wrote.  Returns the error bits afterwards.
+extern "C" int core_second_launch(int32_t n, int32_t err, int32_t* colors) {
+  emu::seed = 1;
+  const int32_t all = kMidMax + 64;  // vertices of the first launch
+  std::vector<uint64_t> scratch(core_scratch_bytes(all) / 8 + 1);
+  CoreScratch x;
+  CoreHeader* head;
+  uint64_t* clear;
+  int32_t words;
+  layout(reinterpret_cast<char*>(scratch.data()), all, &x, &head, &clear, &words);
+  for (int32_t v = 0; v < n; ++v) {
+    x.set[1].v[v] = v;
+    x.set[1].t[v] = 1;
+  }
+  head->handed = 1;
+  head->left = n;
+  head->round = 5;
+  std::vector<int32_t> work(n), fw_off(n + 1);
+  std::vector<uint32_t> F(n + 1), bar(kBarWords);
+  std::vector<unsigned long long> acc(kAccSlots * kAccStride);
+  int32_t maxc = 0, rounds = 0, left = 0;
+  IncBufs b{};
+  b.C = colors;
+  b.work = work.data();
+  b.fw_off = fw_off.data();
+  b.F = F.data();
+  b.Fx = F.data() + n;
+  b.maxc = &maxc;
+  b.acc = acc.data();
+  b.rounds_done = &rounds;
+  emu::launch(dim3(kMidMax / 64), dim3(kCoreThreads),
+              [&] { core_kernel(b, x, head, all, 1, INT_MAX, bar.data(), &err, &left, 3000000000u, 6000000000u); }, true);
+  return err;
+}

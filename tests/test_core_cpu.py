@@ -67,3 +67,12 @@ def test_dense_with_uneven_forbidden_colors(lib, m, p, steps):
     for seed in range(6 if m < 500 else 1):
         g, init = core_cases.anchored(m, p, 0.3, steps, seed)
         check(lib, g, init=init, order=seed)
+
+
+@pytest.mark.parametrize("err", [0x800, 0x900])
+def test_second_launch_after_the_first(lib, err):
+    """After a first launch in which a wait gave up (0x100), what it handed
+    over is not complete: the second launch does nothing."""
+    colors = np.zeros(100, np.int32)
+    assert lib.core_second_launch(100, err, emu_lib.ptr(colors)) == err
+    assert (colors == (0 if err & 0x100 else 1)).all()
