@@ -1151,13 +1151,16 @@ __device__ __forceinline__ void walk_two_hop(const GraphView& g, int32_t v, int3
   const int sub = lane_id() & (G - 1);
   int32_t* s_at = s_row;       // row start minus the entries before it
   int32_t* s_end = s_row + G;  // entries up to the row's end
-  // a pass's entries are read two passes ahead, its row bounds one
-  auto entry = [&](int32_t q) { return q < q1 ? g.ci[q] : -1; };
-  int32_t u = entry(q0 + sub), un = entry(q0 + sub + G);
+  // a pass's entries are read two passes ahead, its row bounds one (left: the
+  // entries from the lane's of this pass on; positions behind q1 or behind a
+  // row's end may not fit 32 bits)
+  int32_t q = q0 + sub, left = q1 - q0 - sub;
+  auto entry = [&](int32_t ahead) { return ahead < left ? g.ci[q + ahead] : -1; };
+  int32_t u = entry(0), un = entry(G);
   int32_t b2 = u >= 0 ? g.rp2[u] : 0, e2 = u >= 0 ? g.rp2[u + 1] : 0;
-  for (int32_t qb = q0; qb < q1; qb += G) {
+  for (; left + sub > 0; left -= G, q += G) {
     const int32_t len = e2 - b2;
-    const int32_t unn = entry(qb + sub + 2 * G);
+    const int32_t unn = entry(2 * G);
     const int32_t bn = un >= 0 ? g.rp2[un] : 0, en = un >= 0 ? g.rp2[un + 1] : 0;
     if (MODE == kD2) {
       const int32_t x[4] = {u < g.limit ? u : -1, -1, -1, -1};
@@ -1174,7 +1177,8 @@ __device__ __forceinline__ void walk_two_hop(const GraphView& g, int32_t v, int3
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     const int32_t all = s_end[G - 1];
-    for (int32_t e0 = sub; e0 - sub < all; e0 += 4 * G) {
+    int32_t e0 = sub;
+    for (int32_t more = all; more > 0; more -= 4 * G, e0 += 4 * G) {
       int32_t x[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -1182,7 +1186,7 @@ __device__ __forceinline__ void walk_two_hop(const GraphView& g, int32_t v, int3
         int r = 0;
 #pragma unroll
         for (int step = G / 2; step > 0; step >>= 1) r += s_end[r + step - 1] <= e ? step : 0;
-        x[j] = e < all ? g.ci2[s_at[r] + e] : -1;
+        x[j] = j * G + sub < more ? g.ci2[s_at[r] + e] : -1;
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j)
@@ -1502,9 +1506,9 @@ __global__ __launch_bounds__(kSetThreads) void inc_sets_kernel(GraphView g, cons
     __syncthreads();
     // each wavefront a run of its own, so that its reads run ahead
     const int32_t per = ((z - a + kSetThreads - 1) / kSetThreads) * kWave;
-    const int32_t q = a + wave * per;
-    if (q < z)
-      walk_two_hop<MODE, kWave>(g, v, q, min(q + per, z), s_row[wave],
+    const int32_t skip = wave * per;
+    if (skip < z - a)
+      walk_two_hop<MODE, kWave>(g, v, a + skip, z - a - skip < per ? z : a + skip + per, s_row[wave],
                                 [&](const int32_t (&x)[4]) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)

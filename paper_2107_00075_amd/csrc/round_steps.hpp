@@ -28,7 +28,8 @@ __device__ __forceinline__ X gld(const X* p) {
 // Visits the neighbourhood entries of v reachable from hop-1 positions
 // [beg, end) with lane stride (sub, stride).  get(u) loads what the step needs
 // of entry u (0: nothing), use(x) takes it and returns true to stop (checked
-// once per batch).  A lane has eight entries in flight, D2/PD2 four of each of
+// once per batch).  The loops count the entries left: a position behind the
+// row's end may not fit 32 bits.  A lane has eight entries in flight, D2/PD2 four of each of
 // two second-hop rows: a step's time is its chain of dependent loads (entry,
 // then color), so the chain is walked once per eight entries.  Measured on
 // MI355X against one entry at a time, with the lanes unchanged: D1 27-point
@@ -39,10 +40,11 @@ __device__ __forceinline__ void scan_nbhd(const GraphView& g, int32_t v, int32_t
                                           int sub, int stride, GET&& get, USE&& use) {
   if constexpr (MODE == kD1) {
     constexpr int N = 8;
-    for (int32_t e0 = beg + sub; e0 < end; e0 += N * stride) {
+    int32_t e0 = beg + sub;
+    for (int32_t left = end - beg - sub; left > 0; left -= N * stride, e0 += N * stride) {
       int32_t u[N], x[N];
 #pragma unroll
-      for (int j = 0; j < N; ++j) u[j] = e0 + j * stride < end ? gld<LD>(&g.ci[e0 + j * stride]) : INT_MAX;
+      for (int j = 0; j < N; ++j) u[j] = j * stride < left ? gld<LD>(&g.ci[e0 + j * stride]) : INT_MAX;
 #pragma unroll
       for (int j = 0; j < N; ++j) x[j] = u[j] < g.limit ? get(u[j]) : 0;
       bool stop = false;
@@ -52,32 +54,32 @@ __device__ __forceinline__ void scan_nbhd(const GraphView& g, int32_t v, int32_t
     }
   } else {
     constexpr int N = 4;
-    for (int32_t e0 = beg + sub; e0 < end; e0 += 2 * stride) {
-      int32_t u[2], q[2], z[2], x[2] = {0, 0};
+    int32_t e0 = beg + sub;
+    for (int32_t left = end - beg - sub; left > 0; left -= 2 * stride, e0 += 2 * stride) {
+      int32_t u[2], q[2], n[2], x[2] = {0, 0};
 #pragma unroll
-      for (int h = 0; h < 2; ++h) u[h] = e0 + h * stride < end ? gld<LD>(&g.ci[e0 + h * stride]) : -1;
+      for (int h = 0; h < 2; ++h) u[h] = h * stride < left ? gld<LD>(&g.ci[e0 + h * stride]) : -1;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         q[h] = u[h] >= 0 ? gld<LD>(&g.rp2[u[h]]) : 0;
-        z[h] = u[h] >= 0 ? gld<LD>(&g.rp2[u[h] + 1]) : 0;
+        n[h] = u[h] >= 0 ? gld<LD>(&g.rp2[u[h] + 1]) - q[h] : 0;
         if (MODE == kD2) x[h] = u[h] >= 0 ? get(u[h]) : 0;
       }
       bool stop = false;
       if (MODE == kD2) stop = use(x[0]) || stop, stop = use(x[1]) || stop;
-      while (!stop && (q[0] < z[0] || q[1] < z[1])) {
+      while (!stop && (n[0] > 0 || n[1] > 0)) {
         int32_t w[2 * N], y[2 * N];
 #pragma unroll
-        for (int j = 0; j < 2 * N; ++j) {
-          const int h = j / N;
-          const int32_t at = q[h] + j % N;
-          w[j] = at < z[h] ? gld<LD>(&g.ci2[at]) : v;
-        }
+        for (int j = 0; j < 2 * N; ++j) w[j] = j % N < n[j / N] ? gld<LD>(&g.ci2[q[j / N] + j % N]) : v;
 #pragma unroll
         for (int j = 0; j < 2 * N; ++j) y[j] = w[j] != v ? get(w[j]) : 0;
 #pragma unroll
         for (int j = 0; j < 2 * N; ++j) stop = use(y[j]) || stop;
-        q[0] += N;
-        q[1] += N;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          q[h] += N;
+          n[h] -= N;
+        }
       }
       if (stop) return;
     }

@@ -9,15 +9,17 @@
 
 namespace gcol {
 
-// Sum of 1 + (second-hop row length) over the first-hop entries beg, beg +
-// stride, ... below end, eight in flight.
-__device__ __forceinline__ int64_t hop_work(const GraphView& g, int32_t beg, int32_t end, int32_t stride) {
+// Sum of 1 + (second-hop row length) over the first-hop entries beg + sub, beg
+// + sub + stride, ... below end, eight in flight.  (The entries left are
+// counted: a position behind the last may not fit 32 bits.)
+__device__ __forceinline__ int64_t hop_work(const GraphView& g, int32_t beg, int32_t end, int32_t sub, int32_t stride) {
   constexpr int N = 8;
   int64_t w = 0;
-  for (int32_t q = beg; q < end; q += N * stride) {
+  int32_t q = beg + sub;
+  for (int32_t left = end - beg - sub; left > 0; left -= N * stride, q += N * stride) {
     int32_t u[N], a[N], z[N];
 #pragma unroll
-    for (int j = 0; j < N; ++j) u[j] = q + j * stride < end ? g.ci[q + j * stride] : -1;
+    for (int j = 0; j < N; ++j) u[j] = j * stride < left ? g.ci[q + j * stride] : -1;
 #pragma unroll
     for (int j = 0; j < N; ++j) {
       a[j] = u[j] >= 0 ? g.rp2[u[j]] : 0;
@@ -36,7 +38,7 @@ template <int MODE>
 __device__ __forceinline__ int64_t vertex_work(const GraphView& g, int32_t v) {
   const int32_t b = g.rp[v], e = g.rp[v + 1];
   if (MODE == kD1) return e - b;
-  return hop_work(g, b, e, 1);
+  return hop_work(g, b, e, 0, 1);
 }
 
 // Bookkeeping of one vertex once its work is known: work, bin, initial colors,
@@ -200,13 +202,13 @@ __global__ __launch_bounds__(kBlock) void bin_kernel(GraphView g, BinSetup s) {
       // walked up to kSetupHeavy entries: 1.06 ms on the 4M x 1M pattern)
       const int32_t q0 = active ? g.rp[v] : 0, q1 = active ? g.rp[v + 1] : 0;
       const bool wide = q1 - q0 > kThreadHop;
-      int64_t w = wide ? 0 : hop_work(g, q0, q1, 1);
+      int64_t w = wide ? 0 : hop_work(g, q0, q1, 0, 1);
       uint64_t bal = __ballot(wide);
       while (bal) {
         const int l = __builtin_ctzll(bal);
         bal &= bal - 1ull;
         const int32_t a = __builtin_amdgcn_readlane(q0, l), z = __builtin_amdgcn_readlane(q1, l);
-        int64_t x = hop_work(g, a + lane_id(), z, kWave);
+        int64_t x = hop_work(g, a, z, lane_id(), kWave);
 #pragma unroll
         for (int off = 1; off < kWave; off <<= 1) x += __shfl_xor(x, off, kWave);
         if (lane_id() == l) w = x;
@@ -236,7 +238,7 @@ __global__ __launch_bounds__(kBlock) void heavy_work_kernel(GraphView g, BinSetu
                               __attribute__((always_inline)) {
     if (threadIdx.x == 0) s_sum = 0ull;
     __syncthreads();
-    uint64_t w = static_cast<uint64_t>(hop_work(g, a + static_cast<int32_t>(threadIdx.x), z, kBlock));
+    uint64_t w = static_cast<uint64_t>(hop_work(g, a, z, static_cast<int32_t>(threadIdx.x), kBlock));
 #pragma unroll
     for (int off = 1; off < kWave; off <<= 1) w += __shfl_xor(w, off, kWave);
     if (lane_id() == 0 && w) atomicAdd(&s_sum, static_cast<unsigned long long>(w));
