@@ -81,26 +81,36 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def d1_kernel_bytes(st):
+def key_only_round(st, n, entries):
+    """(vertices, entries) of the pull engine's first round if it ran without
+    the color kernel (a call without initial colors): the detect kernel then
+    reads ids and keys only, no tentative colors."""
+    return (n, entries) if st.color_launches < st.detect_launches else (0, 0)
+
+
+def d1_kernel_bytes(st, n, nnz):
     """Algorithmic bytes of the pull engine's D1 color kernel and detect kernel
-    over a call.  Per worklist vertex: worklist id, two row offsets, the
-    static work value / T[v], and one 4-byte write (T[v], or C[v] / the next
-    worklist slot); per adjacency entry: the neighbour id and the neighbour's
-    color."""
-    color = 20 * st.vertex_visits + 8 * st.edge_visits
-    detect = 20 * st.vertex_visits + 8 * st.edge_visits
-    return color, detect
+    over a call on n vertices.  Per worklist vertex: worklist id, two row
+    offsets, the static work value / T[v], and one 4-byte write (T[v], or C[v]
+    / the next worklist slot); per adjacency entry: the neighbour id and the
+    neighbour's color."""
+    n1, e1 = key_only_round(st, n, nnz)
+    color = 20 * (st.vertex_visits - n1) + 8 * (st.edge_visits - e1)
+    return color, color + 16 * n1 + 4 * e1
 
 
-def pull_two_hop_bytes(st, avg_deg):
+def pull_two_hop_bytes(st, avg_deg, n, walk):
     """Pull engine, D2/PD2: per worklist vertex 20 bytes; per first-hop entry
     its id and the two row offsets of its hop-2 row (12 bytes); per hop-2
     entry its id and color (8 bytes).  edge_visits counts first-hop plus
-    hop-2 entries; the first-hop share is estimated as avg_deg per visit."""
-    e1 = min(st.edge_visits, int(st.vertex_visits * avg_deg))
-    e2 = st.edge_visits - e1
-    b = 20 * st.vertex_visits + 12 * e1 + 8 * e2
-    return b, b
+    hop-2 entries; the first-hop share is estimated as avg_deg per visit.
+    walk: the entries of all n vertices' two-hop walks."""
+    n1, w1 = key_only_round(st, n, walk)
+    v, e = st.vertex_visits - n1, st.edge_visits - w1
+    h = min(e, int(v * avg_deg))
+    color = 20 * v + 12 * h + 8 * (e - h)
+    h1 = min(w1, int(n1 * avg_deg))
+    return color, color + 16 * n1 + 12 * h1 + 4 * (w1 - h1)
 
 
 def make_d1_workload():
@@ -274,7 +284,7 @@ def bench_d1(args, torch, gc, dev):
                 cb, db = st.color_bytes, st.detect_bytes
             else:
                 names = ("color_round_kernel<D1>", "detect_round_kernel<D1>")
-                cb, db = d1_kernel_bytes(st)
+                cb, db = d1_kernel_bytes(st, g.n, g.nnz)
             for kname, byts, ns, nl in kernel_rows(gc, st, names, cb, db):
                 acc = kern.setdefault(kname, [0, 0, 0])
                 acc[0] += byts
@@ -383,6 +393,8 @@ def bench_d1(args, torch, gc, dev):
 def bench_d2pd2(args, torch, gc, dev):
     """D2 on the 7-point stencil 96^3 and PD2 on the 4,000,000 x 1,000,000
     power-law pattern (8 columns per row, tail exponent 2.1), one step = both."""
+    import numpy as np
+
     import graphgen as gg
     t = time.time()
     g = gg.stencil((96, 96, 96), 7)
@@ -417,13 +429,15 @@ def bench_d2pd2(args, torch, gc, dev):
     tm = sum(times) / len(times)
     kern, graphs = {}, {}
     for s1, s2 in stats:
-        for name, st, nnz, deg, mode in (("stencil7_96_d2", s1, g.nnz, g.nnz / g.n, "D2"),
-                                         ("pd2_4m_1m", s2, b.nnz, b.nnz / b.n_cols, "PD2")):
+        for name, st, nnz, n, mode, hop2 in (("stencil7_96_d2", s1, g.nnz, g.n, "D2", g.row_ptr),
+                                             ("pd2_4m_1m", s2, b.nnz, b.n_cols, "PD2", b.row_ptr)):
             if st.engine == gc.ENGINE_INCREMENTAL:
                 names, (cb, db) = ("inc_color_kernel", "inc_detect_kernel"), (st.color_bytes, st.detect_bytes)
             else:
                 names = (f"color_round_kernel<{mode}>", f"detect_round_kernel<{mode}>")
-                cb, db = pull_two_hop_bytes(st, deg)
+                # every first-hop entry u is walked 1 + (length of row u) entries far
+                rows = np.diff(hop2).astype(np.int64)
+                cb, db = pull_two_hop_bytes(st, nnz / n, n, int((rows * (rows + 1)).sum()))
             for kname, byts, ns, nl in kernel_rows(gc, st, names, cb, db):
                 acc = kern.setdefault(kname, [0, 0, 0])
                 acc[0] += byts
@@ -741,7 +755,9 @@ def bench_ghost(args, torch, gc, dev):
         if layers == 1:
             names = ("inc_color_kernel", "inc_detect_kernel") if st.engine == gc.ENGINE_INCREMENTAL else \
                 ("color_round_kernel<D1>", "detect_round_kernel<D1>")
-            cb, db = (st.color_bytes, st.detect_bytes) if st.engine == gc.ENGINE_INCREMENTAL else d1_kernel_bytes(st)
+            inner = int(np.count_nonzero(lg.col[:owned_nnz] < lg.n_owned))  # phase 1 has the owned entries only
+            cb, db = (st.color_bytes, st.detect_bytes) if st.engine == gc.ENGINE_INCREMENTAL else \
+                d1_kernel_bytes(st, lg.n_owned, inner)
             for kname, byts, ns, nl in kernel_rows(gc, st, names, cb, db):
                 kern[kname] = (byts, ns, nl)
         grp = gc.Params(flags=gc.COLOR_FLAG_GHOST_RECOLOR)

@@ -120,7 +120,9 @@ typedef struct color_stats {
     int32_t trace_cap;           /* in: capacity of worklist_trace */
     int32_t kernel_launches;     /* kernels the call enqueued */
     /* COLOR_FLAG_KERNEL_TIMING only (else 0): summed HIP-event durations of
-       the color and the detect round kernels, and their launch counts */
+       the color and the detect round kernels, and their launch counts (PULL
+       without initial colors: round 1 has no color launch, as every first
+       fit is color 1) */
     int64_t color_kernel_ns;
     int64_t detect_kernel_ns;
     int32_t color_launches;

@@ -302,7 +302,6 @@ int run_phase(Call& c, const GraphView& g, const KeySource& k, const BinLayout& 
         launch_first_round<MODE>(g, k, b, L, round0 + local, grid, static_cast<int32_t>(total), c.st);
         if (c.timing && c.record_event(-1)) return COLOR_EHIP;
         c.launches += 2;
-        c.color_launches += 1;
         c.detect_launches += 1;
         continue;
       }
