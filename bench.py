@@ -178,6 +178,23 @@ def stream_copy(torch, dev, reps=5):
             "frac_of_peak": round(gbs / HBM_PEAK_GBS, 4)}
 
 
+# The cooperative rounds of one call (stats.tail_kernel_ns): the tail kernel
+# and the core kernels, which end in one core_kernel launch.
+TAIL_ROUNDS = "tail and core kernels"
+TAIL_PREFIXES = ("inc_tail_kernel", "core_rank_kernel", "core_build_kernel", "core_wide_kernel", "core_kernel")
+
+
+def summary_names(kernel, names):
+    """Of the names of a counter summary, those that the timed row `kernel`
+    stands for: the kernel itself, every variant of a kernel of several
+    template arguments (detect_round_kernel<D1> is <1, false> and <1, true>),
+    or the kernels of the cooperative rounds."""
+    if kernel == TAIL_ROUNDS:
+        return [k for k in names if k.startswith(TAIL_PREFIXES)]
+    mode = kernel.replace("<D1>", "<1,").replace("<D2>", "<2,").replace("<PD2>", "<3,")
+    return [k for k in names if k == kernel or (mode != kernel and k.startswith(mode))]
+
+
 def load_traffic(kernel, workload):
     """HBM bytes per launch of `kernel` from the committed counter summary of
     the same workload, if it was taken on the current library sources."""
@@ -187,8 +204,17 @@ def load_traffic(kernel, workload):
             t = json.load(f)
         if t.get("source_hash") != source_hash() or t.get("workload") != workload:
             return None
-        k = t["kernels"].get(kernel)
-        return None if k is None else int(k["hbm_bytes_per_launch"])
+        found = {k: t["kernels"][k] for k in summary_names(kernel, t["kernels"])}
+        if not found:
+            return None
+        if len(found) == 1:
+            return int(next(iter(found.values()))["hbm_bytes_per_launch"])
+        total = sum(k["hbm_bytes_per_launch"] * k["dispatches"] for k in found.values())
+        if kernel == TAIL_ROUNDS:  # a "launch" is the rounds of one call
+            launches = max(found[k]["dispatches"] for k in found if k.startswith(("core_kernel", "inc_tail_kernel")))
+        else:
+            launches = sum(k["dispatches"] for k in found.values())
+        return int(total / launches)
     except (OSError, ValueError, KeyError):
         return None
 
@@ -227,12 +253,13 @@ def copy_calibration(torch, dev):
 
 def kernel_rows(gc, st, names, color_bytes, detect_bytes):
     """(kernel, algorithmic bytes, HIP-event ns, launches) of one call's round
-    kernels; the incremental engine's cooperative tail kernel (all rounds once
-    the worklist is small, in one launch) is a kernel of its own."""
+    kernels; the incremental engine's cooperative rounds (the tail kernel and
+    the core kernels, once the worklist is small) are a row of their own, one
+    "launch" per call."""
     rows = [(names[0], color_bytes, st.color_kernel_ns, st.color_launches),
             (names[1], detect_bytes, st.detect_kernel_ns, st.detect_launches)]
     if st.tail_rounds:
-        rows.append(("inc_tail_kernel", st.tail_bytes, st.tail_kernel_ns, 1))
+        rows.append((TAIL_ROUNDS, st.tail_bytes, st.tail_kernel_ns, 1))
     return rows
 
 
