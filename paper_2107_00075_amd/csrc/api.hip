@@ -783,7 +783,10 @@ int run_incremental(Call& c, const GraphView& g, const KeySource& k, const int32
   // worklists of at most core_at vertices go to the core kernels
   const int64_t core_at = std::min<int64_t>(
       tail_at, core_capacity(std::min(core_blocks_resident(), std::max(8, c.P.max_workgroups))));
-  bool core_on = tail_on && core_at > 0;
+  // (a fixed workspace that has no room for their scratch: the tail kernel then
+  // runs all the rounds, in one launch)
+  const bool core_room = !w->inc_core.fixed || w->inc_core.bytes >= core_scratch_bytes(static_cast<int32_t>(core_at));
+  bool core_on = tail_on && core_at > 0 && core_room;
   int local = 0;
   int R = std::max(1, c.P.rounds_per_poll);
   int64_t prev_total = 0;
@@ -1090,7 +1093,9 @@ int color_pd2_fixed(Workspace* ws, int32_t n_rows, int32_t n_cols, const int32_t
 // Buffer sizes of one D2/PD2 call on the incremental engine, computed on the
 // host from the graph the way the engine sizes them on the device (list
 // lengths from the hop-1 and hop-2 rows, bitset words, worklists, list-
-// building bitmaps, scan storage), with no trace and no degree key.
+// building bitmaps, scan storage), with no trace and no degree key.  There is
+// no region for the core kernels' scratch: the planned calls run every round
+// as its own launches.
 size_t plan_incremental(int kind, int32_t n, const int32_t* rp1, const int32_t* ci1, const int32_t* rp2,
                         IncPlan* p) {
   std::memset(p, 0, sizeof(*p));
@@ -1108,7 +1113,9 @@ size_t plan_incremental(int kind, int32_t n, const int32_t* rp1, const int32_t* 
   }
   const size_t entries = static_cast<size_t>(std::max<int64_t>(1, std::min<int64_t>(total, INT_MAX)));
   const size_t words = static_cast<size_t>(n) / 32 + 1;
-  const size_t bm = sizeof(uint32_t) * words * static_cast<size_t>(dedup_grid(static_cast<int32_t>(words)));
+  size_t bm = 0;
+  if (dedup_in_memory(static_cast<int32_t>(words)))
+    bm = sizeof(uint32_t) * words * static_cast<size_t>(dedup_grid(static_cast<int32_t>(words)));
   size_t sets = 0;
   if (nd > 0 && nd * static_cast<int64_t>(words) <= kSetsMaxWords)
     sets = sizeof(uint32_t) * words *
@@ -1123,7 +1130,7 @@ size_t plan_incremental(int kind, int32_t n, const int32_t* rp1, const int32_t* 
   p->inc_len = p->inc_words = p->inc_fwoff = p->inc_aoff = p->inc_L0 = p->inc_Ll = 4 * n1;
   p->inc_F = 4 * static_cast<size_t>(std::max<int64_t>(fw, 1));
   p->inc_B0 = p->inc_B1 = 4 * entries;
-  p->inc_bm = std::max(bm, sets);
+  p->inc_bm = std::max<size_t>(std::max(bm, sets), 1);
   p->inc_wl0 = p->inc_wl1 = 4 * 4 * nn;  // bin regions: at most 4n entries
   p->inc_T8 = (nn + 3) / 4 * 4;  // as run_incremental sizes it
   p->inc_done = 4 * (nn / 32 + 1);
