@@ -371,13 +371,6 @@ __device__ __forceinline__ int32_t wave_reduce(int32_t x, int32_t none, F&& f) {
   return __builtin_amdgcn_readlane(x, kWave - 1);
 }
 
-// Orders a wavefront's accesses to LDS before this point and after it, where
-// lanes take over words from each other.
-__device__ __forceinline__ void wave_step() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // The slots of colors lo .. hi (hi - lo < kCoreSlots).
 __device__ __forceinline__ uint32_t core_slots(int32_t lo, int32_t hi) {
   if (lo > hi) return 0u;

@@ -179,6 +179,13 @@ __device__ __forceinline__ unsigned long long* acc_slot(unsigned long long* acc)
   return acc + kAccStride * (blockIdx.x % kAccSlots);
 }
 
+// Orders a wavefront's accesses to LDS before this point and after it, where
+// lanes take over words from each other.
+__device__ __forceinline__ void wave_step() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Waits until the caller's accesses to memory have completed.  Mutable state
 // that only device-scope accesses (performed beyond the L2s) touch is handed
 // over by this and a flag; __threadfence also writes the L2 back and

@@ -444,6 +444,7 @@ __device__ __forceinline__ void inc_detect_chunk(const KeySource& k, const IncBu
     const int32_t idx = s_pend[i];
     const int8_t state = s_tb[idx];
     const int32_t v = s_ent[idx];
+    wave_step();  // (one lane of the group replaces them below)
     const int32_t tv = ld_mut<MUT>(&b.T[v]);
     const uint64_t kv = key_of(k, v);
     const int32_t base = ld_mut<MUT>(&b.aoff[v]);

@@ -7,8 +7,12 @@
 // run one after another in an order drawn from emu::seed, so that an access
 // that needs a barrier which is not there shows in some order; a lane that
 // sleeps in a polling loop lets the other wavefronts go on.  The
-// workgroups of a cooperative launch run side by side, those of an ordinary
-// one after another.  Arithmetic wraps (built with -fwrapv).
+// workgroups of a cooperative launch, and of any small one, run side by side,
+// else one after another.  Arithmetic wraps (built with -fwrapv).
+//
+// Host calls work on the one memory there is.  Without emu::start_queues
+// everything runs inside the call; with it, streams are spread over so many
+// threads (the hardware queues), each in order.
 #pragma once
 
 #include <stdint.h>
@@ -16,6 +20,9 @@
 
 #include <algorithm>
 #include <chrono>
+#include <condition_variable>
+#include <deque>
+#include <mutex>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -38,13 +45,18 @@ struct dim3 {
   unsigned x, y, z;
   dim3(unsigned a = 1, unsigned b = 1, unsigned c = 1) : x(a), y(b), z(c) {}
 };
-using hipStream_t = void*;
+using hipStream_t = struct EmuStream*;
+using hipEvent_t = struct EmuEvent*;
 using hipError_t = int;
-constexpr hipError_t hipSuccess = 0, hipErrorUnknown = 999;
+constexpr hipError_t hipSuccess = 0, hipErrorNotReady = 600, hipErrorUnknown = 999;
 enum hipDeviceAttribute_t { hipDeviceAttributeMultiprocessorCount, hipDeviceAttributeWallClockRate };
+namespace emu {
+inline int cus = 256;
+}
 inline hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
+inline hipError_t hipSetDevice(int) { return hipSuccess; }
 inline hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
-  return *v = a == hipDeviceAttributeMultiprocessorCount ? 256 : 100000, hipSuccess;
+  return *v = a == hipDeviceAttributeMultiprocessorCount ? emu::cus : 100000, hipSuccess;
 }
 template <typename F>
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, F, int, size_t) {
@@ -93,7 +105,8 @@ enum State { kRun, kWaveOp, kBarrier, kSpin, kDone };
 struct Fiber {
   void* sp = nullptr;
   State state = kRun;
-  int site = 0;  // source line of the wavefront operation it waits in
+  int line = 0;                // source line and
+  const char* site = nullptr;  // call site of the wavefront operation it waits in
   uint64_t value = 0;
 };
 
@@ -131,11 +144,12 @@ inline void entry() {
 
 // Posts x with the wavefront's other active lanes; afterwards snap and mask
 // hold what all of them posted.
-inline void post(uint64_t x, int line) {
+__attribute__((noinline)) inline void post(uint64_t x, int line) {
   Group& g = *g_group;
   Fiber& f = g.fibers[g.cur];
   f.value = x;
-  f.site = line;
+  f.line = line;
+  f.site = static_cast<const char*>(__builtin_return_address(0));
   yield_to_main(kWaveOp);
 }
 
@@ -155,13 +169,18 @@ inline void run_wave(Group& g, int first, int last) {
       spin = g.spinning = true;
     }
     if (spin) return;
-    g.mask = 0;
-    int site = 0;
+    // Lanes that have left a loop or a branch wait for the others where these
+    // join them, further on in the code: the operation at the lowest address
+    // comes first (built without reordering of blocks).
+    const Fiber* at = nullptr;
     for (int i = first; i < last; ++i) {
+      const Fiber& f = g.fibers[i];
+      if (f.state == kWaveOp && (!at || f.site < at->site)) at = &f;
+    }
+    g.mask = 0;
+    for (int i = first; at && i < last; ++i) {
       Fiber& f = g.fibers[i];
-      if (f.state != kWaveOp) continue;
-      if (site && f.site != site) fail("lanes of a wavefront wait in different operations");
-      site = f.site;
+      if (f.state != kWaveOp || f.line != at->line) continue;
       g.mask |= 1ull << (i - first);
       g.snap[i - first] = f.value;
       f.state = kRun;
@@ -170,13 +189,34 @@ inline void run_wave(Group& g, int first, int last) {
   }
 }
 
+// The stacks of a host thread's workgroup, kept for its next one.
+struct Stacks {
+  char* p = nullptr;
+  int n = 0;
+  char* of(int want) {
+    if (want > n) {
+      drop();
+      p = static_cast<char*>(mmap(nullptr, kStack * want, PROT_READ | PROT_WRITE,
+                                  MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0));
+      if (p == MAP_FAILED) fail("no memory for stacks");
+      n = want;
+    }
+    return p;
+  }
+  void drop() {
+    if (p) munmap(p, kStack * n);
+    p = nullptr;
+    n = 0;
+  }
+  ~Stacks() { drop(); }
+};
+inline thread_local Stacks t_stacks;
+
 inline void run_group(dim3 grid, dim3 block, unsigned index, const std::function<void()>& body) {
   Group g;
   const int n = static_cast<int>(block.x);
   g.fibers.resize(n);
-  g.stacks = static_cast<char*>(mmap(nullptr, kStack * n, PROT_READ | PROT_WRITE,
-                                     MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0));
-  if (g.stacks == MAP_FAILED) fail("no memory for stacks");
+  g.stacks = t_stacks.of(n);
   g.body = &body;
   g_group = &g;
   gridDim = grid;
@@ -214,13 +254,12 @@ inline void run_group(dim3 grid, dim3 block, unsigned index, const std::function
     g.barrier_or = 0;
     if (!live) break;
   }
-  munmap(g.stacks, kStack * n);
   g_group = nullptr;
 }
 
 inline void launch(dim3 grid, dim3 block, const std::function<void()>& body, bool together = false) {
   const unsigned blocks = grid.x * grid.y;
-  if (!together) {
+  if (!together && (blocks == 1 || blocks > 16)) {
     for (unsigned i = 0; i < blocks; ++i) run_group(grid, block, i, body);
     return;
   }
@@ -242,6 +281,74 @@ void call(void (*f)(A...), void** a, std::index_sequence<I...>) {
 template <typename... A>
 void add_kernel(void (*f)(A...)) {
   kernels()[reinterpret_cast<const void*>(f)] = [f](void** a) { call(f, a, std::index_sequence_for<A...>()); };
+}
+
+// A hardware queue: work in order, on a thread of its own.
+class Queue {
+ public:
+  Queue() : thread_([this] { run(); }) {}
+  ~Queue() {
+    push(nullptr);
+    thread_.join();
+  }
+  uint64_t push(std::function<void()> f) {
+    std::lock_guard<std::mutex> lk(mu_);
+    work_.push_back(std::move(f));
+    cv_.notify_all();
+    return ++submitted_;
+  }
+  bool done(uint64_t ticket) {
+    std::lock_guard<std::mutex> lk(mu_);
+    return done_ >= ticket;
+  }
+  void wait(uint64_t ticket) {
+    std::unique_lock<std::mutex> lk(mu_);
+    cv_.wait(lk, [&] { return done_ >= ticket; });
+  }
+  uint64_t last() {
+    std::lock_guard<std::mutex> lk(mu_);
+    return submitted_;
+  }
+
+ private:
+  void run() {
+    while (true) {
+      std::function<void()> f;
+      {
+        std::unique_lock<std::mutex> lk(mu_);
+        cv_.wait(lk, [&] { return !work_.empty(); });
+        f = std::move(work_.front());
+        work_.pop_front();
+      }
+      if (!f) return;
+      f();
+      std::lock_guard<std::mutex> lk(mu_);
+      ++done_;
+      cv_.notify_all();
+    }
+  }
+  std::mutex mu_;
+  std::condition_variable cv_;
+  std::deque<std::function<void()>> work_;
+  uint64_t submitted_ = 0, done_ = 0;
+  std::thread thread_;
+};
+inline std::vector<Queue*> queues;
+inline std::mutex host_mu;
+inline std::map<const char*, size_t> pinned_size;  // pinned host allocations
+inline int next_queue = 0;
+
+inline void start_queues(int n) {
+  for (int i = 0; i < n; ++i) queues.push_back(new Queue());
+}
+inline void stop_queues() {
+  for (Queue* q : queues) delete q;
+  queues.clear();
+}
+inline bool is_pinned(const void* p) {
+  std::lock_guard<std::mutex> lk(host_mu);
+  auto it = pinned_size.upper_bound(static_cast<const char*>(p));
+  return it != pinned_size.begin() && static_cast<const char*>(p) < (--it)->first + it->second;
 }
 
 template <typename T>
@@ -267,6 +374,98 @@ T of_lane(int l, T own) {
 
 }  // namespace emu
 
+struct EmuStream {
+  emu::Queue* q;
+};
+struct EmuEvent {
+  emu::Queue* q = nullptr;
+  uint64_t ticket = 0;
+};
+namespace emu {
+inline Queue* queue_of(hipStream_t s) { return s ? s->q : queues.empty() ? nullptr : queues[0]; }
+inline void enqueue(hipStream_t s, std::function<void()> f) {
+  if (Queue* q = queue_of(s)) q->push(std::move(f));
+  else f();
+}
+template <typename... P, typename... A>
+void enqueue_kernel(void (*k)(P...), dim3 grid, dim3 block, hipStream_t s, A... a) {
+  enqueue(s, [=] { launch(grid, block, [&] { k(a...); }); });
+}
+inline void sync_all() {
+  for (Queue* q : queues) q->wait(q->last());
+}
+}  // namespace emu
+
+enum hipMemcpyKind { hipMemcpyHostToDevice, hipMemcpyDeviceToHost, hipMemcpyDeviceToDevice };
+constexpr unsigned hipStreamNonBlocking = 1, hipEventDisableTiming = 2, hipHostMallocDefault = 0;
+inline hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+  *s = new EmuStream{emu::queues.empty() ? nullptr : emu::queues[emu::next_queue++ % emu::queues.size()]};
+  return hipSuccess;
+}
+inline hipError_t hipStreamSynchronize(hipStream_t s) {
+  if (emu::Queue* q = emu::queue_of(s)) q->wait(q->last());
+  return hipSuccess;
+}
+inline hipError_t hipStreamDestroy(hipStream_t s) {
+  (void)hipStreamSynchronize(s);
+  delete s;
+  return hipSuccess;
+}
+inline hipError_t hipEventCreate(hipEvent_t* e) { return *e = new EmuEvent(), hipSuccess; }
+inline hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+inline hipError_t hipEventDestroy(hipEvent_t e) { return delete e, hipSuccess; }
+inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+  e->q = emu::queue_of(s);
+  if (e->q) e->ticket = e->q->push([] {});
+  return hipSuccess;
+}
+inline hipError_t hipEventQuery(hipEvent_t e) { return !e->q || e->q->done(e->ticket) ? hipSuccess : hipErrorNotReady; }
+inline hipError_t hipEventSynchronize(hipEvent_t e) {
+  if (e->q) e->q->wait(e->ticket);
+  return hipSuccess;
+}
+inline hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms = 0, hipSuccess; }
+template <typename T>
+hipError_t hipMalloc(T** p, size_t n) {
+  return *p = static_cast<T*>(std::malloc(n)), *p ? hipSuccess : hipErrorUnknown;
+}
+inline hipError_t hipFree(void* p) {
+  emu::sync_all();
+  std::free(p);
+  return hipSuccess;
+}
+template <typename T>
+hipError_t hipHostMalloc(T** p, size_t n, unsigned = 0) {
+  *p = static_cast<T*>(std::malloc(n));
+  std::lock_guard<std::mutex> lk(emu::host_mu);
+  emu::pinned_size[reinterpret_cast<const char*>(*p)] = n;
+  return hipSuccess;
+}
+inline hipError_t hipHostFree(void* p) {
+  emu::sync_all();
+  {
+    std::lock_guard<std::mutex> lk(emu::host_mu);
+    emu::pinned_size.erase(static_cast<const char*>(p));
+  }
+  std::free(p);
+  return hipSuccess;
+}
+// (a copy from or to pageable host memory is done when the call returns)
+inline hipError_t hipMemcpyAsync(void* to, const void* from, size_t n, hipMemcpyKind kind, hipStream_t s) {
+  emu::enqueue(s, [=] { std::memcpy(to, from, n); });
+  const void* host = kind == hipMemcpyHostToDevice ? from : to;
+  if (kind != hipMemcpyDeviceToDevice && !emu::is_pinned(host)) return hipStreamSynchronize(s);
+  return hipSuccess;
+}
+inline hipError_t hipMemcpy(void* to, const void* from, size_t n, hipMemcpyKind kind) {
+  (void)hipMemcpyAsync(to, from, n, kind, nullptr);
+  return hipStreamSynchronize(nullptr);
+}
+inline hipError_t hipMemsetAsync(void* p, int x, size_t n, hipStream_t s) {
+  emu::enqueue(s, [=] { std::memset(p, x, n); });
+  return hipSuccess;
+}
+
 inline hipError_t hipLaunchCooperativeKernel(const void* f, dim3 grid, dim3 block, void** args, size_t, hipStream_t) {
   auto it = emu::kernels().find(f);
   if (it == emu::kernels().end()) return hipErrorUnknown;
@@ -274,8 +473,9 @@ inline hipError_t hipLaunchCooperativeKernel(const void* f, dim3 grid, dim3 bloc
   return hipSuccess;
 }
 #define hipLaunchKernelGGL(kernel, grid, block, shared, stream, ...) \
-  emu::launch(grid, block, [&] { (kernel)(__VA_ARGS__); })
+  emu::enqueue_kernel(kernel, grid, block, stream, __VA_ARGS__)
 
+#define EMU_OP inline __attribute__((always_inline))
 #define EMU_LINE int line = __builtin_LINE()
 inline int __lane_id() { return emu::lane(); }
 inline void __syncthreads() { emu::yield_to_main(emu::kBarrier); }
@@ -284,7 +484,7 @@ inline int __syncthreads_or(int x) {
   emu::yield_to_main(emu::kBarrier);
   return emu::g_group->barrier_result;
 }
-inline uint64_t __ballot(int p, EMU_LINE) {
+EMU_OP uint64_t __ballot(int p, EMU_LINE) {
   emu::post(p ? 1u : 0u, line);
   uint64_t m = 0;
   for (int l = 0; l < emu::kLanes; ++l)
@@ -292,31 +492,31 @@ inline uint64_t __ballot(int p, EMU_LINE) {
   return m;
 }
 template <typename T>
-T __shfl(T x, int src, int width = 64, EMU_LINE) {
+EMU_OP T __shfl(T x, int src, int width = 64, EMU_LINE) {
   emu::post(emu::bits(x), line);
   return emu::of_lane((emu::lane() & ~(width - 1)) + (src & (width - 1)), x);
 }
 template <typename T>
-T __shfl_xor(T x, int m, int = 64, EMU_LINE) {
+EMU_OP T __shfl_xor(T x, int m, int = 64, EMU_LINE) {
   emu::post(emu::bits(x), line);
   return emu::of_lane(emu::lane() ^ m, x);
 }
 template <typename T>
-T __shfl_up(T x, int d, int width = 64, EMU_LINE) {
+EMU_OP T __shfl_up(T x, int d, int width = 64, EMU_LINE) {
   emu::post(emu::bits(x), line);
   const int l = emu::lane();
   return (l & (width - 1)) >= d ? emu::of_lane(l - d, x) : x;
 }
-inline int emu_readlane(int x, int l, EMU_LINE) {
+EMU_OP int emu_readlane(int x, int l, EMU_LINE) {
   emu::post(emu::bits(x), line);
   if (!(emu::g_group->mask >> l & 1u)) emu::fail("readlane of an inactive lane");
   return emu::from_bits<int>(emu::g_group->snap[l]);
 }
-inline int emu_readfirstlane(int x, EMU_LINE) {
+EMU_OP int emu_readfirstlane(int x, EMU_LINE) {
   emu::post(emu::bits(x), line);
   return emu::from_bits<int>(emu::g_group->snap[__builtin_ctzll(emu::g_group->mask)]);
 }
-inline int emu_dpp(int old, int x, int ctrl, int row_mask, bool zero, EMU_LINE) {
+EMU_OP int emu_dpp(int old, int x, int ctrl, int row_mask, bool zero, EMU_LINE) {
   emu::post(emu::bits(x), line);
   const int l = emu::lane(), row = l / 16;
   if (!(row_mask >> row & 1)) return old;

@@ -1,9 +1,11 @@
-"""Builds a driver of tests/emu (a kernel source compiled with g++ against the
-host emulation of the device operations) and loads it with ctypes."""
+"""Builds the drivers of tests/emu (the library's sources compiled with g++
+against the host emulation of the device operations) and loads them with
+ctypes."""
 import ctypes
 import os
 import subprocess
 import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 import numpy as np
 
@@ -11,14 +13,34 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 _dir = tempfile.TemporaryDirectory(prefix="emu_")
 
 
+EMU = os.path.join(ROOT, "tests", "emu")
+CSRC = os.path.join(ROOT, "paper_2107_00075_amd", "csrc")
+FLAGS = ["-std=c++17", "-fwrapv", "-fPIC", "-fno-reorder-blocks", "-pthread", "-w", "-I", EMU, "-I", CSRC,
+         "-I", os.path.join(ROOT, "include")]
+
+
 def load(driver: str) -> ctypes.CDLL:
     so = os.path.join(_dir.name, driver + ".so")
     if not os.path.exists(so):
-        emu = os.path.join(ROOT, "tests", "emu")
-        subprocess.check_call(
-            ["g++", "-std=c++17", "-O2", "-fwrapv", "-fPIC", "-shared", "-pthread", "-w", "-x", "c++",
-             os.path.join(emu, driver + ".cpp"), "-I", emu, "-I", os.path.join(ROOT, "paper_2107_00075_amd", "csrc"),
-             "-I", os.path.join(ROOT, "include"), "-o", so])
+        subprocess.check_call(["g++", *FLAGS, "-O1", "-shared", "-x", "c++", os.path.join(EMU, driver + ".cpp"), "-o", so])
+    return ctypes.CDLL(so)
+
+
+def load_library() -> ctypes.CDLL:
+    """The library's sources as one shared object on host memory."""
+    so = os.path.join(_dir.name, "library.so")
+    if not os.path.exists(so):
+        srcs = [os.path.join(CSRC, s) for s in ("rounds.hip", "setup.hip", "keys.hip", "api.hip", "batch.hip", "server.cpp")]
+        srcs += [os.path.join(EMU, s) for s in ("library_host.cpp", "library_core.cpp", "library_inc.cpp")]
+
+        def compile_one(src):
+            obj = os.path.join(_dir.name, os.path.basename(src) + ".o")
+            subprocess.check_call(["g++", *FLAGS, "-O1", "-x", "c++", "-c", src, "-o", obj])
+            return obj
+
+        with ThreadPoolExecutor(4) as ex:
+            objs = list(ex.map(compile_one, srcs))
+        subprocess.check_call(["g++", "-shared", "-pthread", *objs, "-o", so])
     return ctypes.CDLL(so)
 
 
