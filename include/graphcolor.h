@@ -31,7 +31,9 @@
  * enqueued on `stream` has finished.  Each call runs on a workspace that no
  * other call holds at the same time, taken from a per-device pool (up to 8
  * workspaces per device, each growing to the largest call it served, kept
- * until color_release_workspace; a 9th concurrent call waits for one), so
+ * until color_release_workspace; a 9th concurrent call waits for one; one that
+ * served an incremental call may hold up to 98 MB of the core kernels' scratch
+ * beside the memory per vertex and entry), so
  * calls made at the same time from different host threads on different
  * streams are independent: they neither wait for nor share memory with each
  * other.  Only color_d1_noalloc (one static array per device) serializes
@@ -151,14 +153,15 @@ typedef struct color_params {
                                no run reaches: each round commits at least one vertex) */
     int32_t rounds_per_poll;/* rounds enqueued between host checks of the worklist size */
     int32_t tail_threshold; /* INCREMENTAL: worklist size at or below which cooperative launches
-                               run all remaining rounds (the tail kernel, grid barriers between
-                               the steps; from 24576 vertices on the core kernels, on rows of
-                               adjacency bits; default 32768).  Its workgroups wait on each other, so they
-                               must all be resident: before writing anything they check in
-                               and wait up to tail_checkin_us for each other; if they are not
-                               all resident by then (other streams keep the device full), the
-                               launch does nothing and the rounds continue as per-round
-                               launches (stats->tail_fallbacks counts this).  The same happens
+                               run all remaining rounds (default 32768): the tail kernel, with
+                               grid barriers between the steps, and once at most 24576 vertices
+                               are left the core kernels, on rows of adjacency bits.  Their
+                               workgroups wait on each other, so they must all be resident:
+                               before writing anything they check in and wait up to
+                               tail_checkin_us for each other; if they are not all resident by
+                               then (other streams keep the device full), the launch does
+                               nothing and the rounds continue as per-round launches
+                               (stats->tail_fallbacks counts this).  The same happens
                                if the runtime refuses the cooperative launch.  A grid barrier
                                that still stalls for 30 s makes the call start over with
                                per-round launches only (COLOR_FLAG_NO_TAIL), which gives the

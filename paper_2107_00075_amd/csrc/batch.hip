@@ -17,6 +17,25 @@
 // [grabbed, min(grabbed + k, units)) are then owned by the caller, and while
 // any of them is outstanding the phase cannot close, so the word's epoch and
 // the job's counts stay put.  An add that finds grabbed >= units owns nothing.
+//
+// Hand-overs: a job's mutable state (its record, C, T, work and worklists) is
+// read and written inside a launch by device-scope loads, stores and atomics
+// only (ld_dev, ld_mut<1>, st_dev).  These act beyond the XCDs' L2s, so no L2
+// holds a line of it to write back or to invalidate, and a hand-over needs no
+// more than that the giver's accesses have completed (wait_own_accesses)
+// before the taker's begin:
+//  * units -> closer: every wavefront waits for its accesses, the workgroup
+//    meets at its barrier, then thread 0 adds to `done` once its own are
+//    complete.  The add that brings `done` to the unit count comes after all
+//    of them, and the closer reads the counts after it.
+//  * closer -> takers: the closer waits for its stores and then stores the
+//    word.  A taker's first access to the job depends on its add on the word
+//    having returned the new epoch.
+//  * launch -> launch (parking, unpark_kernel, copies of records and words):
+//    the end of a launch.
+// What no launch writes is read plainly: the graph with LD = 0.  Where copies
+// rewrite it between launches (the served form's arena; job records and the
+// tuning table everywhere) the reads are device-scope too.
 #include <algorithm>
 #include <chrono>
 #include <climits>
@@ -115,8 +134,6 @@ __device__ __forceinline__ uint32_t phase_units(const int32_t cnt[kBatchBins], c
   return u + static_cast<uint32_t>(cnt[3]);
 }
 
-// Every access to a job's mutable state is device-scope, so handing it over
-// takes wait_own_accesses only.  A workgroup's: before its barrier.
 template <int MODE, int LD>
 __device__ __forceinline__ int64_t job_vertex_work(const GraphView& g, int32_t v) {
   const int32_t b = gld<LD>(&g.rp[v]), e = gld<LD>(&g.rp[v + 1]);
@@ -472,7 +489,7 @@ __global__ void unpark_kernel(BatchJob* jobs, uint64_t* words, int32_t num_jobs,
   st_dev(&J->stop_epoch, static_cast<int32_t>(min(static_cast<int64_t>(e) + budget, int64_t{0xFFFF})));
   st_dev(&J->status, static_cast<int32_t>(kJobRunning));
   atomic_reset_u32(&J->done);
-  __threadfence();
+  // (the end of this launch hands all of it over)
   store_word(&words[j], phase_word(static_cast<uint32_t>(e), static_cast<uint32_t>(ld_dev(&J->parked_units)), 0));
 }
 

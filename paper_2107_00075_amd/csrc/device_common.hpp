@@ -39,13 +39,11 @@ inline uint32_t host_fmix32(uint32_t h) {
 
 inline uint32_t hash_seed(uint32_t seed) { return host_fmix32(seed ^ 0x9E3779B9u); }
 
-// Device-coherent accesses.  Arrays that the library's kernels write and
-// later kernels read (colors, tentative colors, worklists, per-call setup
-// arrays) are written and read with device-scope (sc1) loads and stores.
-// Measured on MI355X: plain loads of such data written by an earlier kernel on
-// another XCD could return stale values (agent- or system-scope fences issued
-// by every wavefront at kernel start and end did not prevent it), while
-// device-scope accesses gave bit-exact results in every run.
+// Device-scope (sc1) accesses, performed beyond the XCDs' L2s.  Needed for
+// what one workgroup writes and another reads inside one launch: the tail, core
+// and batched kernels' hand-overs, counters and flags.  Across launches of a
+// stream plain loads see what earlier launches wrote (ld_mut, below), and the
+// setup kernels' device-scope accesses there are not needed for that.
 template <typename X>
 __device__ __forceinline__ X ld_dev(const X* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -56,7 +54,7 @@ __device__ __forceinline__ void st_dev(X* p, X v) {
 }
 
 // Loads of a round kernel's bulk arrays (worklists, lists, offsets, colors,
-// bitsets).  The per-round kernels read them with plain, L2-cacheable loads
+// bitsets).  The per-round kernels of both engines read them with plain, L2-cacheable loads
 // (MUT = 0): the data was written by earlier launches, whose writes every
 // later launch on the stream sees (measured on MI355X: 3.8e9 reads of lines
 // that another XCD rewrote in the previous launch, none stale), or it is

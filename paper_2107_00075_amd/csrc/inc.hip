@@ -1011,7 +1011,7 @@ __global__ __launch_bounds__(kBlock, 4) void inc_detect_kernel(KeySource k, IncB
 }
 
 // ---------------------------------------------------------------------------
-// tail: all remaining rounds in one cooperative launch
+// tail: small rounds in one cooperative launch, down to stop_at vertices
 // ---------------------------------------------------------------------------
 
 // Rounds round0 .. round_cap of one call: color phase, barrier, detect phase,

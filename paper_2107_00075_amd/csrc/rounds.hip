@@ -10,7 +10,8 @@
 //            uncolored).  Only T is read.  Winners commit C[v] = T[v] in
 //            place; losers are appended to W_{r+1} by ballot/prefix
 //            compaction.
-// Committed neighbours never tie: T[u] == C[u] for them and T[v] avoids every
+// Committed neighbours never tie: T[u] == C[u] for them (or 0, if they
+// committed in a first round without tentative colors) and T[v] avoids every
 // committed neighbour color, so reading T of all neighbours equals reading T
 // of the worklist neighbours only.  Neither kernel reads what it writes, so
 // the round is exactly the synchronous (snapshot) round.
@@ -29,9 +30,9 @@
 // arrive picks the color or commits (the edge-split parallelism that the
 // paper's edge-based kernel provides for very high degrees, Section 3.2).
 // Light bins are cut into chunks of worklist entries that workgroups take
-// by a static XCD-aware partition (no device atomics on the hot path; one
-// atomic per chunk appends the chunk's losers); heavy units are taken
-// dynamically from a device counter afterwards.
+// by a static XCD-aware partition (no device atomics on the hot path but one
+// per several hundred losers of a workgroup, to append them); heavy units are
+// taken dynamically from a device counter afterwards.
 #include <algorithm>
 #include <climits>
 

@@ -64,6 +64,20 @@ hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, F, int, size_t) 
 }
 inline hipError_t hipGetLastError() { return hipSuccess; }
 
+// Under ThreadSanitizer (-fsanitize=thread) device-scope accesses are atomic
+// but order nothing: it then reports every access inside a launch that is
+// neither device-scope nor ordered by a barrier of its workgroup.
+#ifdef __SANITIZE_THREAD__
+#include <sanitizer/tsan_interface.h>
+#define EMU_ORDER __ATOMIC_RELAXED
+#define EMU_FENCE ((void)0)
+#define EMU_TSAN(x) x
+#else
+#define EMU_ORDER __ATOMIC_SEQ_CST
+#define EMU_FENCE __atomic_thread_fence(__ATOMIC_SEQ_CST)
+#define EMU_TSAN(x)
+#endif
+
 extern "C" void emu_switch(void** save, void* load);
 #ifdef EMU_MAIN
 asm(R"(
@@ -104,6 +118,7 @@ enum State { kRun, kWaveOp, kBarrier, kSpin, kDone };
 
 struct Fiber {
   void* sp = nullptr;
+  EMU_TSAN(void* tsan = nullptr;)
   State state = kRun;
   int line = 0;                // source line and
   const char* site = nullptr;  // call site of the wavefront operation it waits in
@@ -114,6 +129,7 @@ struct Group {  // a workgroup
   std::vector<Fiber> fibers;
   char* stacks = nullptr;
   void* main_sp = nullptr;
+  EMU_TSAN(void* tsan = nullptr;)
   int cur = 0;
   int barrier_or = 0, barrier_result = 0;
   uint64_t snap[kLanes];  // what the active lanes of the running wavefront posted
@@ -133,6 +149,7 @@ inline void yield_to_main(State s) {
   Group& g = *g_group;
   Fiber& f = g.fibers[g.cur];
   f.state = s;
+  EMU_TSAN(__tsan_switch_to_fiber(g.tsan, 0);)
   emu_switch(&f.sp, g.main_sp);
 }
 
@@ -160,6 +177,7 @@ inline void run_wave(Group& g, int first, int last) {
       if (f.state != kRun) continue;
       g.cur = i;
       threadIdx.x = static_cast<unsigned>(i);
+      EMU_TSAN(__tsan_switch_to_fiber(f.tsan, 0);)
       emu_switch(&g.main_sp, f.sp);
     }
     bool spin = false;  // the lanes meet again behind a polling loop
@@ -208,7 +226,19 @@ struct Stacks {
     p = nullptr;
     n = 0;
   }
+#ifdef __SANITIZE_THREAD__
+  std::vector<void*> tsan;
+  void* fiber(int i) {
+    while (static_cast<int>(tsan.size()) <= i) tsan.push_back(__tsan_create_fiber(0));
+    return tsan[i];
+  }
+  ~Stacks() {
+    for (void* f : tsan) __tsan_destroy_fiber(f);
+    drop();
+  }
+#else
   ~Stacks() { drop(); }
+#endif
 };
 inline thread_local Stacks t_stacks;
 
@@ -217,6 +247,7 @@ inline void run_group(dim3 grid, dim3 block, unsigned index, const std::function
   const int n = static_cast<int>(block.x);
   g.fibers.resize(n);
   g.stacks = t_stacks.of(n);
+  EMU_TSAN(g.tsan = __tsan_get_current_fiber();)
   g.body = &body;
   g_group = &g;
   gridDim = grid;
@@ -230,6 +261,7 @@ inline void run_group(dim3 grid, dim3 block, unsigned index, const std::function
     *--top = reinterpret_cast<void*>(entry);
     for (int r = 0; r < 6; ++r) *--top = nullptr;
     g.fibers[i].sp = top;
+    EMU_TSAN(g.fibers[i].tsan = t_stacks.fiber(i);)
   }
   std::mt19937_64 rng(seed * 1000003u + index);
   const int waves = (n + kLanes - 1) / kLanes;
@@ -541,10 +573,10 @@ EMU_OP int emu_dpp(int old, int x, int ctrl, int row_mask, bool zero, EMU_LINE) 
   (__builtin_popcount((m) & (emu::lane() <= 32 ? 0u : (1u << (emu::lane() - 32)) - 1u)) + (add))
 // lanes hand data to each other through LDS here: every lane has to arrive
 #define __builtin_amdgcn_wave_barrier() emu::post(0, __LINE__)
-#define __builtin_amdgcn_fence(order, scope) __atomic_thread_fence(__ATOMIC_SEQ_CST)
+#define __builtin_amdgcn_fence(order, scope) EMU_FENCE
 #define __builtin_amdgcn_s_waitcnt(x) ((void)0)
 #define __builtin_amdgcn_s_sleep(x) emu::yield_to_main(emu::kSpin)
-inline void __threadfence() { __atomic_thread_fence(__ATOMIC_SEQ_CST); }
+inline void __threadfence() { EMU_FENCE; }
 inline int __popc(unsigned x) { return __builtin_popcount(x); }
 inline int __popcll(unsigned long long x) { return __builtin_popcountll(x); }
 inline long long wall_clock64() {  // 100 MHz
@@ -552,33 +584,33 @@ inline long long wall_clock64() {  // 100 MHz
 }
 
 #define __HIP_MEMORY_SCOPE_AGENT 0
-#define __hip_atomic_load(p, order, scope) __atomic_load_n(p, __ATOMIC_SEQ_CST)
-#define __hip_atomic_store(p, v, order, scope) __atomic_store_n(p, v, __ATOMIC_SEQ_CST)
-#define __hip_atomic_exchange(p, v, order, scope) __atomic_exchange_n(p, v, __ATOMIC_SEQ_CST)
-#define __hip_atomic_fetch_add(p, v, order, scope) __atomic_fetch_add(p, v, __ATOMIC_SEQ_CST)
+#define __hip_atomic_load(p, order, scope) __atomic_load_n(p, EMU_ORDER)
+#define __hip_atomic_store(p, v, order, scope) __atomic_store_n(p, v, EMU_ORDER)
+#define __hip_atomic_exchange(p, v, order, scope) __atomic_exchange_n(p, v, EMU_ORDER)
+#define __hip_atomic_fetch_add(p, v, order, scope) __atomic_fetch_add(p, v, EMU_ORDER)
 template <typename T>
-T atomicAdd(T* p, std::common_type_t<T> v) { return __atomic_fetch_add(p, v, __ATOMIC_SEQ_CST); }
+T atomicAdd(T* p, std::common_type_t<T> v) { return __atomic_fetch_add(p, v, EMU_ORDER); }
 template <typename T>
-T atomicOr(T* p, std::common_type_t<T> v) { return __atomic_fetch_or(p, v, __ATOMIC_SEQ_CST); }
+T atomicOr(T* p, std::common_type_t<T> v) { return __atomic_fetch_or(p, v, EMU_ORDER); }
 template <typename T>
-T atomicAnd(T* p, std::common_type_t<T> v) { return __atomic_fetch_and(p, v, __ATOMIC_SEQ_CST); }
+T atomicAnd(T* p, std::common_type_t<T> v) { return __atomic_fetch_and(p, v, EMU_ORDER); }
 template <typename T>
-T atomicExch(T* p, std::common_type_t<T> v) { return __atomic_exchange_n(p, v, __ATOMIC_SEQ_CST); }
+T atomicExch(T* p, std::common_type_t<T> v) { return __atomic_exchange_n(p, v, EMU_ORDER); }
 template <typename T>
 T atomicCAS(T* p, std::common_type_t<T> cmp, std::common_type_t<T> v) {
-  __atomic_compare_exchange_n(p, &cmp, v, false, __ATOMIC_SEQ_CST, __ATOMIC_SEQ_CST);
+  __atomic_compare_exchange_n(p, &cmp, v, false, EMU_ORDER, EMU_ORDER);
   return cmp;
 }
 template <typename T>
 T atomicMax(T* p, std::common_type_t<T> v) {
-  T old = *p;
-  while (old < v && !__atomic_compare_exchange_n(p, &old, v, false, __ATOMIC_SEQ_CST, __ATOMIC_SEQ_CST)) {}
+  T old = __atomic_load_n(p, EMU_ORDER);
+  while (old < v && !__atomic_compare_exchange_n(p, &old, v, false, EMU_ORDER, EMU_ORDER)) {}
   return old;
 }
 template <typename T>
 T atomicMin(T* p, std::common_type_t<T> v) {
-  T old = *p;
-  while (v < old && !__atomic_compare_exchange_n(p, &old, v, false, __ATOMIC_SEQ_CST, __ATOMIC_SEQ_CST)) {}
+  T old = __atomic_load_n(p, EMU_ORDER);
+  while (v < old && !__atomic_compare_exchange_n(p, &old, v, false, EMU_ORDER, EMU_ORDER)) {}
   return old;
 }
 using std::max;
