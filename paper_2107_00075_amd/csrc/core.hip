@@ -122,6 +122,19 @@ __device__ __forceinline__ uint32_t core_word(const IncBufs& b, int32_t v, int32
   return w <= b.fw_off[v + 1] - w0 ? b.Fx[w0 + w - 1] : 0u;
 }
 
+// Adds color c to v's forbidden bitset, which only the calling thread reads
+// from here on.
+__device__ __forceinline__ void core_forbid(const IncBufs& b, int32_t v, int32_t c) {
+  const int32_t w = (c - 1) >> 5;
+  const uint32_t bit = 1u << ((c - 1) & 31);
+  if (w == 0) {
+    b.F[v] |= bit;
+    return;
+  }
+  const int32_t w0 = b.fw_off[v];
+  if (w <= b.fw_off[v + 1] - w0) b.Fx[w0 + w - 1] |= bit;  // (beyond: a color v can never take)
+}
+
 // Smallest color >= c that v's forbidden bitset does not hold.
 __device__ __forceinline__ int32_t core_free_from(const IncBufs& b, int32_t v, int32_t c) {
   while (true) {
@@ -855,22 +868,28 @@ struct SmallShared {
   // per lane (rows padded so that neighbouring slots start on other banks)
   alignas(16) uint64_t a[kCoreSlots][kCoreWaves + 2];
   alignas(16) uint64_t c[kWave][kCoreWaves + 2];
+  alignas(16) uint64_t w[kCoreWaves];      // phase B without slots: commits to take in
   int32_t t[kSmallMax];                    // tentative color, or minus the committed one
   int32_t gmin[2], gmax[2], total[2];
 };
 
 // The one-workgroup stage: a thread per vertex, its row of 1024 bits in
-// registers, the slot masks in LDS.  Rounds whose tentative colors span more
-// than their slots compare the colors of the row's vertices one by one.
+// registers, the slot masks in LDS.  While the tentative colors span at most
+// kCoreSlots, a slot holds one color; beyond, the colors that share the slot
+// are told apart by the entries of sh.t that the row meets in it.
 //
-// What the stage's vertices have committed is in the slots only (fw and the
-// bitset hold what was committed before), and a loser tests every color it
-// steps over up to `top`, the largest tentative color of any round so far: no
+// What the stage's vertices have committed is in slots too (fw and the bitset
+// hold what was committed before), and a loser tests every color it steps
+// over up to `top`, the largest tentative color of any round so far: no
 // committed color of the stage is above it.  The largest tentative color of
-// the round will not do, as it falls when its holders commit.  All committed
-// colors that still matter, gmin .. top, have slots while these span at most
-// kWave colors (a slot's color leaves the window only below gmin, which never
-// falls); else the next first fit compares colors one by one too.
+// the round will not do, as it falls when its holders commit.  The committed
+// colors that still matter, gmin .. top, have a slot each while they span at
+// most kWave colors (a slot is cleared when its color has fallen below gmin,
+// which never falls itself).  In rounds beyond that every loser takes its
+// neighbours' new commits into its window, or past that into its own bitset,
+// instead.  (1000 vertices of mean degree 800 over 300 initial colors, 53
+// rounds: 1.2 ms a call; with the colors of the whole row compared for every
+// step 63 ms, in the tail kernel 1.9 ms.)
 __device__ __forceinline__ CoreEnd core_small(const IncBufs& b, const CoreSet& in, int32_t n, int& r, int round_cap,
                                               SmallShared& sh) {
   constexpr int R = kSmallMax / 64;
@@ -880,7 +899,7 @@ __device__ __forceinline__ CoreEnd core_small(const IncBufs& b, const CoreSet& i
   const int32_t v = have ? ld_dev(&in.v[tid]) : -1;
   int32_t t = have ? ld_dev(&in.t[tid]) : 1;
   const int32_t fb = t;
-  const uint64_t fw = have ? ld_dev(&in.fw[tid]) : 0ull;
+  uint64_t fw = have ? ld_dev(&in.fw[tid]) : 0ull;
   uint64_t row[R], near = 0;
 #pragma unroll
   for (int p = 0; p < R; ++p) {
@@ -896,7 +915,8 @@ __device__ __forceinline__ CoreEnd core_small(const IncBufs& b, const CoreSet& i
   bool act = have;
   uint64_t comm = 0;
   int32_t comm_c = 0;
-  bool comm_ok = true;
+  bool comm_ok = true;  // comm holds every commit so far of the colors it stands for
+  bool fw_ok = true;    // the losers' windows and bitsets hold every commit so far
   int32_t top = 0;
   CoreEnd end = kCoreDone;
   __syncthreads();
@@ -948,8 +968,8 @@ __device__ __forceinline__ CoreEnd core_small(const IncBufs& b, const CoreSet& i
     bool wins = false;
     if (on) {
       bool hit = false;
+      const uint64_t* m = sh.a[t & (kCoreSlots - 1)];
       if (fast) {
-        const uint64_t* m = sh.a[t & (kCoreSlots - 1)];
         uint64_t y = near & m[wave];
 #pragma unroll
         for (int p = 0; p < R; ++p)
@@ -958,7 +978,7 @@ __device__ __forceinline__ CoreEnd core_small(const IncBufs& b, const CoreSet& i
       } else if (act) {
 #pragma unroll
         for (int p = 0; p < R; ++p)
-          for (uint64_t y = p < wave ? row[p] : p == wave ? near : 0ull; y && !hit; y &= y - 1ull)
+          for (uint64_t y = (p < wave ? row[p] : p == wave ? near : 0ull) & m[p]; y && !hit; y &= y - 1ull)
             hit = sh.t[64 * p + __builtin_ctzll(y)] == t;
       }
       wins = act && !hit;
@@ -980,7 +1000,6 @@ __device__ __forceinline__ CoreEnd core_small(const IncBufs& b, const CoreSet& i
           const uint64_t m = __ballot(won != 0 && t == cs);
           if (lane == s) comm = m;
         }
-        comm_ok = true;
       } else {
         if (comm_c != c) comm = 0;
         uint64_t rem = ws;
@@ -994,27 +1013,37 @@ __device__ __forceinline__ CoreEnd core_small(const IncBufs& b, const CoreSet& i
       comm_c = c;
       sh.c[lane][wave] = comm;
     } else {
-      comm_ok = false;
+      // rounds with slots came before: their commits as well
+      const uint64_t all = __ballot(won != 0);
+      if (lane == 0) sh.w[wave] = fw_ok ? ws : all;
     }
+    comm_ok = slots;
+    fw_ok = !slots;
     __syncthreads();
     // ---- next first fit
-    if (act) {
+    if (act && slots) {
       while (t <= top) {
-        bool hit = false;
-        if (slots) {
-          const uint64_t* m = sh.c[t & (kWave - 1)];
-          uint64_t y = 0;
+        const uint64_t* m = sh.c[t & (kWave - 1)];
+        uint64_t y = 0;
 #pragma unroll
-          for (int p = 0; p < R; ++p) y |= row[p] & m[p];
-          hit = y != 0ull;
-        } else {
-#pragma unroll
-          for (int p = 0; p < R; ++p)
-            for (uint64_t y = row[p]; y && !hit; y &= y - 1ull) hit = sh.t[64 * p + __builtin_ctzll(y)] == -t;
-        }
-        if (!hit) break;
+        for (int p = 0; p < R; ++p) y |= row[p] & m[p];
+        if (y == 0ull) break;
         t = core_next(b, v, t, fb, fw);
       }
+    } else if (act) {
+      uint64_t y[R];
+#pragma unroll
+      for (int p = 0; p < R; ++p) y[p] = row[p] & sh.w[p];
+#pragma unroll
+      for (int p = 0; p < R; ++p) {
+        for (; y[p]; y[p] &= y[p] - 1ull) {
+          const int32_t c = -sh.t[64 * p + __builtin_ctzll(y[p])];
+          if (c < t) continue;
+          if (c - fb < 64) fw |= 1ull << (c - fb);
+          else core_forbid(b, v, c);
+        }
+      }
+      t = core_next(b, v, t - 1, fb, fw);
     }
     if (!slots) __syncthreads();  // every committed color has been read
   }

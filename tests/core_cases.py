@@ -88,4 +88,4 @@ def beside(g, prio, n: int, seed: int):
 CLIMBS = [(20, 4, 4), (20, 4, 7), (7, 4, 4), (1, 4, 4), (0, 4, 4), (60, 12, 15), (60, 30, 40), (60, 33, 40),
           (80, 40, 45), (40, 100, 20), (100, 70, 80)]
 ANCHORED = [(8, 0.7, 24), (40, 0.5, 24), (150, 0.3, 24), (150, 0.5, 40), (300, 0.2, 24), (300, 0.4, 150),
-            (700, 0.2, 60), (1000, 0.3, 150)]
+            (700, 0.2, 60), (1000, 0.3, 150), (250, 0.8, 300), (120, 0.9, 700)]
