@@ -781,7 +781,7 @@ int run_incremental(Call& c, const GraphView& g, const KeySource& k, const int32
   bool tail_on = !(c.P.flags & COLOR_FLAG_NO_TAIL) && tail_blocks_resident() > 0;
   const int64_t tail_at = c.P.tail_threshold > 0 ? c.P.tail_threshold : kTailDefault;
   // worklists of at most core_at vertices go to the core kernels
-  const int64_t core_at = std::min<int64_t>(
+  int64_t core_at = std::min<int64_t>(
       tail_at, core_capacity(std::min(core_blocks_resident(), std::max(8, c.P.max_workgroups))));
   // (a fixed workspace that has no room for their scratch: the tail kernel then
   // runs all the rounds, in one launch)
@@ -828,8 +828,12 @@ int run_incremental(Call& c, const GraphView& g, const KeySource& k, const int32
             core_on = tail_on = false;
             continue;
           }
-          if (bits) {  // kErrCoreWindow
-            core_on = false;  // it changed nothing: the tail kernel runs the rounds
+          if (bits) {
+            // kErrCoreWindow: it changed nothing, and the tail kernel runs the
+            // rounds until one workgroup can take them (3000 vertices with colors
+            // spread over 150: 1.74 ms a call with all rounds in the tail kernel)
+            core_on = core_at > kCoreSmall;
+            core_at = kCoreSmall;
             continue;
           }
           c.tail_rounds += std::max(0, H->rounds_done - round0 - local);

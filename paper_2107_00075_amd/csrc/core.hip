@@ -39,7 +39,8 @@
 //    span few colors (at most 10 on R-MAT, power-law and dense random graphs
 //    of every size tried); if they ever span more than the slots, every
 //    workgroup sees it in the same round's summary words and the launch ends
-//    having written nothing, and the rounds go on in the tail kernel.
+//    having written nothing, and the rounds go on in the tail kernel, down to
+//    the one-workgroup stage, which takes any spread.
 //  * As the worklist shrinks, the rows are compacted to the vertices left
 //    (core_stage's hand-over): at 4096 vertices to 64 workgroups with 128-word
 //    rows, at 1024 to one workgroup, a thread per vertex, which needs no
@@ -62,7 +63,7 @@ constexpr int kRankPer = 128;           // vertices numbered by one workgroup
 constexpr int kRankChunk = 4096;        // keys staged in LDS at a time
 constexpr int32_t kCoreMaxColor = 1 << 20;  // tentative colors a summary word can carry
 constexpr int32_t kMidMax = kCoreMid;   // vertices of the second stage
-constexpr int32_t kSmallMax = 1024;     // vertices of the one-workgroup stage
+constexpr int32_t kSmallMax = kCoreSmall;  // vertices of the one-workgroup stage
 
 // Row words (stride of the row array) of a stage over n vertices.
 __host__ __device__ constexpr int32_t row_words(int32_t n) {

@@ -8,12 +8,14 @@ namespace gcol {
 
 constexpr int kCoreSlots = 32;          // color classes in flight: the spread of the tentative colors
 constexpr int32_t kCoreMax = 24576;     // vertices: 96 per workgroup, one workgroup on each of 256 CUs
+constexpr int32_t kCoreMid = 4096;    // above: two cooperative launches
+constexpr int32_t kCoreSmall = 1024;  // up to here: one workgroup, which takes any spread of the colors
 constexpr int32_t kErrCoreWindow = 0x400;  // error bit: the tentative colors spread over more than kCoreSlots colors
 constexpr int32_t kErrCoreHanded = 0x800;  // (no error) the wide stage has written colors and handed over
 
 // Vertices a launch of `blocks` workgroups can take.
 inline int32_t core_capacity(int blocks) {
-  return blocks >= 256 ? kCoreMax : blocks >= 64 ? 64 * blocks : blocks > 0 ? 1024 : 0;
+  return blocks >= 256 ? kCoreMax : blocks >= 64 ? 64 * blocks : blocks > 0 ? kCoreSmall : 0;
 }
 
 // Bytes of the scratch one launch over n vertices needs: the vertices in key
@@ -34,7 +36,6 @@ int core_blocks_resident();
 bool launch_core(const KeySource& k, const IncBufs& b, const BinLayout& L, const int32_t cnt[kBins], int32_t n,
                  bool split, int round0, int round_cap, void* scratch, uint32_t* bar, int32_t* err, int32_t* left,
                  int32_t checkin_us, hipStream_t st);
-constexpr int32_t kCoreMid = 4096;  // above: two cooperative launches
 inline int core_launches(int32_t n) { return n > kCoreMid ? 4 : 3; }
 
 }  // namespace gcol
